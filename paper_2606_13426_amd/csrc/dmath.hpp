@@ -32,49 +32,46 @@ __device__ inline double erfcx_pos(double y) {
   return fma(2.0 * p, inv, kInvSqrtPi) * inv;
 }
 
-// log(1 - e^r) for r < 0 as log(-expm1(r)): exact to rounding near 0, and an
-// absolute error of about e^r (harmless in sums of logs) far below it.
-__device__ inline double log1mexp(double r) { return log(-expm1(r)); }
-
-__device__ inline double logaddexp(double a, double b) {
-  const double m = fmax(a, b);
-  if (m == -INFINITY) return -INFINITY;
-  return m + log(exp(a - m) + exp(b - m));
-}
-
-// log(alpha Phi(x) - Phi(x - v)) for x <= u* = log(alpha)/v + v/2, v > 0
-// (the mass below x of the unnormalised residual law, Alg. 7), from
-// e1 = erfcx(|x|/sqrt 2) and e2 = erfcx((v - x)/sqrt 2) (v - x >= v/2 > 0):
-//   log Phi(x)     = log(e1/2) - x^2/2             for x <= 0,
-//                  = log1p(-(e1/2) e^{-x^2/2})     for x > 0,
-//   log Phi(x - v) = log(e2/2) - (x - v)^2/2,
-// and the log-ratio r = log Phi(x - v) - log Phi(x) - log alpha, which for
-// x <= 0 is log(e2/e1) + v (x - u*): the quadratic terms cancel exactly, so r
-// keeps its digits far into the left tail where both log-CDFs are ~ -x^2/2.
-// The result is log alpha + log Phi(x) + log(1 - e^r).
-__device__ inline double log_excess(double x, double la, double v) {
+// The mass below x of the unnormalised residual law (Alg. 7),
+//   alpha Phi(x) - Phi(x - v),  x <= u* = log(alpha)/v + v/2, v > 0,
+// from e1 = erfcx(|x|/sqrt 2), e2 = erfcx((v - x)/sqrt 2) (v - x >= v/2 > 0)
+// and the density ratio E = phi(x - v) / (alpha phi(x)) = e^{v (x - u*)} <= 1:
+//   x <= 0: alpha e^{-x^2/2} (e1 - e2 E) / 2   (the common factor e^{-x^2/2}
+//           stands outside, so the digits survive far into the left tail),
+//   x > 0:  alpha (1 - e^{-x^2/2} (e1 + e2 E) / 2).
+// Three transcendentals in all: a sum of logs of the two CDFs with log1p and
+// expm1 takes six and is no more accurate (both lose the digits of e1 - e2 E
+// when v is small).
+//
+// mass_terms returns the factor in brackets (with the 1/2) and x^2/2.
+__device__ inline double mass_terms(double x, double la, double v, double* hx2) {
   const double us = la / v + 0.5 * v;
   const double e1 = erfcx_pos(fabs(x) * kSqrt1_2);
-  const double e2 = erfcx_pos((v - x) * kSqrt1_2);
-  const double l1 = log(0.5 * e1), l2 = log(0.5 * e2);
-  const double hx2 = 0.5 * x * x;
-  const double right = log1p(-0.5 * e1 * exp(-hx2));
-  const bool left = x <= 0.0;
-  const double lphi = left ? l1 - hx2 : right;
-  const double xv = x - v;
-  const double r = left ? (l2 - l1) + v * (x - us) : (l2 - 0.5 * xv * xv) - lphi - la;
-  return la + lphi + log1mexp(fmin(r, -0.0));
+  const double e2 = erfcx_pos((v - x) * kSqrt1_2) * exp(fmin(v * (x - us), 0.0));
+  *hx2 = 0.5 * x * x;
+  return fmax(x <= 0.0 ? 0.5 * (e1 - e2) : fma(-0.5 * exp(-*hx2), e1 + e2, 1.0), 0.0);
 }
 
-// log h_j of block verification for j < K_b from log alpha_j and
-// ||Delta_{j+1}||: h = v/(v + 1 - alpha), v = alpha Phi(u*) - Phi(u* - ||D||).
-// alpha = 1 gives h = 1; ||Delta_{j+1}|| = 0 with alpha < 1 gives h = 0.
-__device__ inline double block_log_h(double la, double vnext) {
+// log(alpha Phi(x) - Phi(x - v)).
+__device__ inline double log_excess(double x, double la, double v) {
+  double hx2;
+  const double m = mass_terms(x, la, v, &hx2);
+  return la + (x <= 0.0 ? -hx2 : 0.0) + log(m);
+}
+
+// h_j of block verification for j < K_b from log alpha_j and ||Delta_{j+1}||:
+// h = w/(w + 1 - alpha), w = alpha Phi(u*) - Phi(u* - ||D||), where E = 1.
+// alpha = 1 gives h = 1; ||Delta_{j+1}|| = 0 with alpha < 1 gives h = 0.  A w
+// that underflows gives 0, far below the smallest coin (2^-25).
+__device__ inline double block_h(double la, double vnext) {
   const bool pos = vnext > 0.0;
   const double vs = pos ? vnext : 1.0;
-  const double lv = log_excess(la / vs + 0.5 * vs, la, vs);
-  const double lh = lv - logaddexp(lv, log1mexp(fmin(la, -0.0)));
-  return la >= 0.0 ? 0.0 : pos ? lh : -INFINITY;
+  double hx2;
+  const double us = la / vs + 0.5 * vs;
+  const double m = mass_terms(us, la, vs, &hx2);
+  const double w = m * exp(us <= 0.0 ? la - hx2 : la);
+  const double h = w / (w - expm1(la));
+  return la >= 0.0 ? 1.0 : pos ? h : 0.0;
 }
 
 }  // namespace sd

@@ -11,11 +11,9 @@
 // scan_kernel: one wavefront per chain, lane j-1 owns draft step j (K <= 64).
 // Every lane replays the prefix recursion log alpha_j = min(0, log alpha_{j-1}
 // + ell_j) in the same order as the definition, evaluates its h_j, draws its
-// coin, and a ballot gives tau.  U is found by inverting Psi_alpha: the
-// doubling of Alg. 7 is done for all 64 candidate lower ends at once (lane i
-// tests u* - 2^i), and the bisection becomes a 64-way multisection that
-// shrinks the bracket 65-fold per step until it is 1e-8 (relative) wide, then
-// a linear interpolation of log Psi inside it (see usample_exact).
+// coin, and a ballot gives tau.  U is found by inverting Psi_alpha on all 64
+// lanes at once (usample_exact): a grid over the law's bulk, then a window
+// around the cubic inverse interpolant, usually two passes.
 //
 // Both scans take the temperature as w2 = omega^2 (the tempered
 // verifications of the appendix divide every ell_j by omega^2), and the
@@ -111,87 +109,126 @@ __device__ __forceinline__ double log_cdf(double x, double la, double v, double 
   return log_excess(x, la, v) - Lstar;
 }
 
-// Inverse of Psi_alpha at u, with all 64 lanes of the wavefront: the doubling
-// of Alg. 7 for 63 candidate lower ends at once (lane i tests u* - 2^i), then
-// a 64-way multisection (lane i evaluates log Psi at the i+1-th of 65
-// points).  After the second and later multisection passes the four points
-// around the crossing (the pass's points and the bracket's ends) give the
-// cubic inverse interpolant of log Psi at log u; it is taken when it lies in
-// the new bracket and agrees with both quadratic interpolants to 1e-13
-// (relative), i.e. where log Psi is smooth on the scale of the points --
-// typically after the second or third pass.  Otherwise the multisection goes
-// on until the bracket is 1e-8 (relative) wide and a linear interpolation of
-// log Psi between its ends, whose values the lanes already hold, closes it:
-// its error is far below the bracket width except next to u*, where the
-// density vanishes (there it is at most the width).
-__device__ double usample_exact(double u, double la, double v, int lane) {
+// The value of lane i (wavefront-uniform), by a scalar lane read.
+__device__ __forceinline__ double lane_value(double v, int i) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, i);
+  const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), i);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// x at g from four points (x_q, g_q): the cubic interpolant, and in *err the
+// larger distance to the quadratics through the first and the last three.
+__device__ __forceinline__ double cubic_at(const double (&px)[4], const double (&pg)[4], double g,
+                                           double* err) {
+  const double r01 = 1.0 / (pg[0] - pg[1]), r02 = 1.0 / (pg[0] - pg[2]), r03 = 1.0 / (pg[0] - pg[3]);
+  const double r12 = 1.0 / (pg[1] - pg[2]), r13 = 1.0 / (pg[1] - pg[3]), r23 = 1.0 / (pg[2] - pg[3]);
+  const double d0 = g - pg[0], d1 = g - pg[1], d2 = g - pg[2], d3 = g - pg[3];
+  const double x3 = px[0] * (d1 * d2 * d3) * (r01 * r02 * r03) - px[1] * (d0 * d2 * d3) * (r01 * r12 * r13) +
+                    px[2] * (d0 * d1 * d3) * (r02 * r12 * r23) - px[3] * (d0 * d1 * d2) * (r03 * r13 * r23);
+  const double q0 = px[0] * (d1 * d2) * (r01 * r02) - px[1] * (d0 * d2) * (r01 * r12) +
+                    px[2] * (d0 * d1) * (r02 * r12);
+  const double q1 = px[1] * (d2 * d3) * (r12 * r13) - px[2] * (d1 * d3) * (r12 * r23) +
+                    px[3] * (d1 * d2) * (r13 * r23);
+  *err = fmax(fabs(x3 - q0), fabs(x3 - q1));
+  return x3;
+}
+
+// Inverse of Psi_alpha at u (log u given), with all 64 lanes of the wavefront.
+// In the coordinate g = sqrt(-log Psi) the inverse is nearly linear: next to
+// u*, where 1 - Psi vanishes quadratically, and far in the left tail.  Pass 1
+// evaluates a uniform grid of 63 points over the bulk of the law (and the
+// normaliser on lane 63): down from min(u*, 6.5) (Psi there is 1 within the
+// coin's resolution) to where Psi is below the smallest uniform, 2^-25 (the
+// Gaussian tail below m = max(0, -u*) reaches e^-22 at sqrt(m^2 + 44) - m).
+// Pass 2 puts 64 points into a window around the cubic inverse interpolant of
+// the four points about the crossing, eight times as wide as its distance to
+// the quadratics.  A pass is accepted when the crossing lies inside its points
+// and cubic and quadratics agree to 1e-13 (relative): two passes for 97 % of
+// u uniform, log alpha in [-6, 0], v in [1e-3, 300] (a doubling pass and a
+// multisection on log Psi took four or five).  Otherwise the window shrinks
+// again about the new interpolant, or the bracket is cut into 65, until the
+// bracket is 1e-8 (relative) wide and a linear interpolation of log Psi closes
+// it (next to u* only, where the density vanishes).
+__device__ double usample_exact(double logu, double la, double v, int lane) {
   const double us = la / v + 0.5 * v;
-  const double logu = log(u);
-  // one pass: lanes 0..62 the doubling candidates u* - 2^i, lane 63 the
-  // normaliser log(alpha Phi(u*) - Phi(u* - v))
-  const double le = log_excess(lane < 63 ? us - ldexp(1.0, lane) : us, la, v);
-  const double Lstar = __shfl(le, 63);
-  const double fc = le - Lstar;
-  const uint64_t above = __ballot(lane < 63 && fc > logu) | (1ull << 63);
-  const int p = (~above == 0ull) ? 63 : (__ffsll((unsigned long long)~above) - 1);
-  double lo = us - ldexp(1.0, p), flo = p < 63 ? __shfl(fc, p < 63 ? p : 0) : -INFINITY;
-  double hi = p == 0 ? us : us - ldexp(1.0, p - 1), fhi = p == 0 ? 0.0 : __shfl(fc, p > 0 ? p - 1 : 0);
+  const double gt = sqrt(-logu);
+  const double top = fmin(us, 6.5), m = fmax(0.0, -us);
+  const double span = sqrt(fma(m, m, 44.0)) - m + fmax(top, 0.0);
+  double x = lane < 63 ? top - span * ((double)(62 - lane) / 62.0) : us;
+  double fx = log_excess(x, la, v);
+  const double Lstar = lane_value(fx, 63);
+  fx = x >= us ? 0.0 : fmin(fx - Lstar, 0.0);
+  int cnt = __popcll(__ballot(lane < 63 && fx < logu));
+  double lo, flo, hi = us, fhi = 0.0;
+  if (cnt == 0) {
+    // below the grid (a uniform at its smallest values): double the distance
+    hi = lane_value(x, 0);
+    fhi = lane_value(fx, 0);
+    const double xd = us - ldexp(us - hi, lane + 1);
+    const double fd = fmin(log_excess(xd, la, v) - Lstar, 0.0);
+    const uint64_t below = __ballot(fd < logu) | (1ull << 63);
+    const int p = __builtin_amdgcn_readfirstlane(__ffsll((unsigned long long)below) - 1);
+    lo = lane_value(xd, p);
+    flo = lane_value(fd, p);
+    if (p > 0) {
+      hi = lane_value(xd, p - 1);
+      fhi = lane_value(fd, p - 1);
+    }
+  } else {
+    cnt = __builtin_amdgcn_readfirstlane(cnt);
+    lo = lane_value(x, cnt - 1);
+    flo = lane_value(fx, cnt - 1);
+    if (cnt < 63) {
+      hi = lane_value(x, cnt);
+      fhi = lane_value(fx, cnt);
+    }
+  }
+  bool centred = cnt > 0 && cnt < 63;  // the last points hold the crossing
+  int top_lane = 62;                   // their last lane
   for (int it = 0; it < 64; ++it) {
-    const double mid = 0.5 * (lo + hi);
-    if (!(mid > lo && mid < hi) || hi - lo <= 1e-8 * fmax(1.0, fabs(lo))) break;
-    const double x = lo + (hi - lo) * ((double)(lane + 1) / 65.0);
-    const double fx = log_cdf(x, la, v, us, Lstar);
-    const uint64_t below = __ballot(fx < logu);
-    const int cnt = __popcll(below);
-    const double nlo = __shfl(x, cnt > 0 ? cnt - 1 : 0), nflo = __shfl(fx, cnt > 0 ? cnt - 1 : 0);
-    const double nhi = __shfl(x, cnt < 64 ? cnt : 63), nfhi = __shfl(fx, cnt < 64 ? cnt : 63);
-    // the points in order: e = 0 the bracket's low end, e = i + 1 lane i's
-    // point, e = 65 its high end; the crossing lies between e = cnt and cnt + 1
-    const int e0 = min(max(cnt - 1, 0), 62);
-    double px[4], pf[4];  // points and their log Psi, increasing
+    double blo = lo, bhi = hi;
+    if (centred) {
+      const int e0 = min(max(cnt - 2, 0), top_lane - 3);
+      double px[4], pg[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int e = e0 + q;
-      const int src = min(max(e - 1, 0), 63);
-      const double sx = __shfl(x, src), sf = __shfl(fx, src);
-      px[q] = e == 0 ? lo : e == 65 ? hi : sx;
-      pf[q] = e == 0 ? flo : e == 65 ? fhi : sf;
+      for (int q = 0; q < 4; ++q) {
+        px[q] = lane_value(x, e0 + q);
+        pg[q] = sqrt(-lane_value(fx, e0 + q));
+      }
+      double err;
+      const double xc = cubic_at(px, pg, gt, &err);
+      if (it > 0 && err <= 1e-13 * fmax(1.0, fabs(xc)) && xc >= lo && xc <= hi) return xc;
+      const double w = fmax(8.0 * err, 1e-7 * span);
+      if (isfinite(xc) && isfinite(w) && xc - w < hi && xc + w > lo) {
+        blo = fmax(lo, xc - w);
+        bhi = fmin(hi, xc + w);
+      }
     }
-    // (after the first pass the points are still too far apart to pass the test)
-    if (it > 0 && isfinite(pf[0]) && isfinite(pf[3]) && pf[0] < pf[1] && pf[1] < pf[2] &&
-        pf[2] < pf[3]) {
-      // Lagrange weights in log Psi at log u, from the six reciprocal differences
-      const double r01 = 1.0 / (pf[0] - pf[1]), r02 = 1.0 / (pf[0] - pf[2]), r03 = 1.0 / (pf[0] - pf[3]);
-      const double r12 = 1.0 / (pf[1] - pf[2]), r13 = 1.0 / (pf[1] - pf[3]), r23 = 1.0 / (pf[2] - pf[3]);
-      const double d0 = logu - pf[0], d1 = logu - pf[1], d2 = logu - pf[2], d3 = logu - pf[3];
-      const double x3 = px[0] * (d1 * d2 * d3) * (r01 * r02 * r03) - px[1] * (d0 * d2 * d3) * (r01 * r12 * r13) +
-                        px[2] * (d0 * d1 * d3) * (r02 * r12 * r23) - px[3] * (d0 * d1 * d2) * (r03 * r13 * r23);
-      const double q0 = px[0] * (d1 * d2) * (r01 * r02) - px[1] * (d0 * d2) * (r01 * r12) +
-                        px[2] * (d0 * d1) * (r02 * r12);
-      const double q1 = px[1] * (d2 * d3) * (r12 * r13) - px[2] * (d1 * d3) * (r12 * r23) +
-                        px[3] * (d1 * d2) * (r13 * r23);
-      const double blo = cnt > 0 ? nlo : lo, bhi = cnt < 64 ? nhi : hi;
-      if (fmax(fabs(x3 - q0), fabs(x3 - q1)) <= 1e-13 * fmax(1.0, fabs(x3)) && x3 >= blo && x3 <= bhi)
-        return x3;
-    }
+    const double mid = 0.5 * (lo + hi);
+    if (!(mid > lo && mid < hi) || hi - lo <= 1e-8 * fmin(span, fmax(1.0, fabs(lo)))) break;
+    x = blo + (bhi - blo) * ((double)lane / 63.0);
+    fx = x >= us ? 0.0 : fmin(log_excess(x, la, v) - Lstar, 0.0);
+    cnt = __builtin_amdgcn_readfirstlane(__popcll(__ballot(fx < logu)));
     if (cnt > 0) {
-      lo = nlo;
-      flo = nflo;
+      lo = lane_value(x, cnt - 1);
+      flo = lane_value(fx, cnt - 1);
     }
     if (cnt < 64) {
-      hi = nhi;
-      fhi = nfhi;
+      hi = lane_value(x, cnt);
+      fhi = lane_value(fx, cnt);
     }
+    centred = cnt > 0 && cnt < 64;
+    top_lane = 63;
   }
   const double t = fhi > flo ? (logu - flo) / (fhi - flo) : 0.5;
   return lo + (hi - lo) * fmin(fmax(t, 0.0), 1.0);
 }
 
 // The capped doubling/bisection of the paper's experiments (3 + 4 steps).
-__device__ double usample_paper(double u, double la, double v) {
+__device__ double usample_paper(double u, double logu, double la, double v) {
   const double us = la / v + 0.5 * v;
   const double Lstar = log_excess(us, la, v);
-  const double logu = log(u);
   double hi = us, lo = us - 1.0;
   for (int n = 0; n < 3 && log_cdf(lo, la, v, us, Lstar) > logu; ++n) lo = hi - 2.0 * (hi - lo);
   double mid = 0.5 * (lo + hi);
@@ -225,27 +262,39 @@ struct Decision {
 // it, so such decisions are counted.
 constexpr double kTieWindow = 1e-6;
 
-__device__ Decision decide(int mode, int umode, int kb, double ell_raw, double vn, uint32_t b,
-                           uint32_t r, uint64_t seed, int lane, double w2, bool need_u) {
+// The uniforms of one chain's decision, drawn ahead of its log-ratios: the
+// coin of this lane's draft step and the U draw's uniform (with its log).
+struct Draws {
+  double eta, u, logu;
+};
+
+__device__ __forceinline__ Draws draw_uniforms(uint32_t b, uint32_t r, uint64_t seed, int lane) {
+  const uint4 w = philox((uint32_t)(lane >> 2), b, r, TAG_COIN << 24, seed);
+  const uint4 wu = philox(0u, b, r, TAG_USAMPLE << 24, seed);
+  const double u = uniform64(wu.x);
+  return Draws{uniform64(pick(w, lane & 3)), u, log(u)};
+}
+
+__device__ Decision decide(int mode, int umode, int kb, double ell_raw, double vn, const Draws& dr,
+                           int lane, double w2, bool need_u) {
   const bool valid = lane < kb;
   const double ell = ell_raw / w2;
   // prefix recursion, replayed per lane in the definition's order
   double acc = 0.0, la = 0.0;
   for (int i = 0; i < kb; ++i) {
-    const double e = __shfl(ell, i);
-    acc = fmin(0.0, acc + e);
+    acc = fmin(0.0, acc + lane_value(ell, i));
     if (i == lane) la = acc;
   }
   const double vnext = __shfl_down(vn, 1);
-  double lh;
-  if (mode == SD_BLOCK)
-    lh = (lane + 1 < kb) ? block_log_h(la, vnext) : la;
-  else
-    lh = fmin(0.0, ell);
-  const uint4 w = philox((uint32_t)(lane >> 2), b, r, TAG_COIN << 24, seed);
-  const double eta = uniform64(pick(w, lane & 3));
-  const uint64_t cm = __ballot(valid && log(eta) < lh);
-  const uint64_t tm = __ballot(valid && fabs(eta - exp(lh)) <= kTieWindow);
+  double h;
+  if (mode == SD_BLOCK) {
+    h = block_h(la, vnext);
+    if (lane + 1 >= kb) h = exp(la);
+  } else {
+    h = exp(fmin(0.0, ell));
+  }
+  const uint64_t cm = __ballot(valid && dr.eta < h);
+  const uint64_t tm = __ballot(valid && fabs(dr.eta - h) <= kTieWindow);
   const uint64_t vmask = kb >= 64 ? ~0ull : ((1ull << kb) - 1ull);
   int t;
   if (mode == SD_BLOCK) {
@@ -254,19 +303,17 @@ __device__ Decision decide(int mode, int umode, int kb, double ell_raw, double v
     const uint64_t rej = ~cm & vmask;
     t = rej ? __ffsll((unsigned long long)rej) : kb + 1;
   }
-  const double la_prev = __shfl(la, t >= 2 ? t - 2 : 0);
-  const double la_res = (mode == SD_BLOCK && t >= 2) ? la_prev : 0.0;
+  t = __builtin_amdgcn_readfirstlane(t);
+  const double la_res = (mode == SD_BLOCK && t >= 2) ? lane_value(la, t - 2) : 0.0;
   double U = NAN;
   if (t <= kb && need_u) {
-    const double v = __shfl(vn, t - 1);  // > 0: a rejection never lands on a zero offset
-    const uint4 wu = philox(0u, b, r, TAG_USAMPLE << 24, seed);
-    const double u = uniform64(wu.x);
+    const double v = lane_value(vn, t - 1);  // > 0: a rejection never lands on a zero offset
     if (umode == SD_USAMPLE_PAPER) {
       double up = 0.0;
-      if (lane == 0) up = usample_paper(u, la_res, v);
-      U = __shfl(up, 0);
+      if (lane == 0) up = usample_paper(dr.u, dr.logu, la_res, v);
+      U = lane_value(up, 0);
     } else {
-      U = usample_exact(u, la_res, v, lane);
+      U = usample_exact(dr.logu, la_res, v, lane);
     }
   }
   return Decision{t, la_res, U, cm, tm};
@@ -295,9 +342,10 @@ __global__ __launch_bounds__(kThreads) void scan_kernel(
   const bool valid = lane < kb;
   const double ell = valid ? lr[(int64_t)b * K + lane] : 0.0;
   const double vn = valid ? dn[(int64_t)b * K + lane] : 0.0;
+  const Draws dr = draw_uniforms((uint32_t)b, rnd[b], seed, lane);
   if (nanflag && __ballot(valid && !(isfinite(ell) && isfinite(vn))) != 0ull && lane == 0)
     atomicOr(nanflag, 1);
-  const Decision D = decide(mode, umode, kb, ell, vn, (uint32_t)b, rnd[b], seed, lane, w2, true);
+  const Decision D = decide(mode, umode, kb, ell, vn, dr, lane, w2, true);
   if (lane == 0) {
     tau[b] = D.tau;
     lar[b] = D.la_res;
@@ -319,8 +367,12 @@ __global__ __launch_bounds__(kThreads) void scan_kernel(
 //            whose two sums are the log-ratio partials of row tau - 1)
 // The round's decision record (tau, coins, log alpha_res, U) is kept per chain,
 // and the coins within kTieWindow of their thresholds are added to ties[b].
-// It also clears the next round's active flag before looking at its gate,
-// and stores the gate (whether any chain was still active after the previous
+// One workgroup per chain sums the partials with all four wavefronts; the
+// first one then decides.  The kernel's time is one chain's latency: pixel3072
+// (1024 chains in two groups) 23.8 -> 16.7 us per launch, 8 chains of the same
+// size 20.5 -> 10.2, against one wavefront per chain with the earlier U draw.
+// The workgroup after the last chain clears the next round's active flag and
+// stores the gate (whether any chain was still active after the previous
 // round) tagged with that round's index, (pub_round << 1) | flag, into
 // host_prev, a word of mapped host memory that the host polls, so that
 // neither a device-to-host copy nor an event is queued per round.
@@ -332,38 +384,37 @@ __global__ __launch_bounds__(kThreads) void scan_fused_kernel(
     float* __restrict__ rcoef, float* __restrict__ rsig, uint64_t* __restrict__ coins,
     double* __restrict__ lar, double* __restrict__ ures, int32_t* __restrict__ ties,
     int* nanflag, int* act_next, int* host_prev, int pub_round, const int* gate, int chain0) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    *act_next = 0;
-    if (host_prev) {
-      __atomic_store_n(host_prev, (pub_round << 1) | (gate ? *gate : 1), __ATOMIC_RELAXED);
-      __threadfence_system();
-    }
-  }
-  if (gate && *gate == 0) return;
-  const int lane = threadIdx.x & 63;
-  const int b = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
-  if (b >= B) return;
-  const int K1 = K + 1;
-  const int k = kcur[b];
-  const int kb = k < N ? min(K, N - k) : 0;
-  if (kb <= 0) {
-    if (lane == 0) {
-      tau[b] = 0;
-      rmode[b] = 0;
+  if ((int)blockIdx.x == B) {  // the extra workgroup: no chain waits for its system-scope store
+    if (threadIdx.x == 0) {
+      *act_next = 0;
+      if (host_prev) {
+        __atomic_store_n(host_prev, (pub_round << 1) | (gate ? *gate : 1), __ATOMIC_RELAXED);
+        __threadfence_system();
+      }
     }
     return;
   }
-  const bool valid = lane < kb;
+  // every input of the chain is requested before the first one is used (the
+  // gate among them): one trip to memory instead of a chain of them
+  const int lane = threadIdx.x & 63;
+  const int b = blockIdx.x, K1 = K + 1;
+  const int k = kcur[b];
+  const uint32_t r = rcur[b];
+  // sigma of rows 0..K_b (lane j holds row j); the residual's sigma is taken
+  // from these lanes below instead of a second load
+  double sgl = lane <= K ? sigma[(int64_t)b * K1 + lane] : 1.0;
+  const int live = gate ? *gate : 1;
   // Sum the column-tile partials of each draft row: row j is spread over lpr
-  // lanes (64 / K rounded up to a power of two), each lane takes every lpr-th
-  // tile with four independent accumulators (loads in flight together), and
-  // the lanes of a row combine in a fixed xor tree; then lane j fetches row
-  // j's totals.  Fixed order throughout, so the sums are deterministic.
-  int kp = 1;
+  // of the 256 lanes (256 / K rounded down to a power of two, at most 64),
+  // each lane takes every lpr-th tile with four independent accumulators
+  // (loads in flight together), and the lanes of a row combine in a fixed xor
+  // tree; then lane j of the first wavefront reads row j's totals.  Fixed
+  // order throughout, so the sums are deterministic.
+  int kp = 4;
   while (kp < K) kp <<= 1;
-  const int lpr = 64 / kp, j = lane / lpr, sub = lane % lpr;
+  const int lpr = kThreads / kp, j = threadIdx.x / lpr, sub = threadIdx.x % lpr;
   double a2[4] = {0.0, 0.0, 0.0, 0.0}, az[4] = {0.0, 0.0, 0.0, 0.0}, ag[4] = {0.0, 0.0, 0.0, 0.0};
-  if (j < kb) {
+  if (j < K) {
     const double* pl = lrp + ((int64_t)b * K1 + j) * nct * 3;
     int ct = sub;
     for (; ct + 3 * lpr < nct; ct += 4 * lpr) {
@@ -375,11 +426,24 @@ __global__ __launch_bounds__(kThreads) void scan_fused_kernel(
         ag[u] += q[2];
       }
     }
-    for (; ct < nct; ct += lpr) {
-      a2[0] += pl[3 * ct];
-      az[0] += pl[3 * ct + 1];
-      ag[0] += pl[3 * ct + 2];
+#pragma unroll
+    for (int u = 0; u < 3; ++u) {
+      if (ct + u * lpr < nct) {
+        const double* q = pl + 3 * (ct + u * lpr);
+        a2[u] += q[0];
+        az[u] += q[1];
+        ag[u] += q[2];
+      }
     }
+  }
+  if (live == 0) return;
+  const int kb = k < N ? min(K, N - k) : 0;
+  if (kb <= 0) {
+    if (threadIdx.x == 0) {
+      tau[b] = 0;
+      rmode[b] = 0;
+    }
+    return;
   }
   double s2 = (a2[0] + a2[1]) + (a2[2] + a2[3]);
   double sz = (az[0] + az[1]) + (az[2] + az[3]);
@@ -389,33 +453,38 @@ __global__ __launch_bounds__(kThreads) void scan_fused_kernel(
     sz += __shfl_xor(sz, o);
     sgd += __shfl_xor(sgd, o);
   }
-  const int src = min(lane * lpr, 63);
-  s2 = __shfl(s2, src);
-  sz = __shfl(sz, src);
-  sgd = __shfl(sgd, src);
-  // sigma of rows 0..K_b (lane j holds row j); the residual's sigma is taken
-  // from these lanes below instead of a second load
-  const double sgl = lane <= kb ? sigma[(int64_t)b * K1 + lane] : 1.0;
+  __shared__ double sums[SD_MAX_BLOCK][3];
+  if (sub == 0 && j < K) {
+    sums[j][0] = s2;
+    sums[j][1] = sz;
+    sums[j][2] = sgd;
+  }
+  __syncthreads();
+  if (threadIdx.x >= 64) return;  // one wavefront decides
+  const Draws dr = draw_uniforms((uint32_t)(chain0 + b), r, seed, lane);
+  const bool valid = lane < kb;
+  s2 = valid ? sums[lane][0] : 0.0;
+  sz = valid ? sums[lane][1] : 0.0;
+  sgd = valid ? sums[lane][2] : 0.0;
+  if (lane > kb) sgl = 1.0;
   const double sg = valid ? sgl : 1.0;
   const double inv = 1.0 / (sg * sg);
   const double vn = valid ? sqrt(s2 * inv) : 0.0;
   const double ell = valid ? -sz * inv - 0.5 * s2 * inv : 0.0;
   if (__ballot(valid && !(isfinite(ell) && isfinite(vn))) != 0ull && lane == 0) atomicOr(nanflag, 1);
-  const uint32_t r = rcur[b];
-  const Decision D = decide(mode, umode, kb, ell, vn, (uint32_t)(chain0 + b), r, seed, lane, w2,
-                            !reflect);
+  const Decision D = decide(mode, umode, kb, ell, vn, dr, lane, w2, !reflect);
   const int t = D.tau;
   int rm;
   float cf = 0.f, sgo = 0.f;
-  const double st = __shfl(sgl, t <= kb ? t - 1 : kb);
-  const double s2t = __shfl(s2, t <= kb ? t - 1 : 0), szt = __shfl(sz, t <= kb ? t - 1 : 0);
+  const double st = lane_value(sgl, t <= kb ? t - 1 : kb);
+  const double s2t = lane_value(s2, t <= kb ? t - 1 : 0), szt = lane_value(sz, t <= kb ? t - 1 : 0);
   if (t <= kb && reflect) {
     // D.D > 0: a rejection never lands on a zero offset (kept as a guard)
     rm = 4;
     cf = s2t > 0.0 ? (float)(1.0 + 2.0 * szt / s2t) : 1.0f;
   } else if (t <= kb) {
-    const double v = __shfl(vn, t - 1);
-    const double eG = __shfl(sgd, t - 1) / (st * v);
+    const double v = lane_value(vn, t - 1);
+    const double eG = lane_value(sgd, t - 1) / (st * v);
     rm = 1;
     cf = (float)((D.U - eG) / v);
     sgo = (float)st;
@@ -469,8 +538,7 @@ hipError_t scan_fused_launch(int B, int K, int d, int N, int mode, int umode, co
                              uint64_t* coins, double* lar, double* ures, int32_t* ties,
                              int* nanflag, int* act_next, int* host_prev, int pub_round,
                              hipStream_t s, const int* gate, int chain0) {
-  const int per = kThreads / 64;
-  return launch_timed("scan_fused", scan_fused_kernel, dim3((B + per - 1) / per), dim3(kThreads), s,
+  return launch_timed("scan_fused", scan_fused_kernel, dim3(B + 1), dim3(kThreads), s,
                       B, K, d, N, mode, umode, lrp, nct, sigma, kcur, rcur, seed, w2, reflect, tau,
                       rmode, rcoef, rsig, coins, lar, ures, ties, nanflag, act_next, host_prev,
                       pub_round, gate, chain0);
