@@ -232,6 +232,7 @@ sd_status sd_target_create(const sd_schedule* sched, int32_t d, int32_t n_comp, 
             hipMalloc(&t->ls, sizeof(double2) * M * (size_t)sched->n_steps) == hipSuccess &&
             hipMalloc(&t->logw, sizeof(double) * M) == hipSuccess &&
             hipMalloc(&t->musq, sizeof(double) * M) == hipSuccess &&
+            hipMalloc(&t->sig, sizeof(double) * (size_t)(sched->n_steps + 1)) == hipSuccess &&
             hipMalloc(&t->coef, sizeof(float4) * (size_t)(sched->n_steps + 1)) == hipSuccess;
   if (!ok) {
     set_error("sd_target_create: device allocation failed");
@@ -295,13 +296,16 @@ sd_status sd_target_create(const sd_schedule* sched, int32_t d, int32_t n_comp, 
   ok = ok && hipMemcpy(t->ls, ls.data(), sizeof(double2) * ls.size(), hipMemcpyHostToDevice) ==
                  hipSuccess;
   std::vector<float4> coef((size_t)sched->n_steps + 1);
+  std::vector<double> sig((size_t)sched->n_steps + 1);
   for (int n = 0; n <= sched->n_steps; ++n) {
+    sig[n] = sched_signal(t->sc, n);
     const double c2 = sched_c2(t->sc, n);
     coef[n] = make_float4((float)sched_c1(t->sc, n), (float)c2, (float)sched_sigma(t->sc, n),
                           (float)(1.0 / c2));
   }
   ok = ok && hipMemcpy(t->coef, coef.data(), sizeof(float4) * coef.size(), hipMemcpyHostToDevice) ==
-                 hipSuccess;
+                 hipSuccess &&
+       hipMemcpy(t->sig, sig.data(), sizeof(double) * sig.size(), hipMemcpyHostToDevice) == hipSuccess;
   if (!ok) {
     set_error("sd_target_create: copy to device failed");
     sd_target_destroy(reinterpret_cast<sd_target>(t));
@@ -323,6 +327,7 @@ sd_status sd_target_destroy(sd_target target) {
   if (t->ls) (void)hipFree(t->ls);
   if (t->logw) (void)hipFree(t->logw);
   if (t->musq) (void)hipFree(t->musq);
+  if (t->sig) (void)hipFree(t->sig);
   if (t->coef) (void)hipFree(t->coef);
   // a flag group still held by a call that timed out may be written by its
   // kernels later: that memory and those side streams are then left alone

@@ -101,6 +101,7 @@ struct Target {
   uint16_t* muT_split;  // [3][d][M]
   double* logw;   // [M]
   double* musq;   // [M] ||mu_m||^2 (float64 from the float32 means)
+  double* sig;    // [N+1] signal level a_n
   float4* coef;   // [N+1] per step: (c1_n, c2_n, sigma_n, 1/c2_n) rounded to float32
   double2* ls;    // [N][M] per step and component: (log s2, 1/s2), s2 = a_n^2 var_m + 1 - a_n^2
   int device;
@@ -157,8 +158,9 @@ hipError_t target_mean_lr_bf16_launch(const Target& t, int rows, int K1, const f
 int lr_tiles_bf16(const Target& t, int K1);
 // Softmax over the split logits partials part[S][rows][M] (+ xsq[S][rows]):
 // P[rows][M] = r a / s2 (float32, or bf16 when p_bf16) and rowc[rows][3] =
-// (c1, c2, rho) of each row's step.
-hipError_t gmm_softmax_launch(const Target& t, int rows, int S, const float* part,
+// (c1, c2, rho) of each row's step; plan_rows: the whole batch's rows, which
+// fix the order of the sums.
+hipError_t gmm_softmax_launch(const Target& t, int rows, int plan_rows, int S, const float* part,
                               const double* xsq, const int32_t* step, void* P, bool p_bf16,
                               float* rowc, hipStream_t s, const int* gate);
 // Sampler verification on the fused partials (see scan_fused_kernel).

@@ -28,6 +28,7 @@
 #include "philox.hpp"
 #include "rows.hpp"
 #include "rowsum.hpp"
+#include "wavered.hpp"
 
 namespace sd {
 namespace {
@@ -36,7 +37,6 @@ constexpr int kThreads = 256;
 constexpr int TILE = 64;
 constexpr int KC = 64;
 constexpr int LDW = KC + 4;  // LDS row stride in floats (16-byte aligned rows)
-constexpr int kFuseSoftmaxMaxM = 256;  // up to this many components the last split does the softmax
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
@@ -293,229 +293,143 @@ __global__ __launch_bounds__(kThreads, 2) void gmm_logits_split_kernel(
   }
 }
 
-// One wavefront per row.  With the per-(step, component) table
+// Softmax over a row's components.  With the per-(step, component) table
 // ls[n][m] = (log s2, 1/s2):
 //   logit_m = log w_m - (d/2) log s2 - (||x||^2 - 2 a x.mu_m + a^2 ||mu_m||^2) / (2 s2)
-// in float64 (kept in registers, up to kMaxPer per lane), then one max
-// reduction, one exp per component and one sum reduction.
-constexpr int kMaxPer = 16;  // components per lane held in registers (M <= 1024)
-
-template <class TP>
-__global__ __launch_bounds__(kThreads) void gmm_softmax_kernel(
+// in float64, then one maximum, one exp per component, and the sums of
+// e_m and e_m / s2_m (rho is their ratio).
+//
+// The kernel is a chain of dependent latencies (step -> tables -> reductions).
+// SPREAD, for few rows, spreads a row as wide as it goes: a wavefront takes 64
+// components; lane 16 q + l first sums the split partials s = q, q + 4, .. of
+// the components 4 l .. 4 l + 3 of its wavefront (all in flight together), and
+// a reduce-scatter over q leaves each lane one component.  Otherwise, where
+// the wavefronts' own instructions are the limit, a lane keeps all splits of
+// four components and a wavefront takes 256.  NW wavefronts hold a row; every
+// input that does not hang on the step is requested at the start; lane l < S
+// sums ||x||^2.  The maximum is only a shift, so it is taken in float32.
+// Per launch (rocprofv3), against one kernel of four components per lane with
+// LDS-permute reductions and the splits summed serially: 64 rows x 64
+// components of 24 splits 12.3 -> 4.7 us, 72 rows 11.9 -> 4.7, 4608 rows 11.9
+// -> 9.3, 777 rows x 100 8.8 -> 5.7, 2304 x 1024 (66 MB of partials) 18.5 ->
+// 18.0.
+template <int NW, bool SPREAD, bool QUAD, class TP>
+__global__ __launch_bounds__(NW > 4 ? 64 * NW : kThreads) void gmm_softmax_kernel(
     int R, int M, int d, int S, const float* __restrict__ part, const double* __restrict__ xsq,
-    const int32_t* __restrict__ step, Sched sc, const double2* __restrict__ ls,
+    const int32_t* __restrict__ step, const double* __restrict__ sig, const double2* __restrict__ ls,
     const double* __restrict__ logw, const double* __restrict__ musq, const float4* __restrict__ coef,
     TP* __restrict__ P, float* __restrict__ rowc, const int* gate) {
-  if (gate && *gate == 0) return;
-  const int lane = threadIdx.x & 63;
-  const int row = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
-  if (row >= R) return;
-  const int n = step[row];
-  const double a = sched_signal(sc, n), a2 = a * a;
-  const double2* lsn = ls + (int64_t)n * M;
+  constexpr int kT = NW > 4 ? 64 * NW : kThreads, RPW = kT / (64 * NW);
+  constexpr int NC = SPREAD ? 1 : 4, DS = SPREAD ? 4 : 1;  // components per lane, split stride
+  const int lane = threadIdx.x & 63, w = (threadIdx.x >> 6) % NW;
+  const int row = blockIdx.x * RPW + (int)(threadIdx.x >> 6) / NW;
+  const bool on = row < R;
+  const int rr = on ? row : R - 1;  // wavefronts of a missing row follow the last one (no stores)
+  const int live = gate ? *gate : 1;
+  const int n = step[rr];
+  const int q = SPREAD ? lane >> 4 : 0, l = SPREAD ? lane & 15 : lane;
+  // the quad summed, and the first component kept (SPREAD: lane bits 5 and 4
+  // select it after the reduce-scatter)
+  const int m0 = (SPREAD ? 64 : 256) * w + 4 * l, m = m0 + q;
+  double lw[NC], mq2[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const int mc = min(m + c, M - 1);
+    lw[c] = logw[mc];
+    mq2[c] = musq[mc];
+  }
   double xs = 0.0;
-  for (int s = 0; s < S; ++s) xs += xsq[(int64_t)s * R + row];
-  const double hd = 0.5 * (double)d;
-  // the split partials of x.mu_m, split by split so that the loads of one
-  // split (one per component of this lane) are in flight together
-  double lg[kMaxPer];
+  for (int s = lane; s < S; s += 64) xs += xsq[(int64_t)s * R + rr];
+  double dot[4] = {0.0, 0.0, 0.0, 0.0};
+  if (m0 < M) {
+    const float* pr = part + (int64_t)rr * M + m0;
+#pragma unroll 8
+    for (int s = q; s < S; s += DS) {
+      const float* ps = pr + (int64_t)s * R * M;
+      if constexpr (QUAD) {
+        const float4 v = *reinterpret_cast<const float4*>(ps);
+        dot[0] += (double)v.x;
+        dot[1] += (double)v.y;
+        dot[2] += (double)v.z;
+        dot[3] += (double)v.w;
+      } else {
 #pragma unroll
-  for (int i = 0; i < kMaxPer; ++i) lg[i] = 0.0;
-  for (int s = 0; s < S; ++s) {
-    const float* ps = part + ((int64_t)s * R + row) * M;
-#pragma unroll
-    for (int i = 0; i < kMaxPer; ++i) {
-      const int m = lane + 64 * i;
-      if (m < M) lg[i] += (double)ps[m];
+        for (int c = 0; c < 4; ++c) dot[c] += (double)ps[m0 + c < M ? c : 0];
+      }
     }
   }
-  double mx = -INFINITY;
+  const double a = sig[n];
+  double2 t[NC];
 #pragma unroll
-  for (int i = 0; i < kMaxPer; ++i) {
-    const int m = lane + 64 * i;
-    if (m < M) {
-      const double2 t = lsn[m];
-      lg[i] = logw[m] - hd * t.x - 0.5 * (xs - 2.0 * a * lg[i] + a2 * musq[m]) * t.y;
-      mx = fmax(mx, lg[i]);
-    } else {
-      lg[i] = -INFINITY;
-    }
+  for (int c = 0; c < NC; ++c) t[c] = ls[(int64_t)n * M + min(m + c, M - 1)];
+  const float4 cf = coef[n];
+  if (live == 0) return;
+  xs = wave_sum(xs);
+  if constexpr (SPREAD) {
+    const double d02 = swap_add<true>(dot[0], dot[2]), d13 = swap_add<true>(dot[1], dot[3]);
+    dot[0] = swap_add<false>(d02, d13);
   }
+  double lg[NC];
+  float mx = -INFINITY;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
-  float e[kMaxPer];
-  float sum = 0.0f;
-#pragma unroll
-  for (int i = 0; i < kMaxPer; ++i) {
-    e[i] = lane + 64 * i < M ? __expf((float)(lg[i] - mx)) : 0.0f;
-    sum += e[i];
+  for (int c = 0; c < NC; ++c) {
+    lg[c] = lw[c] - 0.5 * (double)d * t[c].x - 0.5 * (xs - 2.0 * a * dot[c] + a * a * mq2[c]) * t[c].y;
+    if (m + c < M) mx = fmaxf(mx, (float)lg[c]);
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-  const double inv = 1.0 / (double)sum;
-  double rho = 0.0;
-#pragma unroll
-  for (int i = 0; i < kMaxPer; ++i) {
-    const int m = lane + 64 * i;
-    if (m < M) {
-      const double rm = (double)e[i] * inv;
-      const double is2 = lsn[m].y;
-      const float pm = (float)(rm * a * is2);
-      if constexpr (sizeof(TP) == 2)
-        P[(int64_t)row * M + m] = __builtin_bit_cast(uint16_t, (__bf16)pm);
-      else
-        P[(int64_t)row * M + m] = pm;
-      rho += rm * is2;
-    }
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) rho += __shfl_xor(rho, o);
-  if (lane == 0) {
-    const float4 cf = coef[n];
-    rowc[3 * (int64_t)row + 0] = cf.x;
-    rowc[3 * (int64_t)row + 1] = cf.y;
-    rowc[3 * (int64_t)row + 2] = (float)rho;
-  }
-}
-
-// The softmax for M % 4 == 0, M <= 4 G: a row is spread over G lanes (G a
-// power of two, 16 .. 256) with four consecutive components per lane, so
-// every per-component input is one 16-byte load per lane (one per split for
-// the logit partials) and a workgroup holds 256 / G rows.  Arithmetic as in
-// gmm_softmax_kernel; the max, then the normaliser sum_m e_m together with
-// sum_m e_m / s2_m (rho is their ratio), are reduced over the G lanes
-// (shuffles within a wavefront, then LDS across the wavefronts of a row).
-template <int G>
-__device__ __forceinline__ double group_reduce(double v, bool is_max, double* red) {
-  constexpr int W = G < 64 ? G : 64;
-#pragma unroll
-  for (int o = W / 2; o > 0; o >>= 1) {
-    const double u = __shfl_xor(v, o);
-    v = is_max ? fmax(v, u) : v + u;
-  }
-  if constexpr (G > 64) {
-    constexpr int NW = G / 64;  // wavefronts per row: the row's are w0 .. w0 + NW - 1
-    const int w = threadIdx.x >> 6, w0 = w - w % NW;
-    __syncthreads();  // the previous use of red is complete
-    if ((threadIdx.x & 63) == 0) red[w] = v;
+  __shared__ float redm[kT / 64];
+  __shared__ double2 reds[kT / 64];
+  mx = wave_max(mx);
+  const int w0 = (int)(threadIdx.x >> 6) - w;  // the row's first wavefront
+  if constexpr (NW > 1) {
+    if (lane == 0) redm[w0 + w] = mx;
     __syncthreads();
-    v = red[w0];
 #pragma unroll
-    for (int i = 1; i < NW; ++i) v = is_max ? fmax(v, red[w0 + i]) : v + red[w0 + i];
+    for (int i = 0; i < NW; ++i) mx = fmaxf(mx, redm[w0 + i]);
   }
-  return v;
-}
-
-// Both sums of v over the G lanes of a row, as group_reduce.
-template <int G>
-__device__ __forceinline__ double2 group_sum2(double2 v, double* red) {
-  constexpr int W = G < 64 ? G : 64;
+  float e[NC];
+  double sum = 0.0, sis = 0.0;
 #pragma unroll
-  for (int o = W / 2; o > 0; o >>= 1) {
-    v.x += __shfl_xor(v.x, o);
-    v.y += __shfl_xor(v.y, o);
+  for (int c = 0; c < NC; ++c) {
+    e[c] = m + c < M ? __expf((float)(lg[c] - (double)mx)) : 0.0f;
+    sum += (double)e[c];
+    sis += (double)e[c] * t[c].y;
   }
-  if constexpr (G > 64) {
-    constexpr int NW = G / 64;
-    const int w = threadIdx.x >> 6, w0 = w - w % NW;
-    __syncthreads();  // the previous use of red is complete
-    if ((threadIdx.x & 63) == 0) {
-      red[2 * w] = v.x;
-      red[2 * w + 1] = v.y;
-    }
+  sum = wave_sum(sum);
+  sis = wave_sum(sis);
+  if constexpr (NW > 1) {
+    if (lane == 0) reds[w0 + w] = make_double2(sum, sis);
     __syncthreads();
-    v = make_double2(red[2 * w0], red[2 * w0 + 1]);
+    sum = reds[w0].x;
+    sis = reds[w0].y;
 #pragma unroll
     for (int i = 1; i < NW; ++i) {
-      v.x += red[2 * (w0 + i)];
-      v.y += red[2 * (w0 + i) + 1];
+      sum += reds[w0 + i].x;
+      sis += reds[w0 + i].y;
     }
   }
-  return v;
-}
-
-template <int G, class TP>
-__global__ __launch_bounds__(kThreads) void gmm_softmax_quad_kernel(
-    int R, int M, int d, int S, const float* __restrict__ part, const double* __restrict__ xsq,
-    const int32_t* __restrict__ step, Sched sc, const double2* __restrict__ ls,
-    const double* __restrict__ logw, const double* __restrict__ musq, const float4* __restrict__ coef,
-    TP* __restrict__ P, float* __restrict__ rowc, const int* gate) {
-  static_assert(G >= 16 && G <= kThreads && (G & (G - 1)) == 0, "G: a power of two in 16..256");
-  if (gate && *gate == 0) return;
-  __shared__ double red[2 * (kThreads / 64)];
-  constexpr int RPW = kThreads / G;
-  const int gl = threadIdx.x % G;
-  const int row = blockIdx.x * RPW + (int)threadIdx.x / G;
-  const bool on = row < R;
-  const int rr = on ? row : R - 1;  // lanes of a missing row follow the last one (no stores)
-  const int m0 = 4 * gl;
-  const bool has = m0 < M;
-  const int mc = has ? m0 : 0;  // loads of lanes past M read component 0 (unused)
-  // the partials first (independent of the step), then the step's tables
-  double dot[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll 8
-  for (int sp = 0; sp < S; ++sp) {
-    const float4 v = *reinterpret_cast<const float4*>(part + ((int64_t)sp * R + rr) * M + mc);
-    dot[0] += (double)v.x;
-    dot[1] += (double)v.y;
-    dot[2] += (double)v.z;
-    dot[3] += (double)v.w;
-  }
-  double xs = 0.0;
-#pragma unroll 8
-  for (int sp = 0; sp < S; ++sp) xs += xsq[(int64_t)sp * R + rr];
-  const int n = step[rr];
-  const double a = sched_signal(sc, n), a2 = a * a, hd = 0.5 * (double)d;
-  const double2* lsn = ls + (int64_t)n * M + mc;
-  double2 t[4];
+  const double inv = 1.0 / sum;
+  if (on && m < M) {
+    TP o[NC];
 #pragma unroll
-  for (int c = 0; c < 4; ++c) t[c] = lsn[c];
-  const double2 w01 = *reinterpret_cast<const double2*>(logw + mc);
-  const double2 w23 = *reinterpret_cast<const double2*>(logw + mc + 2);
-  const double2 q01 = *reinterpret_cast<const double2*>(musq + mc);
-  const double2 q23 = *reinterpret_cast<const double2*>(musq + mc + 2);
-  const double lw[4] = {w01.x, w01.y, w23.x, w23.y}, mq2[4] = {q01.x, q01.y, q23.x, q23.y};
-  double lg[4];
-  double mx = -INFINITY;
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    lg[c] = lw[c] - hd * t[c].x - 0.5 * (xs - 2.0 * a * dot[c] + a2 * mq2[c]) * t[c].y;
-    if (has) mx = fmax(mx, lg[c]);
-  }
-  mx = group_reduce<G>(mx, true, red);
-  float e[4];
-  float sum = 0.0f;
-  double sum_is2 = 0.0;
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    e[c] = has ? __expf((float)(lg[c] - mx)) : 0.0f;
-    sum += e[c];
-    sum_is2 += (double)e[c] * t[c].y;
-  }
-  const double2 tot = group_sum2<G>(make_double2((double)sum, sum_is2), red);
-  const double inv = 1.0 / tot.x;
-  const double rho = tot.y * inv;
-  float pm[4];
-#pragma unroll
-  for (int c = 0; c < 4; ++c) pm[c] = (float)((double)e[c] * inv * a * t[c].y);
-  if (on && has) {
-    if constexpr (sizeof(TP) == 2) {
-      uint2 pk;
-      pk.x = (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)pm[0]) |
-             ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)pm[1]) << 16);
-      pk.y = (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)pm[2]) |
-             ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)pm[3]) << 16);
-      *reinterpret_cast<uint2*>(P + (int64_t)row * M + m0) = pk;
+    for (int c = 0; c < NC; ++c) {
+      const float pm = (float)((double)e[c] * inv * a * t[c].y);
+      if constexpr (sizeof(TP) == 2)
+        o[c] = __builtin_bit_cast(uint16_t, (__bf16)pm);
+      else
+        o[c] = pm;
+    }
+    TP* pp = P + (int64_t)row * M + m;
+    if constexpr (NC == 4 && QUAD) {
+      struct alignas(4 * sizeof(TP)) Quad { TP v[4]; };
+      *reinterpret_cast<Quad*>(pp) = Quad{{o[0], o[1], o[2], o[3]}};
     } else {
-      *reinterpret_cast<float4*>(P + (int64_t)row * M + m0) = make_float4(pm[0], pm[1], pm[2], pm[3]);
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        if (m + c < M) pp[c] = o[c];
     }
   }
-  if (on && gl == 0) {
-    const float4 cf = coef[n];
-    rowc[3 * (int64_t)row + 0] = cf.x;
-    rowc[3 * (int64_t)row + 1] = cf.y;
-    rowc[3 * (int64_t)row + 2] = (float)rho;
-  }
+  if (on && w == 0 && lane < 3)
+    rowc[3 * (int64_t)row + lane] = lane == 0 ? cf.x : lane == 1 ? cf.y : (float)(sis * inv);
 }
 
 // O = P mu with the EM epilogue on float32 matrix instructions: the path for M
@@ -843,87 +757,8 @@ __global__ __launch_bounds__(kThreads) void gmm_mean_lr_kernel(
   }
 }
 
-// The softmax for M <= 64 (M % 4 == 0): sixteen lanes per row, four
-// components per lane read as one float4 per split, four rows per wavefront;
-// the same arithmetic as gmm_softmax_kernel with 16-lane reductions.
-__global__ __launch_bounds__(kThreads) void gmm_softmax_small_kernel(
-    int R, int M, int d, int S, const float* __restrict__ part, const double* __restrict__ xsq,
-    const int32_t* __restrict__ step, Sched sc, const double2* __restrict__ ls,
-    const double* __restrict__ logw, const double* __restrict__ musq, const float4* __restrict__ coef,
-    float* __restrict__ P, float* __restrict__ rowc, const int* gate) {
-  if (gate && *gate == 0) return;
-  const int q = threadIdx.x & 15;
-  const int row = blockIdx.x * (kThreads / 16) + (threadIdx.x >> 4);
-  const bool on = row < R;
-  const int rr = on ? row : R - 1;  // lanes of a missing row follow the last one (no stores)
-  const int n = step[rr];
-  const double a = sched_signal(sc, n), a2 = a * a, hd = 0.5 * (double)d;
-  double xs = 0.0;
-#pragma unroll 8
-  for (int sp = 0; sp < S; ++sp) xs += xsq[(int64_t)sp * R + rr];
-  const int m0 = 4 * q;
-  const bool has = m0 < M;
-  double dot[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll 8
-  for (int sp = 0; sp < S; ++sp) {
-    if (has) {
-      const float4 v = *reinterpret_cast<const float4*>(part + ((int64_t)sp * R + rr) * M + m0);
-      dot[0] += (double)v.x;
-      dot[1] += (double)v.y;
-      dot[2] += (double)v.z;
-      dot[3] += (double)v.w;
-    }
-  }
-  const double2* lsn = ls + (int64_t)n * M;
-  double lg[4];
-  double mx = -INFINITY;
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    lg[c] = -INFINITY;
-    if (has) {
-      const int m = m0 + c;
-      const double2 t = lsn[m];
-      lg[c] = logw[m] - hd * t.x - 0.5 * (xs - 2.0 * a * dot[c] + a2 * musq[m]) * t.y;
-      mx = fmax(mx, lg[c]);
-    }
-  }
-#pragma unroll
-  for (int o = 8; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
-  float e[4];
-  float sum = 0.0f;
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    e[c] = has ? __expf((float)(lg[c] - mx)) : 0.0f;
-    sum += e[c];
-  }
-#pragma unroll
-  for (int o = 8; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-  const double inv = 1.0 / (double)sum;
-  double rho = 0.0;
-  float pv[4];
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    pv[c] = 0.0f;
-    if (has) {
-      const double rm = (double)e[c] * inv;
-      const double is2 = lsn[m0 + c].y;
-      pv[c] = (float)(rm * a * is2);
-      rho += rm * is2;
-    }
-  }
-  if (on && has)
-    *reinterpret_cast<float4*>(P + (int64_t)row * M + m0) = make_float4(pv[0], pv[1], pv[2], pv[3]);
-#pragma unroll
-  for (int o = 8; o > 0; o >>= 1) rho += __shfl_xor(rho, o);
-  if (q == 0 && on) {
-    const float4 cf = coef[n];
-    rowc[3 * (int64_t)row + 0] = cf.x;
-    rowc[3 * (int64_t)row + 1] = cf.y;
-    rowc[3 * (int64_t)row + 2] = (float)rho;
-  }
-}
-
 struct Plan {
+  int rows;  // the rows the plan is for (the whole batch's, for a part of one)
   int S, ksplit;
   size_t off_part, off_xsq, off_p, off_rowc, total;
 };
@@ -953,6 +788,7 @@ Plan make_plan(const Target& t, int R, int plan_rows = 0) {
       best_per = per;
     }
   }
+  p.rows = Rp;
   p.ksplit = best_per * KC;
   p.S = (t.d + p.ksplit - 1) / p.ksplit;
   size_t off = 0;
@@ -991,47 +827,41 @@ size_t target_ws_bytes(const Target& t, int rows, int plan_rows) {
                            : make_plan(t, rows, plan_rows).total;
 }
 
-hipError_t gmm_softmax_launch(const Target& t, int R, int S, const float* part, const double* xsq,
+hipError_t gmm_softmax_launch(const Target& t, int R, int plan_rows, int S, const float* part, const double* xsq,
                               const int32_t* step, void* P, bool p_bf16, float* rowc,
                               hipStream_t s, const int* gate) {
-  if (!p_bf16 && t.M <= 64 && t.M % 4 == 0) {
-    const int nbs = (R + kThreads / 16 - 1) / (kThreads / 16);
-    return launch_timed("gmm_softmax", gmm_softmax_small_kernel, dim3(nbs), dim3(kThreads), s, R,
-                        t.M, t.d, S, part, xsq, step, t.sc, t.ls, t.logw, t.musq, t.coef,
-                        static_cast<float*>(P), rowc, gate);
-  }
-  if (t.M % 4 == 0 && t.M <= 4 * kThreads) {
-    // G lanes per row: the smallest power of two >= M / 4, at least 16
-    int g = 16;
-    while (4 * g < t.M) g <<= 1;
-    const int nbq = (R + kThreads / g - 1) / (kThreads / g);
-    auto launch = [&](auto gtag) {
-      constexpr int GG = decltype(gtag)::value;
-      if (p_bf16)
-        return launch_timed("gmm_softmax", gmm_softmax_quad_kernel<GG, uint16_t>, dim3(nbq),
-                            dim3(kThreads), s, R, t.M, t.d, S, part, xsq, step, t.sc, t.ls, t.logw,
-                            t.musq, t.coef, static_cast<uint16_t*>(P), rowc, gate);
-      return launch_timed("gmm_softmax", gmm_softmax_quad_kernel<GG, float>, dim3(nbq),
-                          dim3(kThreads), s, R, t.M, t.d, S, part, xsq, step, t.sc, t.ls, t.logw,
-                          t.musq, t.coef, static_cast<float*>(P), rowc, gate);
+  auto launch = [&](auto nw, auto spread) {
+    constexpr int NW = decltype(nw)::value;
+    constexpr bool SP = decltype(spread)::value;
+    constexpr int kT = NW > 4 ? 64 * NW : kThreads, RPW = kT / (64 * NW);
+    auto go = [&](auto kernel, auto* p) {
+      return launch_timed("gmm_softmax", kernel, dim3((R + RPW - 1) / RPW), dim3(kT), s, R, t.M, t.d, S,
+                          part, xsq, step, t.sig, t.ls, t.logw, t.musq, t.coef, p, rowc, gate);
     };
-    switch (g) {
-      case 16: return launch(std::integral_constant<int, 16>{});
-      case 32: return launch(std::integral_constant<int, 32>{});
-      case 64: return launch(std::integral_constant<int, 64>{});
-      case 128: return launch(std::integral_constant<int, 128>{});
-      default: return launch(std::integral_constant<int, 256>{});
-    }
+    const bool quad = t.M % 4 == 0;
+    if (p_bf16)
+      return go(quad ? gmm_softmax_kernel<NW, SP, true, uint16_t> : gmm_softmax_kernel<NW, SP, false, uint16_t>,
+                static_cast<uint16_t*>(P));
+    return go(quad ? gmm_softmax_kernel<NW, SP, true, float> : gmm_softmax_kernel<NW, SP, false, float>,
+              static_cast<float*>(P));
+  };
+  // Spread rows while their wavefronts are at most eight per SIMD (a latency);
+  // beyond, four components per lane
+  // (2304 x 1024: 18.0 us against 29.7 spread; 4352 x 256: 26.3 against 30.1).  plan_rows, not R,
+  // decides, so that a part of a batch sums as the whole does.
+  const int64_t waves = (int64_t)plan_rows * ((t.M + 63) / 64);
+  const std::true_type sp{};
+  const std::false_type wide{};
+  if (t.M <= 64) return launch(std::integral_constant<int, 1>{}, sp);
+  if (t.M <= 128) return launch(std::integral_constant<int, 2>{}, sp);
+  if (waves > 8192) {
+    if (t.M <= 256) return launch(std::integral_constant<int, 1>{}, wide);
+    if (t.M <= 512) return launch(std::integral_constant<int, 2>{}, wide);
+    return launch(std::integral_constant<int, 4>{}, wide);
   }
-  const int per = kThreads / 64;
-  const int nb = (R + per - 1) / per;
-  if (p_bf16)
-    return launch_timed("gmm_softmax", gmm_softmax_kernel<uint16_t>, dim3(nb), dim3(kThreads), s, R,
-                        t.M, t.d, S, part, xsq, step, t.sc, t.ls, t.logw, t.musq, t.coef,
-                        static_cast<uint16_t*>(P), rowc, gate);
-  return launch_timed("gmm_softmax", gmm_softmax_kernel<float>, dim3(nb), dim3(kThreads), s, R, t.M,
-                      t.d, S, part, xsq, step, t.sc, t.ls, t.logw, t.musq, t.coef,
-                      static_cast<float*>(P), rowc, gate);
+  if (t.M <= 256) return launch(std::integral_constant<int, 4>{}, sp);
+  if (t.M <= 512) return launch(std::integral_constant<int, 8>{}, sp);
+  return launch(std::integral_constant<int, 16>{}, sp);
 }
 
 hipError_t target_mean_launch(const Target& t, int R, const float* x, int64_t ldx,
@@ -1049,7 +879,7 @@ hipError_t target_mean_launch(const Target& t, int R, const float* x, int64_t ld
   float* rowc = reinterpret_cast<float*>(base + p.off_rowc);
   hipError_t e = logits_launch(t, p, R, x, ldx, part, xsq, s, gate);
   if (e != hipSuccess) return e;
-  e = gmm_softmax_launch(t, R, p.S, part, xsq, step, P, false, rowc, s, gate);
+  e = gmm_softmax_launch(t, R, p.rows, p.S, part, xsq, step, P, false, rowc, s, gate);
   if (e != hipSuccess) return e;
   dim3 g2((R + TILE - 1) / TILE, (t.d + TILE - 1) / TILE);
   const bool vec = t.M % KC == 0 && t.M < 1 << 22;
@@ -1076,7 +906,7 @@ hipError_t target_mean_lr_launch(const Target& t, int R, int K1, const float* x,
   float* rowc = reinterpret_cast<float*>(base + p.off_rowc);
   hipError_t e = logits_launch(t, p, R, x, t.d, part, xsq, s, gate);
   if (e != hipSuccess) return e;
-  e = gmm_softmax_launch(t, R, p.S, part, xsq, step, P, false, rowc, s, gate);
+  e = gmm_softmax_launch(t, R, p.rows, p.S, part, xsq, step, P, false, rowc, s, gate);
   if (e != hipSuccess) return e;
   dim3 g2((t.d + TILE - 1) / TILE, (R + TILE - 1) / TILE);
   // the buffer path: whole chunks of M and tiles of d, aligned rows, at least

@@ -709,6 +709,7 @@ inline bool big_mean_ok(const Target& t, int K1, bool vecd) {
 }
 
 struct Plan {
+  int rows;  // the rows the plan is for (the whole batch's, for a part of one)
   int S, ksplit;
   bool wide;  // the logits GEMM may run on 256 x 256 tiles (d a whole number of chunks)
   size_t off_part, off_xsq, off_p, off_rowc, total;
@@ -740,6 +741,7 @@ Plan make_plan(const Target& t, int R, int plan_rows = 0) {
       best_per = per;
     }
   }
+  p.rows = Rp;
   p.ksplit = best_per * KC;
   p.S = (t.d + p.ksplit - 1) / p.ksplit;
   size_t off = 0;
@@ -788,7 +790,7 @@ hipError_t logits_and_softmax(const Target& t, const Plan& p, const Bufs& w, int
                      g1, dim3(kThreads), s, R, t.M, t.d, x, ldx, t.mu16, p.ksplit, w.part, w.xsq,
                      gate);
   if (e != hipSuccess) return e;
-  return gmm_softmax_launch(t, R, p.S, w.part, w.xsq, step, w.P, true, w.rowc, s, gate);
+  return gmm_softmax_launch(t, R, p.rows, p.S, w.part, w.xsq, step, w.P, true, w.rowc, s, gate);
 }
 
 }  // namespace

@@ -22,18 +22,13 @@
 #include "common.hpp"
 #include "dmath.hpp"
 #include "philox.hpp"
+#include "wavered.hpp"
 
 namespace sd {
 namespace {
 
 constexpr int kThreads = 256;
 typedef float f4v __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
-}
 
 __global__ __launch_bounds__(kThreads) void logratio_kernel(
     int K, int d, const float* __restrict__ yd, int64_t yc, int64_t yr,
