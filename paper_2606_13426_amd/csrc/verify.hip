@@ -471,7 +471,9 @@ __global__ __launch_bounds__(kThreads) void scan_fused_kernel(
   const int t = D.tau;
   int rm;
   float cf = 0.f, sgo = 0.f;
-  const double st = lane_value(sgl, t <= kb ? t - 1 : kb);
+  // (row 64 of a full accept with K_b = 64 is in no lane)
+  const double st = t <= kb || kb < 64 ? lane_value(sgl, t <= kb ? t - 1 : kb)
+                                       : sigma[(int64_t)b * K1 + kb];
   const double s2t = lane_value(s2, t <= kb ? t - 1 : 0), szt = lane_value(sz, t <= kb ? t - 1 : 0);
   if (t <= kb && reflect) {
     // D.D > 0: a rejection never lands on a zero offset (kept as a guard)

@@ -95,3 +95,19 @@ def test_small_configs_match_oracle(d, M, B, K, N, seed):
         assert list(trace[: len(taus), b]) == taus, (b, taus, list(trace[: len(taus) + 1, b]))
         assert np.all(trace[len(taus):, b] == 0)
         assert_rows_close(y[b][None], ref["y"][i][None], what=f"Y_N chain {b}")
+
+
+def test_full_accept_of_a_64_step_block():
+    """K = 64, every draft accepted (a huge temperature): the full accept draws
+    its extra state with sigma of row 64, one past the lanes of the wavefront
+    that decides."""
+    N, K, B, seed = 200, 64, 4, 3
+    p = dict(mu=np.zeros((1, 3), np.float32), var=np.ones(1, np.float32), log_w=np.zeros(1, np.float32))
+    tgt = _lib.Target(_lib.schedule(N), p["mu"], p["var"], p["log_w"])
+    y, _, trace = _lib.sd_run_sampler_ex(tgt, B, K, seed, omega=1e6, trace_rounds=4)
+    torch.cuda.synchronize()
+    ref = osamp.run_sampler(GMM(p["mu"], p["var"], p["log_w"]), Schedule(N), B, K, seed, omega=1e6)
+    for i in range(B):
+        taus = [info["tau"] for info in ref["trace"][i]]
+        assert K + 1 in taus and list(trace[: len(taus), i].cpu().numpy()) == taus
+    assert_rows_close(y.cpu().numpy(), ref["y"], what="Y_N")
