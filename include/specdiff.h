@@ -16,13 +16,14 @@
  *  - The caller owns all memory.  The library allocates device memory only in
  *    sd_target_create (freed by sd_target_destroy); everything else lives in
  *    caller buffers, including a caller workspace sized by the *_workspace query.
- *    sd_target_create also allocates 1 KB of mapped pinned host memory: the
+ *    sd_target_create also allocates 42 KB of mapped pinned host memory: the
  *    words through which a running sampler call learns, round by round,
- *    whether any chain is still active: 64 slots per target, one per running
- *    call and chain group (SD_EUNSUPPORTED beyond that).
+ *    whether any chain is still active, and its final statistics: 64 slots per
+ *    target, one per running call and chain group (SD_EUNSUPPORTED beyond
+ *    that).
  *    A sampler call that runs two chain groups (sd_sampler_options.groups)
- *    creates one HIP stream the first time it uses a given slot of those
- *    words; the target keeps it until sd_target_destroy.
+ *    creates one HIP stream and two events the first time it uses a given slot
+ *    of those words; the target keeps them until sd_target_destroy.
  *  - Work is enqueued asynchronously on `stream` (a hipStream_t; NULL is the
  *    null stream).  Only sd_run_sampler reads results back: a per-round "any
  *    chain active" flag that its kernels store into the mapped host memory,

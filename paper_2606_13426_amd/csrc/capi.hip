@@ -146,6 +146,8 @@ hipError_t scratch_address(void** out) {
     }                                                                          \
   } while (0)
 
+static inline size_t a256(size_t x) { return (x + 255) & ~(size_t)255; }
+
 static bool sched_ok(const sd_schedule* s) {
   return s && s->n_steps >= 1 && s->beta_min > 0.0 && s->beta_max >= s->beta_min &&
          s->churn > 0.0 && isfinite(s->beta_max) && isfinite(s->churn);
@@ -222,33 +224,44 @@ sd_status sd_target_create(const sd_schedule* sched, int32_t d, int32_t n_comp, 
   t->prec = precision;
   (void)hipGetDevice(&t->device);
   const bool bf = precision == SD_BF16;
-  // the operand copies of the chosen precision only
+  // the operand copies of the chosen precision only, and one allocation for
+  // the tables (ls, logw, musq, coef, sig), filled on the host and copied once
+  const size_t Ns = (size_t)sched->n_steps;
+  const size_t o_ls = 0, o_logw = a256(o_ls + sizeof(double2) * M * Ns), o_musq = a256(o_logw + sizeof(double) * M),
+               o_coef = a256(o_musq + sizeof(double) * M), o_sig = a256(o_coef + sizeof(float4) * (Ns + 1)),
+               table_bytes = o_sig + sizeof(double) * (Ns + 1);
   bool ok = (bf ? hipMalloc(&t->mu16, sizeof(uint16_t) * M * D) == hipSuccess &&
                       hipMalloc(&t->muT16, sizeof(uint16_t) * M * D) == hipSuccess
                 : hipMalloc(&t->mu, sizeof(float) * M * D) == hipSuccess &&
                       hipMalloc(&t->muT, sizeof(float) * M * D) == hipSuccess &&
                       hipMalloc(&t->mu_split, sizeof(uint16_t) * 3 * M * D) == hipSuccess &&
                       hipMalloc(&t->muT_split, sizeof(uint16_t) * 3 * M * D) == hipSuccess) &&
-            hipMalloc(&t->ls, sizeof(double2) * M * (size_t)sched->n_steps) == hipSuccess &&
-            hipMalloc(&t->logw, sizeof(double) * M) == hipSuccess &&
-            hipMalloc(&t->musq, sizeof(double) * M) == hipSuccess &&
-            hipMalloc(&t->sig, sizeof(double) * (size_t)(sched->n_steps + 1)) == hipSuccess &&
-            hipMalloc(&t->coef, sizeof(float4) * (size_t)(sched->n_steps + 1)) == hipSuccess;
+            hipMalloc(&t->tables, table_bytes) == hipSuccess;
   if (!ok) {
     set_error("sd_target_create: device allocation failed");
     sd_target_destroy(reinterpret_cast<sd_target>(t));
     return SD_ENOMEM;
   }
-  // the sampler's per-round flags: mapped pinned host words, one group per
-  // concurrent sampler call
+  auto at = [&](size_t o) { return static_cast<char*>(t->tables) + o; };
+  t->ls = reinterpret_cast<double2*>(at(o_ls));
+  t->logw = reinterpret_cast<double*>(at(o_logw));
+  t->musq = reinterpret_cast<double*>(at(o_musq));
+  t->coef = reinterpret_cast<float4*>(at(o_coef));
+  t->sig = reinterpret_cast<double*>(at(o_sig));
+  // the sampler's per-round flags and final statistics: mapped pinned host
+  // words, one group per concurrent sampler call
+  const size_t flag_bytes = a256(sizeof(int32_t) * kFlagGroups * kFlagSlots);
+  void* mapped = nullptr;
   if (hipHostMalloc(reinterpret_cast<void**>(&t->host_flags),
-                    sizeof(int32_t) * kFlagGroups * kFlagSlots, hipHostMallocDefault) != hipSuccess ||
-      hipHostGetDevicePointer(reinterpret_cast<void**>(&t->host_flags_dev), t->host_flags, 0) !=
-          hipSuccess) {
+                    flag_bytes + sizeof(int64_t) * kFlagGroups * kStatWords, hipHostMallocDefault) != hipSuccess ||
+      hipHostGetDevicePointer(&mapped, t->host_flags, 0) != hipSuccess) {
     set_error("sd_target_create: mapped host flags could not be allocated");
     sd_target_destroy(reinterpret_cast<sd_target>(t));
     return SD_ENOMEM;
   }
+  t->host_flags_dev = static_cast<int32_t*>(mapped);
+  t->host_stats = reinterpret_cast<int64_t*>(reinterpret_cast<char*>(t->host_flags) + flag_bytes);
+  t->host_stats_dev = reinterpret_cast<int64_t*>(static_cast<char*>(mapped) + flag_bytes);
   t->flag_busy = 0;
   // set-up of the no-allocation scratch on this device
   void* scr = nullptr;
@@ -281,31 +294,25 @@ sd_status sd_target_create(const sd_schedule* sched, int32_t d, int32_t n_comp, 
          hipMemcpy(t->muT_split, spT.data(), sizeof(uint16_t) * 3 * n, hipMemcpyHostToDevice) ==
              hipSuccess;
   }
-  ok = ok &&
-
-       hipMemcpy(t->logw, lw.data(), sizeof(double) * M, hipMemcpyHostToDevice) == hipSuccess &&
-       hipMemcpy(t->musq, msq.data(), sizeof(double) * M, hipMemcpyHostToDevice) == hipSuccess;
-  std::vector<double2> ls(M * (size_t)sched->n_steps);
-  for (int n = 0; n < sched->n_steps; ++n) {
-    const double a = sched_signal(t->sc, n), a2 = a * a;
+  std::vector<char> tables(table_bytes);
+  auto host_at = [&](size_t o) { return tables.data() + o; };
+  double2* ls = reinterpret_cast<double2*>(host_at(o_ls));
+  float4* coef = reinterpret_cast<float4*>(host_at(o_coef));
+  double* sig = reinterpret_cast<double*>(host_at(o_sig));
+  memcpy(host_at(o_logw), lw.data(), sizeof(double) * M);
+  memcpy(host_at(o_musq), msq.data(), sizeof(double) * M);
+  for (int n = 0; n <= sched->n_steps; ++n) {
+    const double a = sched_signal(t->sc, n), a2 = a * a, c2 = sched_c2(t->sc, n);
+    sig[n] = a;
+    coef[n] = make_float4((float)sched_c1(t->sc, n), (float)c2, (float)sched_sigma(t->sc, n),
+                          (float)(1.0 / c2));
+    if (n == sched->n_steps) break;
     for (size_t m = 0; m < M; ++m) {
       const double s2 = a2 * vv[m] + 1.0 - a2;
       ls[(size_t)n * M + m] = make_double2(log(s2), 1.0 / s2);
     }
   }
-  ok = ok && hipMemcpy(t->ls, ls.data(), sizeof(double2) * ls.size(), hipMemcpyHostToDevice) ==
-                 hipSuccess;
-  std::vector<float4> coef((size_t)sched->n_steps + 1);
-  std::vector<double> sig((size_t)sched->n_steps + 1);
-  for (int n = 0; n <= sched->n_steps; ++n) {
-    sig[n] = sched_signal(t->sc, n);
-    const double c2 = sched_c2(t->sc, n);
-    coef[n] = make_float4((float)sched_c1(t->sc, n), (float)c2, (float)sched_sigma(t->sc, n),
-                          (float)(1.0 / c2));
-  }
-  ok = ok && hipMemcpy(t->coef, coef.data(), sizeof(float4) * coef.size(), hipMemcpyHostToDevice) ==
-                 hipSuccess &&
-       hipMemcpy(t->sig, sig.data(), sizeof(double) * sig.size(), hipMemcpyHostToDevice) == hipSuccess;
+  ok = ok && hipMemcpy(t->tables, tables.data(), table_bytes, hipMemcpyHostToDevice) == hipSuccess;
   if (!ok) {
     set_error("sd_target_create: copy to device failed");
     sd_target_destroy(reinterpret_cast<sd_target>(t));
@@ -324,17 +331,16 @@ sd_status sd_target_destroy(sd_target target) {
   if (t->muT_split) (void)hipFree(t->muT_split);
   if (t->mu16) (void)hipFree(t->mu16);
   if (t->muT16) (void)hipFree(t->muT16);
-  if (t->ls) (void)hipFree(t->ls);
-  if (t->logw) (void)hipFree(t->logw);
-  if (t->musq) (void)hipFree(t->musq);
-  if (t->sig) (void)hipFree(t->sig);
-  if (t->coef) (void)hipFree(t->coef);
+  if (t->tables) (void)hipFree(t->tables);
   // a flag group still held by a call that timed out may be written by its
   // kernels later: that memory and those side streams are then left alone
   const bool idle = __atomic_load_n(&t->flag_busy, __ATOMIC_ACQUIRE) == 0;
   if (t->host_flags && idle) (void)hipHostFree(t->host_flags);
-  for (int g = 0; g < kFlagGroups && idle; ++g)
+  for (int g = 0; g < kFlagGroups && idle; ++g) {
+    if (t->fork[g]) (void)hipEventDestroy(t->fork[g]);
+    if (t->join[g]) (void)hipEventDestroy(t->join[g]);
     if (t->side[g]) (void)hipStreamDestroy(t->side[g]);
+  }
   delete t;
   return SD_OK;
 }
@@ -387,7 +393,7 @@ size_t sd_target_mean_noalloc_max_bytes(void) { return kScratchBytes; }
 sd_status sd_init_chains(int32_t B, int32_t d, uint64_t seed, float* y, sd_stream stream) {
   SD_CHECK_ARG(B >= 1 && d >= 1, "sd_init_chains: need B >= 1 and d >= 1");
   SD_CHECK_ARG(y, "sd_init_chains: y is NULL");
-  SD_HIP(init_chains_launch(B, d, seed, y, nullptr, 0, (hipStream_t)stream));
+  SD_HIP(init_chains_launch(B, d, seed, y, (hipStream_t)stream));
   return SD_OK;
 }
 
@@ -500,7 +506,7 @@ namespace {
 
 struct SamplerLayout {
   size_t y, x, sv, mq, sigma, step, k2, rnd2, crow2, cstep2, tau, rmode, rcoef, rsig, hist, steps,
-      act, nan, kb, left, dummy_i32, dummy_i64, coins, lar, ures, ties, lrp, tws, tws1, total;
+      act, nan, totals, coins, lar, ures, ties, lrp, tws, tws1, total;
   size_t tws_bytes, tws1_bytes;
   int nct;
 };
@@ -521,8 +527,6 @@ inline int choose_groups(int B, int K, int requested) {
   if (requested == 1 || requested == 2) return requested;
   return (int64_t)(B / 2) * (K + 1) >= 2048 ? 2 : 1;
 }
-
-inline size_t a256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 SamplerLayout sampler_layout(const Target& t, int B, int K) {
   SamplerLayout L{};
@@ -552,10 +556,7 @@ SamplerLayout sampler_layout(const Target& t, int B, int K) {
   L.steps = take(8 * Bs);
   L.act = take(4 * 2 * 2);  // [group][round parity]
   L.nan = take(4);
-  L.kb = take(4 * Bs);
-  L.left = take(4 * Bs);
-  L.dummy_i32 = take(4 * (Bs + 2));
-  L.dummy_i64 = take(8 * (SD_MAX_BLOCK + 3));
+  L.totals = take(8 * kStatNan);
   L.coins = take(8 * Bs);
   L.lar = take(8 * Bs);
   L.ures = take(8 * Bs);
@@ -620,6 +621,33 @@ hipError_t wait_bounded(hipStream_t s, Clock::time_point deadline, bool* timed_o
     }
     std::this_thread::sleep_for(std::chrono::microseconds(50));
   }
+}
+
+// Wait until *word holds tag, stored by the last kernel queued on the stream:
+// the word is polled (no sleep, no stream query's marker) and the runtime is
+// asked for errors only now and then; results as wait_bounded.
+hipError_t wait_tag(const int64_t* word, int64_t tag, hipStream_t s, Clock::time_point deadline,
+                    bool* timed_out) {
+  *timed_out = false;
+  auto next_query = Clock::now() + std::chrono::milliseconds(20);
+  for (uint32_t spin = 1; __atomic_load_n(word, __ATOMIC_ACQUIRE) != tag; ++spin) {
+    if ((spin & 1023u) != 0) continue;
+    const Clock::time_point now = Clock::now();
+    if (now >= deadline) {
+      *timed_out = true;
+      return hipErrorNotReady;
+    }
+    if (now < next_query) continue;
+    next_query = now + std::chrono::milliseconds(20);
+    const hipError_t q = hipStreamQuery(s);
+    if (q == hipErrorNotReady) {
+      (void)hipGetLastError();  // a status, not a failure
+      continue;
+    }
+    if (__atomic_load_n(word, __ATOMIC_ACQUIRE) == tag) break;
+    return q == hipSuccess ? hipErrorUnknown : q;
+  }
+  return hipSuccess;
 }
 
 // One group of the target's mapped flag words for the duration of a call.
@@ -701,12 +729,11 @@ sd_status sd_run_sampler_ex(sd_target target, int32_t B, int32_t K,
   double *sigma = D(L.sigma), *lrp = D(L.lrp), *lar = D(L.lar), *ures = D(L.ures);
   int32_t *step = I(L.step), *k2 = I(L.k2), *crow2 = I(L.crow2), *cstep2 = I(L.cstep2),
           *tau = I(L.tau), *rmode = I(L.rmode), *hist = I(L.hist), *act = I(L.act),
-          *nanflag = I(L.nan), *kb = I(L.kb), *left = I(L.left), *dummy = I(L.dummy_i32),
-          *ties = I(L.ties);
+          *nanflag = I(L.nan), *ties = I(L.ties);
   uint32_t* rnd2 = reinterpret_cast<uint32_t*>(base + L.rnd2);
   uint64_t* coins = reinterpret_cast<uint64_t*>(base + L.coins);
   int64_t* steps = reinterpret_cast<int64_t*>(base + L.steps);
-  int64_t* dummy64 = reinterpret_cast<int64_t*>(base + L.dummy_i64);
+  int64_t* totals = reinterpret_cast<int64_t*>(base + L.totals);
   void* tws = base + L.tws;
   const sd_stride xs{(int64_t)K1 * d, d}, mqs{(int64_t)K1 * d, d};
   const int G = choose_groups(B, K, opts->groups);
@@ -718,33 +745,21 @@ sd_status sd_run_sampler_ex(sd_target target, int32_t B, int32_t K,
     // (row 0 of mq) seeds the Free Drafter's cached score; the round-0 rows'
     // steps and sigmas; the first draft block.  The Frozen Drafter makes that
     // call and draft at the start of every round instead.
-    SD_HIP(fill_i32_launch(k2, 2 * (int64_t)B, 0, s));
-    SD_HIP(fill_i32_launch(reinterpret_cast<int32_t*>(rnd2), 2 * (int64_t)B, 0, s));
-    SD_HIP(fill_i32_launch(crow2, 2 * (int64_t)B, 0, s));
-    SD_HIP(fill_i32_launch(cstep2, 2 * (int64_t)B, 0, s));
-    SD_HIP(fill_i32_launch(hist, (int64_t)B * (SD_MAX_BLOCK + 2), 0, s));
-    SD_HIP(fill_i64_launch(steps, B, 0, s));
-    SD_HIP(fill_i32_launch(ties, B, 0, s));
-    SD_HIP(fill_i32_launch(act, 4, 0, s));
-    SD_HIP(fill_i32_launch(nanflag, 1, 0, s));
-    SD_HIP(fill_i32_launch(step, B, 0, s));
-    SD_HIP(fill_i32_launch(tau, B, 0, s));
-    SD_HIP(fill_i32_launch(dummy, B + 2, 0, s));
-    SD_HIP(init_chains_launch(B, d, seed, y, x, (int64_t)K1 * d, s));
-    if (!frozen)
-      SD_HIP(target_mean_launch(t, B, x, (int64_t)K1 * d, step, mq, (int64_t)K1 * d, nullptr, 0,
-                                tws, s, nullptr));
-    SD_HIP(prepare_launch(t.sc, B, K, k2, kb, left, step, sigma, tau, dummy, dummy + B,
-                          dummy + B + 1, dummy64, dummy64 + SD_MAX_BLOCK + 2, s));
-    if (!frozen)
+    SD_HIP(sampler_init_launch(t.sc, B, K, d, seed, y, x, k2, rnd2, crow2, cstep2, hist, steps, ties, tau,
+                               step, sigma, act, nanflag, s));
+    if (!frozen) {
+      SD_HIP(target_mean_launch(t, B, x, (int64_t)K1 * d, cstep2, mq, (int64_t)K1 * d, nullptr, 0, tws, s,
+                                nullptr));
       SD_HIP(draft_cached_launch(t.sc, t.coef, B, K, d, y, crow2, cstep2, mq, mqs, k2, rnd2, seed,
                                  x, xs, sv, s, nullptr));
+    }
+  } else {
+    // each group's gate of round `start` (whether any of its chains is still
+    // active), from the chains' steps: the resumed run may group its chains
+    // differently from the call that left the state
+    const int par0 = start & 1;
+    SD_HIP(chains_active_launch(B, G == 2 ? B / 2 : B, N, k2 + par0 * B, act + par0, act + 2 + par0, s));
   }
-  // each group's gate of round `start` (whether any of its chains is still
-  // active), from the chains' steps: a resumed run may group its chains
-  // differently from the call that left the state
-  const int par0 = start & 1;
-  SD_HIP(chains_active_launch(B, G == 2 ? B / 2 : B, N, k2 + par0 * B, act + par0, act + 2 + par0, s));
 
   // Round r's scan publishes round r - 1's active flag, tagged with r - 1, into
   // slot (r - 1) % kFlagSlots of its group's block of mapped host words.  After
@@ -790,25 +805,24 @@ sd_status sd_run_sampler_ex(sd_target target, int32_t B, int32_t K,
     q.st = s;
     if (g == 1) {
       hipStream_t& side = tp->side[q.grp];
-      if (!side && hipStreamCreateWithFlags(&side, hipStreamNonBlocking) != hipSuccess) {
-        side = nullptr;
+      hipEvent_t &ef = tp->fork[q.grp], &ej = tp->join[q.grp];
+      bool ok = side || hipStreamCreateWithFlags(&side, hipStreamNonBlocking) == hipSuccess;
+      if (!ok) side = nullptr;
+      if (ok && !ef && hipEventCreateWithFlags(&ef, hipEventDisableTiming) != hipSuccess) ef = nullptr;
+      if (ok && !ej && hipEventCreateWithFlags(&ej, hipEventDisableTiming) != hipSuccess) ej = nullptr;
+      if (!ok || !ef || !ej) {
         release_all();
-        set_error("sd_run_sampler: the second chain group's stream could not be created");
+        set_error("sd_run_sampler: the second chain group's stream and events could not be created");
         return SD_EHIP;
       }
       q.st = side;
     }
   }
+  int64_t* const host_stats = t.host_stats + gr[0].grp * kStatWords;
+  int64_t* const host_stats_dev = t.host_stats_dev + gr[0].grp * kStatWords;
+  host_stats[kStatTag] = 0;
   std::atomic_thread_fence(std::memory_order_seq_cst);
-  hipEvent_t fork = nullptr, join = nullptr;
-  if (G == 2) {
-    if (hipEventCreateWithFlags(&fork, hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&join, hipEventDisableTiming) != hipSuccess) {
-      release_all();
-      set_error("sd_run_sampler: could not create the events of the second chain group");
-      return SD_EHIP;
-    }
-  }
+  const hipEvent_t fork = G == 2 ? tp->fork[gr[1].grp] : nullptr, join = G == 2 ? tp->join[gr[1].grp] : nullptr;
   bool forked = false;
   constexpr int kQuietMs = 20;
   const int first_flag = start > 0 ? start - 1 : 0;
@@ -929,18 +943,18 @@ sd_status sd_run_sampler_ex(sd_target target, int32_t B, int32_t K,
   }
   const Clock::time_point deadline = Clock::now() + std::chrono::seconds(kStallSeconds);
   bool finished = rounds >= 0;
-  if (st == SD_OK && !finished) {
-    // every launched round finishes; the flags of rounds up to r - 2 are then
-    // in their slots, and the last round's, which no later scan publishes, is
-    // copied
-    int32_t last_flag[2] = {1, 1};
+  if (st == SD_OK) {
+    // the totals over the chains come back through mapped host words whose tag
+    // is stored last: one wait, no copies into pageable memory
     hipError_t e = hipSuccess;
+    auto copy_y = [&]() {
+      return hipMemcpyAsync(y_out, y, sizeof(float) * (size_t)B * d, hipMemcpyDeviceToDevice, s);
+    };
+    if (finished) e = copy_y();
+    if (e == hipSuccess)
+      e = sampler_finish_launch(B, hist, steps, ties, nanflag, act, r & 1, totals, host_stats_dev, 1, s);
     bool late = false;
-    if (r > start) {
-      for (int g = 0; g < G && e == hipSuccess; ++g)
-        e = hipMemcpyAsync(&last_flag[g], act + 2 * g + (r & 1), sizeof(int32_t), hipMemcpyDeviceToHost, s);
-      if (e == hipSuccess) e = wait_bounded(s, deadline, &late);
-    }
+    if (e == hipSuccess) e = wait_tag(host_stats + kStatTag, 1, s, deadline, &late);
     if (late) {
       set_error("sd_run_sampler: the last rounds did not finish within %d s", kStallSeconds);
       return SD_EHIP;  // keep the flag groups (see above)
@@ -949,17 +963,29 @@ sd_status sd_run_sampler_ex(sd_target target, int32_t B, int32_t K,
       set_error("sd_run_sampler: waiting for the last rounds failed: %s", hipGetErrorString(e));
       st = SD_EHIP;
     }
-    for (int back = std::max(r - kLag, first_flag); st == SD_OK && back < r; ++back) {
+    // every launched round has finished: the flags of rounds up to r - 2 are in
+    // their slots, and the last round's gates among the totals
+    for (int back = std::max(r - kLag, first_flag); st == SD_OK && !finished && back < r; ++back) {
       bool any = false;
       for (int g = 0; g < G; ++g) {
         const int32_t v = gr[g].pub[back % kFlagSlots];
-        const int32_t flag = back == r - 1 ? last_flag[g] : ((v >> 1) == back ? (v & 1) : 1);
+        const int64_t flag = back == r - 1 ? (r > start ? host_stats[kStatGate + g] : 1)
+                                           : ((v >> 1) == back ? (v & 1) : 1);
         if (flag != 0) any = true;
       }
       if (!any) {
         rounds = back + 1;
         finished = true;
-        break;
+        e = copy_y();
+        if (e == hipSuccess) e = wait_bounded(s, deadline, &late);
+        if (late) {
+          set_error("sd_run_sampler: the final copy did not finish within %d s", kStallSeconds);
+          return SD_EHIP;  // keep the flag groups (see above)
+        }
+        if (e != hipSuccess) {
+          set_error("sd_run_sampler: final copy failed: %s", hipGetErrorString(e));
+          st = SD_EHIP;
+        }
       }
     }
     if (st == SD_OK && !finished) {
@@ -971,65 +997,32 @@ sd_status sd_run_sampler_ex(sd_target target, int32_t B, int32_t K,
       }
     }
   }
-  if (st == SD_OK) {
-    std::vector<int32_t> h_hist((size_t)B * (SD_MAX_BLOCK + 2)), h_ties(B);
-    std::vector<int64_t> h_steps(B);
-    int32_t h_nan = 0;
-    hipError_t e = hipSuccess;
-    if (finished)
-      e = hipMemcpyAsync(y_out, y, sizeof(float) * (size_t)B * d, hipMemcpyDeviceToDevice, s);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(h_hist.data(), hist, sizeof(int32_t) * h_hist.size(), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(h_steps.data(), steps, sizeof(int64_t) * B, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(h_ties.data(), ties, sizeof(int32_t) * B, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(&h_nan, nanflag, sizeof(int32_t), hipMemcpyDeviceToHost, s);
-    bool late = false;
-    if (e == hipSuccess) e = wait_bounded(s, deadline, &late);
-    if (late) {
-      set_error("sd_run_sampler: the final copies did not finish within %d s", kStallSeconds);
-      return SD_EHIP;  // keep the flag groups (see above)
+  if (st == SD_OK && stats) {
+    memset(stats, 0, sizeof(*stats));
+    stats->rounds = rounds;
+    stats->finished = finished ? 1 : 0;
+    stats->groups = G;
+    stats->steps = host_stats[SD_MAX_BLOCK + 2];
+    stats->ties = host_stats[SD_MAX_BLOCK + 3];
+    double tau_sum = 0.0;
+    for (int i = 0; i < SD_MAX_BLOCK + 2; ++i) {
+      stats->tau_hist[i] = host_stats[i];
+      stats->chain_rounds += stats->tau_hist[i];
+      tau_sum += (double)i * (double)stats->tau_hist[i];
     }
-    if (e != hipSuccess) {
-      set_error("sd_run_sampler: final copy failed: %s", hipGetErrorString(e));
-      st = SD_EHIP;
-    } else {
-      if (stats) {
-        memset(stats, 0, sizeof(*stats));
-        stats->rounds = rounds;
-        stats->finished = finished ? 1 : 0;
-        stats->groups = G;
-        double tau_sum = 0.0;
-        for (int b = 0; b < B; ++b) {
-          stats->steps += h_steps[b];
-          stats->ties += h_ties[b];
-          for (int i = 0; i < SD_MAX_BLOCK + 2; ++i) stats->tau_hist[i] += h_hist[(size_t)b * (SD_MAX_BLOCK + 2) + i];
-        }
-        for (int i = 0; i < SD_MAX_BLOCK + 2; ++i) {
-          stats->chain_rounds += stats->tau_hist[i];
-          tau_sum += (double)i * (double)stats->tau_hist[i];
-        }
-        stats->mean_tau = stats->chain_rounds > 0 ? tau_sum / (double)stats->chain_rounds : 0.0;
-      }
-      if (h_nan) {
-        set_error("sd_run_sampler: non-finite log-ratio met");
-        st = SD_ENUMERIC;
-      }
-    }
+    stats->mean_tau = stats->chain_rounds > 0 ? tau_sum / (double)stats->chain_rounds : 0.0;
   }
-  bool late = false;
-  (void)wait_bounded(s, deadline, &late);
-  if (late) {
-    if (st == SD_OK) {
-      set_error("sd_run_sampler: the stream did not drain within %d s", kStallSeconds);
-      st = SD_EHIP;
-    }
-    return st;  // keep the flag groups (see above)
+  if (st == SD_OK && host_stats[kStatNan]) {
+    set_error("sd_run_sampler: non-finite log-ratio met");
+    st = SD_ENUMERIC;
+  }
+  if (st == SD_EHIP) {
+    // the queue's state is unknown: hand the flag groups back only once it drains
+    bool late = false;
+    (void)wait_bounded(s, deadline, &late);
+    if (late) return st;
   }
   release_all();
-  if (fork) (void)hipEventDestroy(fork);
-  if (join) (void)hipEventDestroy(join);
   return st;
 }
 
@@ -1087,7 +1080,7 @@ sd_status sd_run_plain_em(sd_target target, int32_t B, uint64_t seed, float* y_o
   int32_t* step = reinterpret_cast<int32_t*>(base + a256(sizeof(float) * (size_t)B * t.d));
   void* tws = base + a256(sizeof(float) * (size_t)B * t.d) + a256(sizeof(int32_t) * (size_t)B);
   const int d = t.d;
-  SD_HIP(init_chains_launch(B, d, seed, y_out, nullptr, 0, s));
+  SD_HIP(init_chains_launch(B, d, seed, y_out, s));
   SD_HIP(fill_i32_launch(step, B, 0, s));
   for (int n = 0; n < t.sc.N; ++n) {
     SD_HIP(target_mean_launch(t, B, y_out, d, step, mq, d, nullptr, 0, tws, s, nullptr));

@@ -99,6 +99,7 @@ struct Target {
   // contractions of gemm_split.hpp
   uint16_t* mu_split;   // [3][M][d]
   uint16_t* muT_split;  // [3][d][M]
+  void* tables;   // one allocation that holds the five tables below
   double* logw;   // [M]
   double* musq;   // [M] ||mu_m||^2 (float64 from the float32 means)
   double* sig;    // [N+1] signal level a_n
@@ -111,13 +112,22 @@ struct Target {
   // back atomically; a group whose call timed out is never given back).
   int32_t* host_flags;      // host address [kFlagGroups][kFlagSlots]
   int32_t* host_flags_dev;  // the same memory as the device sees it
+  // The words through which a call's totals come back (kStat*), per flag group.
+  int64_t* host_stats;      // host address [kFlagGroups][kStatWords]
+  int64_t* host_stats_dev;
   uint64_t flag_busy;
   // the second stream of a sampler call that runs two chain groups, one per
   // flag group (created at its first use, used only by the call that holds
   // that flag group)
   hipStream_t side[64];
+  hipEvent_t fork[64], join[64];  // its events, made with it
 };
 constexpr int kFlagGroups = 64, kFlagSlots = 4;
+// tau histogram, steps, ties (SD_MAX_BLOCK + 4 totals), non-finite flag, the
+// two chain groups' gates, tag
+constexpr int kStatNan = SD_MAX_BLOCK + 4, kStatGate = kStatNan + 1, kStatTag = kStatGate + 2,
+              kStatWords = 80;
+static_assert(kStatTag < kStatWords, "the words hold every total and the tag");
 static_assert(sizeof(Target::side) / sizeof(hipStream_t) == kFlagGroups, "one side stream per flag group");
 
 // Workspace of a target call on `rows` rows whose logits GEMM is split over d
@@ -195,8 +205,18 @@ hipError_t advance_launch(const Sched& sc, const float4* coef, int B, int K, int
                           int64_t stream_bytes = 0);
 
 // ---------------------------------------------------------------- kernels --
-hipError_t init_chains_launch(int B, int d, uint64_t seed, float* y, float* x0, int64_t x0c,
-                              hipStream_t s);
+hipError_t init_chains_launch(int B, int d, uint64_t seed, float* y, hipStream_t s);
+// A new run's state: Y_0 into y [B][d] and row 0 of x [B][K+1][d], and every
+// chain's bookkeeping, the round-0 gates set.
+hipError_t sampler_init_launch(const Sched& sc, int B, int K, int d, uint64_t seed, float* y, float* x,
+                               int32_t* k2, uint32_t* rnd2, int32_t* crow2, int32_t* cstep2,
+                               int32_t* hist, int64_t* steps, int32_t* ties, int32_t* tau,
+                               int32_t* step, double* sigma, int32_t* act, int32_t* nan, hipStream_t s);
+// The run's totals over the chains (stats: device, kStatNan words) into mapped
+// host words, with the gates of round parity `parity`, and tag last.
+hipError_t sampler_finish_launch(int B, const int32_t* hist, const int64_t* steps, const int32_t* ties,
+                                 const int32_t* nan, const int32_t* act, int parity, int64_t* stats,
+                                 int64_t* host, int64_t tag, hipStream_t s);
 hipError_t draft_launch(const Sched& sc, int B, int K, int d, const float* y, const float* cs,
                         const int32_t* k, const uint32_t* rnd, uint64_t seed, float* x,
                         sd_stride xs, float* mp, sd_stride mps, hipStream_t s, const int* gate);
@@ -232,23 +252,11 @@ hipError_t reflection_launch(int B, int K, int d, const float* yd, sd_stride ys,
 hipError_t em_noise_launch(int B, int d, int n, float sigma_n, uint64_t seed, const float* mq,
                            float* y, int32_t* step, hipStream_t s);
 // Sampler-only kernels.
-hipError_t residual_commit_launch(int B, int K, int d, int N, const float* yd, sd_stride ys,
-                                  const float* mp, sd_stride mps, const float* mq, sd_stride mqs,
-                                  const double* sigma, const int32_t* kb, const int32_t* left,
-                                  const int32_t* tau, const double* ures, const double* dn,
-                                  uint32_t* rnd, uint64_t seed, float* y, int32_t* k,
-                                  int32_t* crow, int32_t* cstep, int32_t* adv, int32_t* trace,
-                                  int r, int trace_rounds, hipStream_t s, const int* gate);
 hipError_t fill_i32_launch(int32_t* p, int64_t n, int32_t v, hipStream_t s);
 // *f0 = 1 if a chain of [0, split) has k < N, else 0; *f1 the same for
 // [split, B) (one workgroup).
 hipError_t chains_active_launch(int B, int split, int N, const int32_t* k, int* f0, int* f1,
                                 hipStream_t s);
-hipError_t fill_i64_launch(int64_t* p, int64_t n, int64_t v, hipStream_t s);
-hipError_t prepare_launch(const Sched& sc, int B, int K, const int32_t* k, int32_t* kb,
-                          int32_t* left, int32_t* step, double* sigma, int32_t* tau,
-                          int32_t* adv, int* cnt_cur, int* cnt_next, int64_t* hist,
-                          int64_t* steps, hipStream_t s);
 hipError_t philox_words_launch(uint64_t seed, int n, const uint32_t* ctr, uint32_t* out,
                                hipStream_t s);
 hipError_t philox_normals_launch(uint64_t seed, uint32_t chain, uint32_t rnd, uint32_t tag,

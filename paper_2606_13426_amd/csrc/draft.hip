@@ -14,19 +14,56 @@ namespace {
 constexpr int kThreads = 256;
 
 __global__ __launch_bounds__(kThreads) void init_chains_kernel(int d, uint64_t seed, float* y,
-                                                               float* x0, int64_t x0c) {
+                                                               bool vec) {
   const int b = blockIdx.y;
   const int g = blockIdx.x * kThreads + threadIdx.x;
   const int e0 = 4 * g;
   if (e0 >= d) return;
   const float4 z = normals4(philox((uint32_t)g, (uint32_t)b, 0u, TAG_INIT << 24, seed));
-  float* p = y + (int64_t)b * d + e0;
+  const float v[4] = {z.x, z.y, z.z, z.w};
   const int cnt = min(4, d - e0);
-  for (int c = 0; c < cnt; ++c) p[c] = get4(z, c);
-  if (x0) {
-    float* q = x0 + (int64_t)b * x0c + e0;
-    for (int c = 0; c < cnt; ++c) q[c] = get4(z, c);
+  store4(y + (int64_t)b * d + e0, cnt, vec && cnt == 4, v);
+}
+
+// A new run's state in one launch: Y_0 into y and into row 0 of the chain's x
+// block, and the bookkeeping of every chain (its first workgroup) and of the
+// run (the first workgroup of all): a launch each took 2 us apiece.
+__global__ __launch_bounds__(kThreads) void sampler_init_kernel(
+    Sched sc, int B, int K, int d, uint64_t seed, float* __restrict__ y, float* __restrict__ x,
+    bool vec, int32_t* __restrict__ k2, uint32_t* __restrict__ rnd2, int32_t* __restrict__ crow2,
+    int32_t* __restrict__ cstep2, int32_t* __restrict__ hist, int64_t* __restrict__ steps,
+    int32_t* __restrict__ ties, int32_t* __restrict__ tau, int32_t* __restrict__ step,
+    double* __restrict__ sigma, int32_t* __restrict__ act, int32_t* __restrict__ nan) {
+  const int b = blockIdx.y, K1 = K + 1, t = threadIdx.x;
+  if (blockIdx.x == 0) {
+    if (t < 2) {
+      k2[t * B + b] = 0;
+      rnd2[t * B + b] = 0u;
+      crow2[t * B + b] = 0;
+      cstep2[t * B + b] = 0;
+    }
+    if (t == 2) {
+      steps[b] = 0;
+      ties[b] = 0;
+      tau[b] = 0;
+    }
+    if (b == 0 && t < 4) act[t] = t % 2 == 0 ? 1 : 0;  // [group][round parity]: round 0 is active
+    if (b == 0 && t == 4) *nan = 0;
+    if (t >= 64 && t < 64 + SD_MAX_BLOCK + 2) hist[(int64_t)b * (SD_MAX_BLOCK + 2) + t - 64] = 0;
+    if (t >= 64 && t < 64 + K1) {
+      const int j = t - 64;
+      step[(int64_t)b * K1 + j] = min(j, sc.N - 1);
+      sigma[(int64_t)b * K1 + j] = sched_sigma(sc, min(j, sc.N));
+    }
   }
+  const int g = blockIdx.x * kThreads + t;
+  const int e0 = 4 * g;
+  if (e0 >= d) return;
+  const float4 z = normals4(philox((uint32_t)g, (uint32_t)b, 0u, TAG_INIT << 24, seed));
+  const float v[4] = {z.x, z.y, z.z, z.w};
+  const int cnt = min(4, d - e0);
+  store4(y + (int64_t)b * d + e0, cnt, vec && cnt == 4, v);
+  store4(x + (int64_t)b * K1 * d + e0, cnt, vec && cnt == 4, v);
 }
 
 // Draft block of one chain, four coordinates per thread.  The cached target
@@ -79,54 +116,6 @@ __global__ __launch_bounds__(kThreads) void draft_kernel(
              cnt, vec, stream);
 }
 
-// One thread per chain, at the start of a round:
-//  * books the previous round's outcome (tau histogram, steps advanced) and
-//    clears it, so that a round is counted exactly once;
-//  * counts the chains still active (a ballot per wavefront) into cnt_cur,
-//    which gates every later kernel of the round, and clears the next slot;
-//  * writes the block size K_b, the steps left, the step index of every
-//    target row and sigma_{k+j} for j = 0..K.
-__global__ __launch_bounds__(kThreads) void prepare_kernel(
-    Sched sc, int B, int K, const int32_t* __restrict__ kk, int32_t* kb, int32_t* left,
-    int32_t* step, double* sigma, int32_t* tau, int32_t* adv, int* cnt_cur, int* cnt_next,
-    int64_t* hist, int64_t* steps) {
-  __shared__ int h[SD_MAX_BLOCK + 2];
-  for (int i = threadIdx.x; i < SD_MAX_BLOCK + 2; i += kThreads) h[i] = 0;
-  __syncthreads();
-  const int b = blockIdx.x * kThreads + threadIdx.x;
-  if (b == 0) *cnt_next = 0;
-  const bool in = b < B;
-  const int t = in ? tau[b] : 0;
-  const int a = in ? adv[b] : 0;
-  const int k = in ? kk[b] : sc.N;
-  if (in) {
-    if (t > 0 && t < SD_MAX_BLOCK + 2) atomicAdd(&h[t], 1);
-    tau[b] = 0;
-    adv[b] = 0;
-  }
-  unsigned long long sa = (unsigned long long)a;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) sa += __shfl_xor(sa, o);
-  const uint64_t act = __ballot(in && k < sc.N);
-  if ((threadIdx.x & 63) == 0) {
-    if (act) atomicAdd(cnt_cur, __popcll(act));
-    if (sa) atomicAdd((unsigned long long*)steps, sa);
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < SD_MAX_BLOCK + 2; i += kThreads)
-    if (h[i]) atomicAdd((unsigned long long*)&hist[i], (unsigned long long)h[i]);
-  if (!in || k >= sc.N) {
-    if (in) kb[b] = 0;
-    return;
-  }
-  kb[b] = min(K, sc.N - k);
-  left[b] = sc.N - k;
-  for (int j = 0; j <= K; ++j) {
-    step[(int64_t)b * (K + 1) + j] = min(k + j, sc.N - 1);
-    sigma[(int64_t)b * (K + 1) + j] = sched_sigma(sc, min(k + j, sc.N));
-  }
-}
-
 __global__ void fill_i32_kernel(int32_t* p, int64_t n, int32_t v) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;
@@ -155,9 +144,42 @@ __global__ __launch_bounds__(kThreads) void chains_active_kernel(int B, int spli
   }
 }
 
-__global__ void fill_i64_kernel(int64_t* p, int64_t n, int64_t v) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
+// Totals over the chains, one workgroup each: stats[c] for c <= SD_MAX_BLOCK + 1
+// the rounds with tau = c, then steps advanced and tied coins.
+__global__ __launch_bounds__(kThreads) void sampler_totals_kernel(int B, const int32_t* __restrict__ hist,
+                                                                  const int64_t* __restrict__ steps,
+                                                                  const int32_t* __restrict__ ties,
+                                                                  int64_t* __restrict__ stats) {
+  constexpr int H = SD_MAX_BLOCK + 2;
+  const int c = blockIdx.x;
+  int64_t v = 0;
+#pragma unroll 4
+  for (int b = threadIdx.x; b < B; b += kThreads)
+    v += c < H ? (int64_t)hist[(int64_t)b * H + c] : c == H ? steps[b] : (int64_t)ties[b];
+  __shared__ long long red[kThreads / 64];
+  long long t = v;
+  for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = t;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int i = 1; i < kThreads / 64; ++i) t += red[i];
+    stats[c] = t;
+  }
+}
+
+// The totals, the non-finite flag and the groups' gates into mapped host
+// words, then the tag that the host polls.
+__global__ __launch_bounds__(128) void sampler_publish_kernel(const int64_t* __restrict__ stats,
+                                                              const int32_t* __restrict__ nan,
+                                                              const int32_t* __restrict__ act, int parity,
+                                                              int64_t* host, int64_t tag) {
+  const int t = threadIdx.x;
+  if (t < kStatNan) host[t] = stats[t];
+  if (t == kStatNan) host[t] = *nan;
+  if (t == kStatGate || t == kStatGate + 1) host[t] = act[2 * (t - kStatGate) + parity];
+  __threadfence_system();
+  __syncthreads();
+  if (t == 0) __atomic_store_n(host + kStatTag, tag, __ATOMIC_RELEASE);
 }
 
 __global__ void philox_words_kernel(uint64_t seed, int n, const uint32_t* ctr, uint32_t* out) {
@@ -181,12 +203,30 @@ __global__ void philox_normals_kernel(uint64_t seed, uint32_t chain, uint32_t rn
 
 }  // namespace
 
-hipError_t init_chains_launch(int B, int d, uint64_t seed, float* y, float* x0, int64_t x0c,
-                              hipStream_t s) {
+hipError_t init_chains_launch(int B, int d, uint64_t seed, float* y, hipStream_t s) {
   const int ng = (d + 3) / 4;
-  dim3 grid((ng + kThreads - 1) / kThreads, B);
-  return timed("init_chains", s,
-               [&] { init_chains_kernel<<<grid, kThreads, 0, s>>>(d, seed, y, x0, x0c); });
+  return launch_timed("init_chains", init_chains_kernel, dim3((ng + kThreads - 1) / kThreads, B), dim3(kThreads), s,
+                      d, seed, y, d % 4 == 0 && aligned16(y));
+}
+
+hipError_t sampler_init_launch(const Sched& sc, int B, int K, int d, uint64_t seed, float* y, float* x,
+                               int32_t* k2, uint32_t* rnd2, int32_t* crow2, int32_t* cstep2,
+                               int32_t* hist, int64_t* steps, int32_t* ties, int32_t* tau,
+                               int32_t* step, double* sigma, int32_t* act, int32_t* nan, hipStream_t s) {
+  const int ng = (d + 3) / 4;
+  return launch_timed("init_chains", sampler_init_kernel, dim3((ng + kThreads - 1) / kThreads, B), dim3(kThreads), s,
+                      sc, B, K, d, seed, y, x, d % 4 == 0 && aligned16(y) && aligned16(x), k2, rnd2, crow2, cstep2,
+                      hist, steps, ties, tau, step, sigma, act, nan);
+}
+
+hipError_t sampler_finish_launch(int B, const int32_t* hist, const int64_t* steps, const int32_t* ties,
+                                 const int32_t* nan, const int32_t* act, int parity, int64_t* stats,
+                                 int64_t* host, int64_t tag, hipStream_t s) {
+  sampler_totals_kernel<<<SD_MAX_BLOCK + 4, kThreads, 0, s>>>(B, hist, steps, ties, stats);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  sampler_publish_kernel<<<1, 128, 0, s>>>(stats, nan, act, parity, host, tag);
+  return hipGetLastError();
 }
 
 static bool draft_vec(int d, sd_stride xs, sd_stride mps, const float* y, const float* x,
@@ -228,17 +268,6 @@ hipError_t draft_cached_launch(const Sched& sc, const float4* coef, int B, int K
   });
 }
 
-hipError_t prepare_launch(const Sched& sc, int B, int K, const int32_t* k, int32_t* kb,
-                          int32_t* left, int32_t* step, double* sigma, int32_t* tau,
-                          int32_t* adv, int* cnt_cur, int* cnt_next, int64_t* hist,
-                          int64_t* steps, hipStream_t s) {
-  const int nb = (B + kThreads - 1) / kThreads;
-  return timed("prepare_round", s, [&] {
-    prepare_kernel<<<nb, kThreads, 0, s>>>(sc, B, K, k, kb, left, step, sigma, tau, adv, cnt_cur,
-                                           cnt_next, hist, steps);
-  });
-}
-
 hipError_t fill_i32_launch(int32_t* p, int64_t n, int32_t v, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   const int64_t nb = (n + 255) / 256;
@@ -249,13 +278,6 @@ hipError_t fill_i32_launch(int32_t* p, int64_t n, int32_t v, hipStream_t s) {
 hipError_t chains_active_launch(int B, int split, int N, const int32_t* k, int* f0, int* f1,
                                 hipStream_t s) {
   chains_active_kernel<<<1, kThreads, 0, s>>>(B, split, N, k, f0, f1);
-  return hipGetLastError();
-}
-
-hipError_t fill_i64_launch(int64_t* p, int64_t n, int64_t v, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  const int64_t nb = (n + 255) / 256;
-  fill_i64_kernel<<<(unsigned)nb, 256, 0, s>>>(p, n, v);
   return hipGetLastError();
 }
 

@@ -1,5 +1,4 @@
-// The new state of each chain after verification (Alg. 8, residual part) and
-// the sampler's commit step.
+// The new state of each chain after verification (Alg. 8, residual part).
 //
 // residual_kernel: one workgroup per chain.  For a rejection at tau the
 // Decomposition residual (Prop. 1, Alg. 5) is
@@ -181,32 +180,22 @@ __device__ __forceinline__ void reflection_row(int d, const float* yh, const flo
   }
 }
 
-// With COMMIT (the sampler) the same workgroup then advances the chain:
-// k <- min(k + tau, N), round <- round + 1, and records where the Free Drafter
-// finds its cached score next round (row min(tau, K_b) of this round's target
-// means, at step k + min(tau, K_b)) and how many steps the chain advanced.
 // Four wavefronts per SIMD (two 512-thread workgroups per compute unit): the
 // register budget of 128 keeps a second chain's loads in flight while one
 // workgroup reduces.
-template <bool COMMIT, bool VEC>
+template <bool VEC>
 __global__ __launch_bounds__(kMaxThreads, 4) void residual_kernel(
-    int B, int K, int d, int N, const float* __restrict__ yd, int64_t yc, int64_t yr,
+    int K, int d, const float* __restrict__ yd, int64_t yc, int64_t yr,
     const float* __restrict__ mp, int64_t pc, int64_t pr, const float* __restrict__ mq,
     int64_t qc, int64_t qr, const double* __restrict__ sigma, const int32_t* __restrict__ kbv,
     const int32_t* __restrict__ left, const int32_t* __restrict__ tauv,
-    const double* __restrict__ ures, const double* __restrict__ dn, uint32_t* rnd, uint64_t seed,
-    float* __restrict__ y, int32_t* kk, int32_t* crow, int32_t* cstep, int32_t* adv,
-    int32_t* trace, int r_round, int trace_rounds, bool reflect, const int* gate) {
+    const double* __restrict__ ures, const double* __restrict__ dn, const uint32_t* __restrict__ rnd,
+    uint64_t seed, float* __restrict__ y, bool reflect) {
   __shared__ double red[kMaxThreads / 64];
-  if (gate && *gate == 0) return;
   const int b = blockIdx.x;
   const int t = tauv[b];
   const int kb = min(kbv[b], K);
-  if (t <= 0 || kb <= 0 || t > kb + 1) {
-    if (COMMIT && threadIdx.x == 0 && trace && r_round < trace_rounds)
-      trace[(int64_t)r_round * B + b] = 0;
-    return;
-  }
+  if (t <= 0 || kb <= 0 || t > kb + 1) return;
   const uint32_t r = rnd[b];
   float* out = y + (int64_t)b * d;
   const int ng = (d + 3) / 4;
@@ -233,20 +222,6 @@ __global__ __launch_bounds__(kMaxThreads, 4) void residual_kernel(
     const float* src = yd + (int64_t)b * yc + (int64_t)(kb - 1) * yr;
     for (int i = threadIdx.x; i < d; i += blockDim.x) out[i] = src[i];
   }
-  if (COMMIT) {
-    __syncthreads();  // every thread has read rnd[b] before it changes
-    if (threadIdx.x == 0) {
-      const int k = kk[b];
-      const int knew = min(k + t, N);
-      const int cr = min(t, kb);
-      kk[b] = knew;
-      rnd[b] = r + 1u;
-      crow[b] = cr;
-      cstep[b] = min(k + cr, N - 1);
-      adv[b] = knew - k;
-      if (trace && r_round < trace_rounds) trace[(int64_t)r_round * B + b] = t;
-    }
-  }
 }
 
 // Threads per workgroup: one float4 group per thread up to 512 threads.
@@ -272,10 +247,9 @@ hipError_t residual_launch(int B, int K, int d, const float* yd, sd_stride ys, c
                            uint64_t seed, float* y, hipStream_t s) {
   const bool vec = residual_vec(d, mps, mqs, mp, mq, y);
   return timed("residual_draw", s, [&] {
-    (vec ? residual_kernel<false, true> : residual_kernel<false, false>)<<<B, residual_threads(d), 0, s>>>(
-        B, K, d, 0, yd, ys.chain, ys.row, mp, mps.chain, mps.row, mq, mqs.chain, mqs.row, sigma,
-        kb, left, tau, ures, dn, const_cast<uint32_t*>(rnd), seed, y, nullptr, nullptr, nullptr,
-        nullptr, nullptr, 0, 0, false, nullptr);
+    (vec ? residual_kernel<true> : residual_kernel<false>)<<<B, residual_threads(d), 0, s>>>(
+        K, d, yd, ys.chain, ys.row, mp, mps.chain, mps.row, mq, mqs.chain, mqs.row, sigma, kb, left,
+        tau, ures, dn, rnd, seed, y, false);
   });
 }
 
@@ -284,26 +258,9 @@ hipError_t reflection_launch(int B, int K, int d, const float* yd, sd_stride ys,
                              const int32_t* kb, const int32_t* left, const int32_t* tau,
                              const uint32_t* rnd, uint64_t seed, float* y, hipStream_t s) {
   return timed("residual_reflect", s, [&] {
-    residual_kernel<false, false><<<B, residual_threads(d), 0, s>>>(
-        B, K, d, 0, yd, ys.chain, ys.row, mp, mps.chain, mps.row, mq, mqs.chain, mqs.row, sigma,
-        kb, left, tau, nullptr, nullptr, const_cast<uint32_t*>(rnd), seed, y, nullptr, nullptr,
-        nullptr, nullptr, nullptr, 0, 0, true, nullptr);
-  });
-}
-
-hipError_t residual_commit_launch(int B, int K, int d, int N, const float* yd, sd_stride ys,
-                                  const float* mp, sd_stride mps, const float* mq, sd_stride mqs,
-                                  const double* sigma, const int32_t* kb, const int32_t* left,
-                                  const int32_t* tau, const double* ures, const double* dn,
-                                  uint32_t* rnd, uint64_t seed, float* y, int32_t* k,
-                                  int32_t* crow, int32_t* cstep, int32_t* adv, int32_t* trace,
-                                  int r, int trace_rounds, hipStream_t s, const int* gate) {
-  const bool vec = residual_vec(d, mps, mqs, mp, mq, y);
-  return timed("residual_commit", s, [&] {
-    (vec ? residual_kernel<true, true> : residual_kernel<true, false>)<<<B, residual_threads(d), 0, s>>>(
-        B, K, d, N, yd, ys.chain, ys.row, mp, mps.chain, mps.row, mq, mqs.chain, mqs.row, sigma,
-        kb, left, tau, ures, dn, rnd, seed, y, k, crow, cstep, adv, trace, r, trace_rounds, false,
-        gate);
+    residual_kernel<false><<<B, residual_threads(d), 0, s>>>(
+        K, d, yd, ys.chain, ys.row, mp, mps.chain, mps.row, mq, mqs.chain, mqs.row, sigma, kb, left,
+        tau, nullptr, nullptr, rnd, seed, y, true);
   });
 }
 
