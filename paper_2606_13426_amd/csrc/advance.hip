@@ -42,13 +42,17 @@ __global__ __launch_bounds__(kThreads) void advance_kernel(
     double* __restrict__ sigma, int32_t* __restrict__ hist, int64_t* __restrict__ steps,
     int* act_next, int32_t* __restrict__ trace, int r_round, int trace_rounds, bool vec_ok,
     bool frozen, bool stream, const int* gate, int chain0, int trace_ld) {
-  if (gate && *gate == 0) return;
+  // every scalar input is requested before the first is used (the gate too)
+  __shared__ float4 cfs[SD_MAX_BLOCK];
   const int N = sc.N, K1 = K + 1;
   const int b = blockIdx.y;
   const uint32_t chain = (uint32_t)(chain0 + b);  // the generator's chain index
   const int t = tauv[b];
   const int k = kcur[b];
   const uint32_t r = rcur[b];
+  const int rm = rmode[b], cstep_now = cstep_cur[b];
+  const float sg = rsig[b], cf = rcoef[b];
+  if (gate && *gate == 0) return;
   const bool active = t > 0;
   const int kb = active ? min(K, N - k) : 0;
   const int knew = active ? min(k + t, N) : k;
@@ -67,7 +71,7 @@ __global__ __launch_bounds__(kThreads) void advance_kernel(
       knext[b] = k;
       rnext[b] = r;
       crow_next[b] = crow_cur[b];
-      cstep_next[b] = cstep_cur[b];
+      cstep_next[b] = cstep_now;
     }
     if (trace && r_round < trace_rounds) trace[(int64_t)r_round * trace_ld + b] = active ? t : 0;
   }
@@ -78,6 +82,12 @@ __global__ __launch_bounds__(kThreads) void advance_kernel(
     step[(int64_t)b * K1 + j] = min(knew + j, N - 1);
     sigma[(int64_t)b * K1 + j] = sched_sigma(sc, min(knew + j, N));
   }
+  const float4 cc = step_coef(sc, coef, cs);
+  const bool drafts = !frozen && knew < N;
+  if (drafts) {
+    draft_coefs(sc, coef, knew, min(K, N - knew), cc.w, cfs);
+    __syncthreads();
+  }
   const int g = blockIdx.x * kThreads + threadIdx.x;
   const int e0 = 4 * g;
   if (e0 >= d) return;
@@ -87,7 +97,6 @@ __global__ __launch_bounds__(kThreads) void advance_kernel(
   float* sb = SV + (int64_t)b * d + e0;
   const float* qb = MQ + (int64_t)b * K1 * d + e0;
   float yv[4];
-  const int rm = rmode[b];
   if (rm == 1) {
     // m^p of row t - 1 from its draft state and this round's cache
     float xv[4], qv[4], sv[4];
@@ -95,8 +104,7 @@ __global__ __launch_bounds__(kThreads) void advance_kernel(
     load4(qb + (int64_t)(t - 1) * d, cnt, vec, qv);
     load4(sb, cnt, vec, sv);
     const float4 cn = step_coef(sc, coef, k + t - 1);
-    const float c2s = cn.y * step_coef(sc, coef, cstep_cur[b]).w;
-    const float sg = rsig[b], cf = rcoef[b];
+    const float c2s = cn.y * step_coef(sc, coef, cstep_now).w;
     const float4 z = normals4(philox((uint32_t)g, chain, r, TAG_RESID << 24, seed));
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -111,8 +119,7 @@ __global__ __launch_bounds__(kThreads) void advance_kernel(
     load4(qb + (int64_t)(t - 1) * d, cnt, vec, qv);
     load4(sb, cnt, vec, sv);
     const float4 cn = step_coef(sc, coef, k + t - 1);
-    const float c2s = cn.y * step_coef(sc, coef, cstep_cur[b]).w;
-    const float cf = rcoef[b];
+    const float c2s = cn.y * step_coef(sc, coef, cstep_now).w;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       const float pv = draft_mean(cn.x, xv[c], c2s, sv[c]);
@@ -121,7 +128,6 @@ __global__ __launch_bounds__(kThreads) void advance_kernel(
   } else if (rm == 2) {
     float qv[4];
     load4(qb + (int64_t)kb * d, cnt, vec, qv);
-    const float sg = rsig[b];
     const float4 z = normals4(philox((uint32_t)g, chain, r, TAG_TARGET << 24, seed));
 #pragma unroll
     for (int c = 0; c < 4; ++c) yv[c] = qv[c] + sg * get4(z, c);
@@ -140,13 +146,11 @@ __global__ __launch_bounds__(kThreads) void advance_kernel(
   float xcv[4], qcv[4], sv[4];
   load4(xb + (int64_t)cr * d, cnt, vec, xcv);
   load4(qb + (int64_t)cr * d, cnt, vec, qcv);
-  const float4 cc = step_coef(sc, coef, cs);
 #pragma unroll
   for (int c = 0; c < 4; ++c) sv[c] = qcv[c] - cc.x * xcv[c];  // c2_c S_c
   store4(sb, cnt, vec, sv);
   store4(xb, cnt, vec, yv, stream);
-  draft_rows(sc, coef, K, knew, min(K, N - knew), chain, r + 1u, seed, g, yv, sv, cc.w, xb,
-             d, nullptr, d, cnt, vec, stream);
+  draft_rows(cfs, K, min(K, N - knew), chain, r + 1u, seed, g, yv, sv, xb, d, nullptr, d, cnt, vec, stream);
 }
 
 }  // namespace

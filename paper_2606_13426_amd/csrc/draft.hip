@@ -83,37 +83,37 @@ __global__ __launch_bounds__(kThreads) void draft_kernel(
     int64_t xr, float* __restrict__ mp, int64_t mc, int64_t mr, float* __restrict__ svout,
     bool vec_ok, bool stream, const int* gate, int chain0) {
   if (gate && *gate == 0) return;
+  __shared__ float4 cfs[SD_MAX_BLOCK];
   const int b = blockIdx.y;
-  const int g = blockIdx.x * kThreads + threadIdx.x;
-  const int e0 = 4 * g;
-  if (e0 >= d) return;
   const int k = kk[b];
   if (k >= sc.N) return;
   const int kb = min(K, sc.N - k);
   const uint32_t r = rnd[b];
+  const float4 cc = CACHE_FROM_MEANS ? step_coef(sc, coef, cstep[b]) : make_float4(0.f, 0.f, 0.f, 1.0f);
+  draft_coefs(sc, coef, k, kb, cc.w, cfs);
+  __syncthreads();
+  const int g = blockIdx.x * kThreads + threadIdx.x;
+  const int e0 = 4 * g;
+  if (e0 >= d) return;
   const int cnt = min(4, d - e0);
   const bool vec = vec_ok && cnt == 4;
   float yv[4], sv[4];
   float* xb = x + (int64_t)b * xc + e0;
   float* mb = mp ? mp + (int64_t)b * mc + e0 : nullptr;
   load4(y + (int64_t)b * d + e0, cnt, vec, yv);
-  float scale = 1.0f;
   if (CACHE_FROM_MEANS) {
     const int cr = crow[b];
-    const float4 cc = step_coef(sc, coef, cstep[b]);
     float xcv[4], qcv[4];
     load4(xb + (int64_t)cr * xr, cnt, vec, xcv);
     load4(mqprev + (int64_t)b * qc + (int64_t)cr * qr + e0, cnt, vec, qcv);
 #pragma unroll
     for (int c = 0; c < 4; ++c) sv[c] = qcv[c] - cc.x * xcv[c];  // c2_c S_c
-    scale = cc.w;
     if (svout) store4(svout + (int64_t)b * d + e0, cnt, vec, sv);
   } else {
     load4(cs + (int64_t)b * d + e0, cnt, vec, sv);
   }
   store4(xb, cnt, vec, yv, stream);
-  draft_rows(sc, coef, K, k, kb, (uint32_t)(chain0 + b), r, seed, g, yv, sv, scale, xb, xr, mb, mr,
-             cnt, vec, stream);
+  draft_rows(cfs, K, kb, (uint32_t)(chain0 + b), r, seed, g, yv, sv, xb, xr, mb, mr, cnt, vec, stream);
 }
 
 __global__ void fill_i32_kernel(int32_t* p, int64_t n, int32_t v) {
@@ -241,7 +241,8 @@ hipError_t draft_launch(const Sched& sc, int B, int K, int d, const float* y, co
   const int ng = (d + 3) / 4;
   dim3 grid((ng + kThreads - 1) / kThreads, B);
   const bool vec = draft_vec(d, xs, mps, y, x, mp) && aligned16(cs);
-  const bool stream = stream_rows((int64_t)B * (K + 1) * d * 4);
+  // (both blocks are written: together they decide what the cache can hold)
+  const bool stream = stream_rows((int64_t)B * (2 * K + 1) * d * 4);
   return timed("draft_block", s, [&] {
     draft_kernel<false><<<grid, kThreads, 0, s>>>(sc, nullptr, K, d, y, cs, nullptr, nullptr, nullptr, 0, 0,
                                                   k, rnd, seed, x, xs.chain, xs.row, mp, mps.chain,
