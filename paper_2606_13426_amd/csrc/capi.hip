@@ -15,7 +15,6 @@
 #include <vector>
 
 #include "common.hpp"
-#include "gemm_split.hpp"
 
 namespace sd {
 
@@ -178,13 +177,6 @@ sd_status sd_schedule_table(const sd_schedule* sched, double* host_out) {
 }
 
 // ---------------------------------------------------------------- target --
-// float32 -> bf16 bits, round to nearest even (finite inputs).
-static uint16_t bf16_rne(float f) {
-  uint32_t u;
-  memcpy(&u, &f, 4);
-  return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
-}
-
 sd_status sd_target_create(const sd_schedule* sched, int32_t d, int32_t n_comp, const float* mu,
                            const float* var, const float* log_w, sd_precision precision,
                            sd_target* out) {
@@ -200,7 +192,6 @@ sd_status sd_target_create(const sd_schedule* sched, int32_t d, int32_t n_comp, 
     SD_CHECK_ARG(isfinite(log_w[m]), "sd_target_create: log_w[%d] is not finite", m);
   }
   const size_t M = (size_t)n_comp, D = (size_t)d;
-  std::vector<float> muT(D * M);
   std::vector<double> vv(M), lw(M), msq(M);
   for (size_t m = 0; m < M; ++m) {
     double s = 0.0;
@@ -211,7 +202,6 @@ sd_status sd_target_create(const sd_schedule* sched, int32_t d, int32_t n_comp, 
         return SD_EINVAL;
       }
       s += (double)x * (double)x;
-      muT[i * M + m] = x;
     }
     msq[m] = s;
     vv[m] = var[m];
@@ -230,12 +220,14 @@ sd_status sd_target_create(const sd_schedule* sched, int32_t d, int32_t n_comp, 
   const size_t o_ls = 0, o_logw = a256(o_ls + sizeof(double2) * M * Ns), o_musq = a256(o_logw + sizeof(double) * M),
                o_coef = a256(o_musq + sizeof(double) * M), o_sig = a256(o_coef + sizeof(float4) * (Ns + 1)),
                table_bytes = o_sig + sizeof(double) * (Ns + 1);
-  bool ok = (bf ? hipMalloc(&t->mu16, sizeof(uint16_t) * M * D) == hipSuccess &&
-                      hipMalloc(&t->muT16, sizeof(uint16_t) * M * D) == hipSuccess
-                : hipMalloc(&t->mu, sizeof(float) * M * D) == hipSuccess &&
-                      hipMalloc(&t->muT, sizeof(float) * M * D) == hipSuccess &&
-                      hipMalloc(&t->mu_split, sizeof(uint16_t) * 3 * M * D) == hipSuccess &&
-                      hipMalloc(&t->muT_split, sizeof(uint16_t) * 3 * M * D) == hipSuccess) &&
+  t->Mp = (n_comp + 63) / 64 * 64;
+  t->dp = (int)((D + 7) / 8 * 8);
+  t->Mk = (n_comp + 7) / 8 * 8;
+  const size_t planes = bf ? 1 : 3, na = planes * M * (size_t)t->dp, nt = planes * D * (size_t)t->Mk;
+  uint16_t *&opa = bf ? t->mu16 : t->mu_split, *&opt = bf ? t->muT16 : t->muT_split;
+  bool ok = hipMalloc(&t->mu, sizeof(float) * M * D) == hipSuccess &&
+            hipMalloc(&opa, sizeof(uint16_t) * (na + kOperandSlack)) == hipSuccess &&
+            hipMalloc(&opt, sizeof(uint16_t) * (nt + kOperandSlack)) == hipSuccess &&
             hipMalloc(&t->tables, table_bytes) == hipSuccess;
   if (!ok) {
     set_error("sd_target_create: device allocation failed");
@@ -270,30 +262,11 @@ sd_status sd_target_create(const sd_schedule* sched, int32_t d, int32_t n_comp, 
     sd_target_destroy(reinterpret_cast<sd_target>(t));
     return SD_EHIP;
   }
-  if (bf) {
-    std::vector<uint16_t> h(M * D), hT(M * D);
-    for (size_t m = 0; m < M; ++m)
-      for (size_t i = 0; i < D; ++i) {
-        const uint16_t v = bf16_rne(mu[m * D + i]);
-        h[m * D + i] = v;
-        hT[i * M + m] = v;
-      }
-    ok = hipMemcpy(t->mu16, h.data(), sizeof(uint16_t) * M * D, hipMemcpyHostToDevice) ==
-             hipSuccess &&
-         hipMemcpy(t->muT16, hT.data(), sizeof(uint16_t) * M * D, hipMemcpyHostToDevice) ==
-             hipSuccess;
-  } else {
-    const size_t n = M * D;
-    std::vector<uint16_t> sp(3 * n), spT(3 * n);
-    split::split_host(mu, n, sp.data(), sp.data() + n, sp.data() + 2 * n);
-    split::split_host(muT.data(), n, spT.data(), spT.data() + n, spT.data() + 2 * n);
-    ok = hipMemcpy(t->mu, mu, sizeof(float) * n, hipMemcpyHostToDevice) == hipSuccess &&
-         hipMemcpy(t->muT, muT.data(), sizeof(float) * n, hipMemcpyHostToDevice) == hipSuccess &&
-         hipMemcpy(t->mu_split, sp.data(), sizeof(uint16_t) * 3 * n, hipMemcpyHostToDevice) ==
-             hipSuccess &&
-         hipMemcpy(t->muT_split, spT.data(), sizeof(uint16_t) * 3 * n, hipMemcpyHostToDevice) ==
-             hipSuccess;
-  }
+  // the operand planes are made on the device (rounding, split and transpose)
+  ok = hipMemcpy(t->mu, mu, sizeof(float) * M * D, hipMemcpyHostToDevice) == hipSuccess &&
+       fill_i32_launch(reinterpret_cast<int32_t*>(opa + na), kOperandSlack / 2, 0, nullptr) == hipSuccess &&
+       fill_i32_launch(reinterpret_cast<int32_t*>(opt + nt), kOperandSlack / 2, 0, nullptr) == hipSuccess &&
+       operands_launch(*t, (int)planes, t->mu, opa, opt, nullptr) == hipSuccess;
   std::vector<char> tables(table_bytes);
   auto host_at = [&](size_t o) { return tables.data() + o; };
   double2* ls = reinterpret_cast<double2*>(host_at(o_ls));
@@ -312,7 +285,12 @@ sd_status sd_target_create(const sd_schedule* sched, int32_t d, int32_t n_comp, 
       ls[(size_t)n * M + m] = make_double2(log(s2), 1.0 / s2);
     }
   }
-  ok = ok && hipMemcpy(t->tables, tables.data(), table_bytes, hipMemcpyHostToDevice) == hipSuccess;
+  ok = ok && hipMemcpy(t->tables, tables.data(), table_bytes, hipMemcpyHostToDevice) == hipSuccess &&
+       hipStreamSynchronize(nullptr) == hipSuccess;
+  if (bf) {
+    (void)hipFree(t->mu);
+    t->mu = nullptr;
+  }
   if (!ok) {
     set_error("sd_target_create: copy to device failed");
     sd_target_destroy(reinterpret_cast<sd_target>(t));
@@ -326,7 +304,6 @@ sd_status sd_target_destroy(sd_target target) {
   if (!target) return SD_OK;
   Target* t = reinterpret_cast<Target*>(target);
   if (t->mu) (void)hipFree(t->mu);
-  if (t->muT) (void)hipFree(t->muT);
   if (t->mu_split) (void)hipFree(t->mu_split);
   if (t->muT_split) (void)hipFree(t->muT_split);
   if (t->mu16) (void)hipFree(t->mu16);
@@ -376,14 +353,22 @@ sd_status sd_target_mean_noalloc(sd_target target, int32_t rows, const float* x,
   SD_CHECK_ARG(x && step && mq, "sd_target_mean_noalloc: x, step and mq must be non-NULL");
   SD_CHECK_ARG(x_row_stride >= t.d && mq_row_stride >= t.d, "sd_target_mean_noalloc: row strides must be >= d = %d", t.d);
   SD_CHECK_ARG(!score || score_row_stride >= t.d, "sd_target_mean_noalloc: score row stride must be >= d");
-  const size_t need = target_ws_bytes(t, rows);
+  // The limit is on rows of M components; the kernels' rows hold Mp.  Where
+  // those exceed the scratch the rows go in parts, each summed as the whole.
+  const size_t need = target_ws_bytes_unpadded(t, rows);
   SD_CHECK_ARG(need <= kScratchBytes,
                "sd_target_mean_noalloc: %d rows need %zu bytes of scratch, more than the %zu it holds "
                "(split the rows over calls)", rows, need, kScratchBytes);
+  int part = rows;
+  while (part > 1 && target_ws_bytes(t, part, rows) > kScratchBytes) part = (part + 1) / 2;
   void* ws = nullptr;
   SD_HIP(scratch_address(&ws));
-  SD_HIP(target_mean_launch(t, rows, x, x_row_stride, step, mq, mq_row_stride, score,
-                            score_row_stride, ws, (hipStream_t)stream, nullptr));
+  for (int r = 0; r < rows; r += part) {
+    const int n = std::min(part, rows - r);
+    SD_HIP(target_mean_launch(t, n, x + r * x_row_stride, x_row_stride, step + r, mq + r * mq_row_stride,
+                              mq_row_stride, score ? score + r * score_row_stride : nullptr, score_row_stride, ws,
+                              (hipStream_t)stream, nullptr, rows));
+  }
   return SD_OK;
 }
 

@@ -90,15 +90,18 @@ struct Target {
   Sched sc;
   int d, M;
   sd_precision prec;
-  float* mu;      // [M][d]
-  float* muT;     // [d][M]
-  uint16_t* mu16;   // [M][d] bf16 (round to nearest even), bf16 precision only
-  uint16_t* muT16;  // [d][M] bf16, bf16 precision only
+  // Row lengths: Mp = M rounded up to 64 (partial logits, P), dp and Mk = d
+  // and M rounded up to 8 (the bf16 operand planes, whose rows start at
+  // 16-byte addresses; kOperandSlack elements follow the last plane, for the
+  // chunk that crosses the last row's end).
+  int Mp, dp, Mk;
+  float* mu;      // [M][d], float32 precision only
+  uint16_t* mu16;   // [M][dp] bf16 (round to nearest even), bf16 precision only
+  uint16_t* muT16;  // [d][Mk] bf16, bf16 precision only
   // float32 precision: the exact three-term bf16 splits of mu and mu^T
-  // (planes hi, mid, lo, each [M][d] resp. [d][M]) for the matrix-core
-  // contractions of gemm_split.hpp
-  uint16_t* mu_split;   // [3][M][d]
-  uint16_t* muT_split;  // [3][d][M]
+  // (planes hi, mid, lo) for the matrix-core contractions of gemm_split.hpp
+  uint16_t* mu_split;   // [3][M][dp]
+  uint16_t* muT_split;  // [3][d][Mk]
   void* tables;   // one allocation that holds the five tables below
   double* logw;   // [M]
   double* musq;   // [M] ||mu_m||^2 (float64 from the float32 means)
@@ -122,6 +125,7 @@ struct Target {
   hipStream_t side[64];
   hipEvent_t fork[64], join[64];  // its events, made with it
 };
+constexpr int kOperandSlack = 64;
 constexpr int kFlagGroups = 64, kFlagSlots = 4;
 // tau histogram, steps, ties (SD_MAX_BLOCK + 4 totals), non-finite flag, the
 // two chain groups' gates, tag
@@ -130,12 +134,19 @@ constexpr int kStatNan = SD_MAX_BLOCK + 4, kStatGate = kStatNan + 1, kStatTag = 
 static_assert(kStatTag < kStatWords, "the words hold every total and the tag");
 static_assert(sizeof(Target::side) / sizeof(hipStream_t) == kFlagGroups, "one side stream per flag group");
 
+// The bf16 operand planes of the device array mu [M][d] (3: the exact split, 1:
+// rounded), A [planes][M][dp] and T [planes][d][Mk].
+hipError_t operands_launch(const Target& t, int planes, const float* mu, uint16_t* A, uint16_t* T, hipStream_t s);
+
 // Workspace of a target call on `rows` rows whose logits GEMM is split over d
 // as for plan_rows rows (0: rows).  The split fixes the order in which the
 // partial logits are summed, so calls on parts of a batch that take the
 // whole batch's row count here give every row the same result as one call.
 size_t target_ws_bytes(const Target& t, int rows, int plan_rows = 0);
 size_t target_ws_bytes_bf16(const Target& t, int rows, int plan_rows = 0);
+// The same with rows of M components (the measure of sd_target_mean_noalloc's limit).
+size_t target_ws_bytes_unpadded(const Target& t, int rows);
+size_t target_ws_bytes_unpadded_bf16(const Target& t, int rows);
 // Rows' EM means (and scores if score != nullptr).  gate: nullable device flag;
 // when it reads 0 every kernel exits at once (finished sampler rounds).
 hipError_t target_mean_launch(const Target& t, int rows, const float* x, int64_t ldx,

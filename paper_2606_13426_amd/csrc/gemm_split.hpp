@@ -16,18 +16,22 @@
 // r) .. + 15, r < RB) and all four 16-column blocks, so each B fragment read
 // from LDS feeds RB row blocks.  A (float32) goes from memory straight into
 // its wavefront's registers, lane l holding row 16 (RB w + r) + l % 16 and
-// k = 8 (l / 16) .. + 7 of each 32-wide step, and is split there.  B comes pre-split (three
-// bf16 planes in memory, row-major with the same leading dimension) and is
-// staged through LDS, 64 k per chunk, three planes of 64 x 72 (row stride 144
-// bytes: the 16 rows of one 16-lane read pass fall in distinct banks).
-// Output block c of row block r of wavefront w: lane l holds rows
-// 16 (RB w + r) + 4 (l / 16) + j (j < 4) of column 16 c + l % 16.
+// k = 8 (l / 16) .. + 7 of each 32-wide step, and is split there.  B comes
+// pre-split (three bf16 planes in memory, row-major) and is staged through
+// LDS, 64 k per chunk, three planes of 64 x 72 (row stride 144 bytes: the 16
+// rows of one 16-lane read pass fall in distinct banks).
+// B is the matrix instruction's first operand, so that a lane's four
+// accumulators of output block c are four CONSECUTIVE columns 16 c + 4 (l / 16)
+// .. + 3 of row l % 16 of its row block: 16-byte stores and epilogue accesses.
 //
-// The aligned path only: every row 16-byte aligned, k ranges whole chunks,
-// rows past a matrix read as zero from the tile's buffer views.
+// Any shape: rows of A and B past the matrix repeat its last row (their outputs
+// are not stored, or masked); A's rows may lie at any 4-byte address (16-byte
+// loads need no more), and only the chunk that crosses the row's end loads
+// element by element, reading zero past it.  B's rows start at multiples of 8
+// elements; past a row's end it reads whatever finite values follow (the last
+// plane has a chunk of slack), which meet A's zeros.
 #pragma once
 
-#include "bufio.hpp"
 #include "common.hpp"
 
 namespace sd {
@@ -65,23 +69,38 @@ __device__ __forceinline__ void split8(const float4& u, const float4& v, bf16x8&
   }
 }
 
+// Four floats at any 4-byte address.
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+
+__device__ __forceinline__ float4 ld4u(const float* p) {
+  const f4u v = *reinterpret_cast<const f4u*>(p);
+  return make_float4(v[0], v[1], v[2], v[3]);
+}
+
 // B chunk in registers: plane p, rows t / 8 + 32 h (h < 2), k = 8 (t % 8) .. + 7.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 struct BChunk {
-  uint4 v[3][2];
+  u32x4 v[3][2];
 };
 
-// views[p]: the (at most 64) rows of plane p of the tile.
-__device__ __forceinline__ void load_b(const __amdgpu_buffer_rsrc_t (&views)[3], int64_t ldb,
-                                       int k0, BChunk& c) {
-  const int t = threadIdx.x;
-  const uint32_t base = (uint32_t)(((t >> 3) * (int)ldb + 8 * (t & 7)) * 2);
-  const uint32_t hstep = (uint32_t)(32 * (int)ldb * 2);
-  const int so = __builtin_amdgcn_readfirstlane(k0 * 2);
+// The thread's piece of the 64 rows row0.. (nrows exist) of the three planes
+// (each `plane` elements, leading dimension ld): pointers at k = 0.
+struct BRows {
+  const uint16_t* p[3];
+  int64_t hstep;  // to the row 32 further down
+};
+__device__ __forceinline__ BRows b_rows(const uint16_t* planes, int64_t plane, int64_t ld, int nrows, int row0) {
+  const int t = threadIdx.x, last = nrows - 1;
+  const int64_t r = min(row0 + (t >> 3), last), r2 = min(row0 + (t >> 3) + 32, last);
+  const uint16_t* q = planes + r * ld + 8 * (t & 7);
+  return BRows{{q, q + plane, q + 2 * plane}, (r2 - r) * ld};
+}
+
+__device__ __forceinline__ void load_b(const BRows& b, int k0, BChunk& c) {
 #pragma unroll
   for (int p = 0; p < 3; ++p)
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
-      c.v[p][h] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(views[p], base + h * hstep, so, 0));
+    for (int h = 0; h < 2; ++h) c.v[p][h] = *reinterpret_cast<const u32x4*>(b.p[p] + h * b.hstep + k0);
 }
 
 __device__ __forceinline__ void store_b(uint16_t* lds, const BChunk& c) {
@@ -90,7 +109,7 @@ __device__ __forceinline__ void store_b(uint16_t* lds, const BChunk& c) {
   for (int p = 0; p < 3; ++p)
 #pragma unroll
     for (int h = 0; h < 2; ++h)
-      *reinterpret_cast<uint4*>(&lds[p * kPlaneElems + ((t >> 3) + 32 * h) * LDH + 8 * (t & 7)]) = c.v[p][h];
+      *reinterpret_cast<u32x4*>(&lds[p * kPlaneElems + ((t >> 3) + 32 * h) * LDH + 8 * (t & 7)]) = c.v[p][h];
 }
 
 // A chunk of this lane's row: k = 32 s + 8 (l / 16) .. + 7 for s < 2.
@@ -98,20 +117,54 @@ struct AChunk {
   float4 v[2][2];
 };
 
-// view: the (at most 64 RB) rows of A of the tile; lane rows 16 (RB w + r) + l % 16.
+// This lane's rows of A (nrows of them exist, leading dimension ld): pointers
+// at k = 8 (l / 16).
 template <int RB>
-__device__ __forceinline__ void load_a(__amdgpu_buffer_rsrc_t view, int64_t lda, int k0, AChunk (&a)[RB]) {
+struct ARows {
+  const float* p[RB];
+};
+template <int RB>
+__device__ __forceinline__ ARows<RB> a_rows(const float* A, int64_t ld, int nrows, int r0) {
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int so = __builtin_amdgcn_readfirstlane(k0 * 4);
+  ARows<RB> a;
 #pragma unroll
-  for (int r = 0; r < RB; ++r) {
-    const uint32_t base = (uint32_t)(((16 * (RB * w + r) + (lane & 15)) * (int)lda + 8 * (lane >> 4)) * 4);
+  for (int r = 0; r < RB; ++r)
+    a.p[r] = A + (int64_t)min(r0 + 16 * (RB * w + r) + (lane & 15), nrows - 1) * ld + 8 * (lane >> 4);
+  return a;
+}
+
+// The chunk at k0 (whole inside the rows).
+template <int RB>
+__device__ __forceinline__ void load_a(const ARows<RB>& rows, int k0, AChunk (&a)[RB]) {
+#pragma unroll
+  for (int r = 0; r < RB; ++r)
 #pragma unroll
     for (int s = 0; s < 2; ++s)
 #pragma unroll
-      for (int q = 0; q < 2; ++q)
-        a[r].v[s][q] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(view, base + (uint32_t)((32 * s + 4 * q) * 4), so, 0));
-  }
+      for (int q = 0; q < 2; ++q) a[r].v[s][q] = ld4u(rows.p[r] + k0 + 32 * s + 4 * q);
+}
+
+// The chunk at k0 of rows of len < k0 + 64 elements, zero past them (loads from
+// the row's start where an element does not exist: no branch).
+template <int RB>
+__device__ __forceinline__ void load_a_tail(const ARows<RB>& rows, int k0, int len, AChunk (&a)[RB]) {
+  const int back = 8 * ((threadIdx.x & 63) >> 4);  // the row's start lies `back` elements before p
+#pragma unroll
+  for (int r = 0; r < RB; ++r)
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        float f[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const int k = k0 + 32 * s + 4 * q + c;
+          const bool in = k + back < len;
+          const float v = rows.p[r][in ? k : -back];
+          f[c] = in ? v : 0.0f;
+        }
+        a[r].v[s][q] = make_float4(f[0], f[1], f[2], f[3]);
+      }
 }
 
 // float64 sum of squares of the lane's A values of a chunk.
@@ -148,31 +201,29 @@ __device__ __forceinline__ void mma_chunk(const uint16_t* lds, const AChunk (&a)
 #pragma unroll
       for (int r = 0; r < RB; ++r) {
         f32x4 c = acc[r].c[b];
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[r], bh, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[r], bl, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am[r], bm, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am[r], bh, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[r], bm, c, 0, 0, 0);
-        acc[r].c[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[r], bh, c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh, al[r], c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bl, ah[r], c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bm, am[r], c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh, am[r], c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bm, ah[r], c, 0, 0, 0);
+        acc[r].c[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh, ah[r], c, 0, 0, 0);
       }
     }
   }
 }
 
-// Accumulate the tile over the chunks of k in [kbeg, kend) (whole chunks, at
-// least one), starting from the first chunk already loaded into ra, rb (so a
-// caller can issue other loads after them: the first wait then excludes
-// those), the B planes staged through `lds` (kLdsBytes); with SQ also this
-// lane's float64 squares of A.  Later chunks are loaded when they are due,
-// not a chunk ahead: a prefetch register set would cost the occupancy that
-// hides those loads behind the other workgroups' matrix work.  The caller's
-// first use of lds afterwards must follow a barrier.
+// Accumulate the tile over the chunks of k in [kbeg, kend) (at least one, all
+// inside A's rows), starting from the first chunk already loaded into ra, rb (so a caller can issue other loads after them:
+// the first wait then excludes those), the B planes staged through `lds`
+// (kLdsBytes); with SQ also this lane's float64 squares of A.  Later chunks
+// are loaded when they are due, not a chunk ahead: a prefetch register set
+// would cost the occupancy that hides those loads behind the other
+// workgroups' matrix work.  The caller's first use of lds afterwards must
+// follow a barrier.
 template <bool SQ, int RB>
-__device__ __forceinline__ void tile_run(uint16_t* lds, __amdgpu_buffer_rsrc_t va, int64_t lda,
-                                         const __amdgpu_buffer_rsrc_t (&vb)[3], int64_t ldb,
-                                         int kbeg, int kend, AChunk (&ra)[RB], BChunk& rb,
-                                         Acc (&acc)[RB], double (&sq)[RB]) {
-  const int n = (kend - kbeg) / KC;
+__device__ __forceinline__ void tile_run(uint16_t* lds, const ARows<RB>& arows, const BRows& brows,
+                                         int kbeg, int kend, AChunk (&ra)[RB], BChunk& rb, Acc (&acc)[RB],
+                                         double (&sq)[RB]) {
   store_b(lds, rb);
   __syncthreads();
   if constexpr (SQ) {
@@ -180,9 +231,9 @@ __device__ __forceinline__ void tile_run(uint16_t* lds, __amdgpu_buffer_rsrc_t v
     for (int r = 0; r < RB; ++r) sq[r] += squares(ra[r]);
   }
   mma_chunk<RB>(lds, ra, acc);
-  for (int c = 1; c < n; ++c) {
-    load_b(vb, ldb, kbeg + c * KC, rb);
-    load_a<RB>(va, lda, kbeg + c * KC, ra);
+  for (int k0 = kbeg + KC; k0 < kend; k0 += KC) {
+    load_b(brows, k0, rb);
+    load_a<RB>(arows, k0, ra);
     __syncthreads();  // every wavefront is done with the previous chunk
     store_b(lds, rb);
     __syncthreads();
@@ -194,45 +245,31 @@ __device__ __forceinline__ void tile_run(uint16_t* lds, __amdgpu_buffer_rsrc_t v
   }
 }
 
-// The (at most 64) rows r0.. of a row-major bf16 plane with leading dimension ld.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rows(const uint16_t* P, int64_t ld, int nrows,
-                                                           int r0) {
-  return buf_view(P + (int64_t)r0 * ld, (int64_t)max(0, min(nrows - r0, TILE)) * ld * 2);
-}
-
-// Row (inside the tile) of accumulator element j of row block r, and column
-// of block b.
-template <int RB>
-__device__ __forceinline__ int out_row(int r, int j) {
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  return 16 * (RB * w + r) + 4 * (lane >> 4) + j;
-}
-__device__ __forceinline__ int out_col(int b) { return 16 * b + (threadIdx.x & 15); }
-
-// The three bf16 planes of a float32 matrix [rows][cols] (host, row-major),
-// each [rows][cols]: the split above, evaluated on the host.
-inline uint16_t bf16_bits_rne(float f) {
-  uint32_t u;
-  __builtin_memcpy(&u, &f, 4);
-  return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
-}
-inline float bf16_value(uint16_t h) {
-  const uint32_t u = (uint32_t)h << 16;
-  float f;
-  __builtin_memcpy(&f, &u, 4);
-  return f;
-}
-inline void split_host(const float* src, size_t n, uint16_t* hi, uint16_t* mid, uint16_t* lo) {
-  for (size_t i = 0; i < n; ++i) {
-    const float v = src[i];
-    const uint16_t h = bf16_bits_rne(v);
-    const float r = v - bf16_value(h);
-    const uint16_t m = bf16_bits_rne(r);
-    hi[i] = h;
-    mid[i] = m;
-    lo[i] = bf16_bits_rne(r - bf16_value(m));
+// The last, partial chunk at k0 of rows of len elements.
+template <bool SQ, int RB>
+__device__ __forceinline__ void tile_tail(uint16_t* lds, const ARows<RB>& arows, const BRows& brows, int k0,
+                                          int len, Acc (&acc)[RB], double (&sq)[RB]) {
+  AChunk ra[RB];
+  BChunk rb;
+  load_b(brows, k0, rb);
+  load_a_tail<RB>(arows, k0, len, ra);
+  __syncthreads();
+  store_b(lds, rb);
+  __syncthreads();
+  if constexpr (SQ) {
+#pragma unroll
+    for (int r = 0; r < RB; ++r) sq[r] += squares(ra[r]);
   }
+  mma_chunk<RB>(lds, ra, acc);
 }
+
+// Row (inside the tile) of row block r's accumulators of this lane, and the
+// first of their four columns in block b.
+template <int RB>
+__device__ __forceinline__ int out_row(int r) {
+  return 16 * (RB * (threadIdx.x >> 6) + r) + (threadIdx.x & 15);
+}
+__device__ __forceinline__ int out_col(int b) { return 16 * b + 4 * ((threadIdx.x >> 4) & 3); }
 
 }  // namespace split
 }  // namespace sd

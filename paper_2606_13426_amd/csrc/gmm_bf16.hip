@@ -38,7 +38,7 @@ static_assert(sizeof(float) * kMaxChains * LDO <= sizeof(OperandLds), "G must fi
 
 template <bool VEC>
 __global__ __launch_bounds__(kThreads, 2) void gmm_logits_bf16_kernel(
-    int R, int M, int d, const float* __restrict__ X, int64_t ldx,
+    int R, int M, int Mp, int d, int dp, const float* __restrict__ X, int64_t ldx,
     const uint16_t* __restrict__ mu, int ksplit, float* __restrict__ part,
     double* __restrict__ xsq, const int* gate) {
   if (gate && *gate == 0) return;
@@ -57,10 +57,10 @@ __global__ __launch_bounds__(kThreads, 2) void gmm_logits_bf16_kernel(
   double sq[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   const bool want_sq = ct == 0;
   if (want_sq)
-    tile<true, VEC>(sm, X, ldx, R, mu, d, M, r0, c0, kbeg, kend, acc, sq);
+    tile<true, VEC>(sm, X, ldx, R, mu, dp, M, r0, c0, kbeg, kend, acc, sq);
   else
-    tile<false, VEC>(sm, X, ldx, R, mu, d, M, r0, c0, kbeg, kend, acc, sq);
-  float* ps = part + (int64_t)s * R * M;
+    tile<false, VEC>(sm, X, ldx, R, mu, dp, M, r0, c0, kbeg, kend, acc, sq);
+  float* ps = part + (int64_t)s * R * Mp;
 #pragma unroll
   for (int qb = 0; qb < 2; ++qb) {
     const int col = c0 + out_col(qb);
@@ -70,7 +70,7 @@ __global__ __launch_bounds__(kThreads, 2) void gmm_logits_bf16_kernel(
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int row = r0 + out_row(qa, v);
-        if (row < R) ps[(int64_t)row * M + col] = acc[qa][qb][v];
+        if (row < R) ps[(int64_t)row * Mp + col] = acc[qa][qb][v];
       }
   }
   if (want_sq) {
@@ -95,7 +95,7 @@ __global__ __launch_bounds__(kThreads, 2) void gmm_logits_bf16_kernel(
 // go to column tile h % nct, so the column tiles (that run side by side)
 // share the work instead of column tile 0 doing all of it.
 __global__ __launch_bounds__(bf16w::kThreads, 2) void gmm_logits_bf16_wide_kernel(
-    int R, int M, int d, const float* __restrict__ X, int64_t ldx,
+    int R, int M, int Mp, int d, int dp, const float* __restrict__ X, int64_t ldx,
     const uint16_t* __restrict__ mu, int ksplit, float* __restrict__ part,
     double* __restrict__ xsq, const int* gate) {
   using namespace bf16w;
@@ -112,12 +112,12 @@ __global__ __launch_bounds__(bf16w::kThreads, 2) void gmm_logits_bf16_wide_kerne
 #pragma unroll
   for (int h = 0; h < 8; ++h) sq[h] = 0.0;
   const __amdgpu_buffer_rsrc_t va = bf16w::tile_view(X, ldx, R, r0);
-  const __amdgpu_buffer_rsrc_t vb = bf16w::tile_view(mu, (int64_t)d, M, c0);
+  const __amdgpu_buffer_rsrc_t vb = bf16w::tile_view(mu, (int64_t)dp, M, c0);
   uint32_t sqmask = 0;
 #pragma unroll
   for (int h = 0; h < 8; ++h) sqmask |= (h % nct == ct ? 1u : 0u) << h;
-  bf16w::tile<true, float>(sm, va, ldx, vb, d, kbeg, kend, acc, sq, sqmask);
-  float* ps = part + (int64_t)s * R * M;
+  bf16w::tile<true, float>(sm, va, ldx, vb, dp, kbeg, kend, acc, sq, sqmask);
+  float* ps = part + (int64_t)s * R * Mp;
 #pragma unroll
   for (int qb = 0; qb < 2; ++qb) {
     const int col = c0 + bf16w::out_col(qb);
@@ -127,7 +127,7 @@ __global__ __launch_bounds__(bf16w::kThreads, 2) void gmm_logits_bf16_wide_kerne
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int row = r0 + bf16w::out_row(qa, v);
-        if (row < R) ps[(int64_t)row * M + col] = acc[qa][qb][v];
+        if (row < R) ps[(int64_t)row * Mp + col] = acc[qa][qb][v];
       }
   }
   // the 16 threads that loaded a row are 16 consecutive lanes
@@ -208,7 +208,7 @@ __device__ __forceinline__ float comp(const float4& v, int c) {
 // Public target call: m^q = c1 x + c2 (O - rho x) (and the score if asked).
 template <bool VEC>
 __global__ __launch_bounds__(kThreads, 2) void gmm_mean_bf16_kernel(
-    int R, int M, int d, const uint16_t* __restrict__ P,
+    int R, int M, int Mp, int Mk, int d, const uint16_t* __restrict__ P,
     const uint16_t* __restrict__ muT, const float* __restrict__ X, int64_t ldx, bool vecx,
     const float* __restrict__ rowc, float* __restrict__ mq, int64_t ldq, bool vecq,
     float* __restrict__ score, int64_t lds, bool vecs, const int* gate) {
@@ -223,7 +223,7 @@ __global__ __launch_bounds__(kThreads, 2) void gmm_mean_bf16_kernel(
   f32x16 acc[2][2];
   zero(acc);
   double unused[8];
-  tile<false, VEC>(sm, P, M, R, muT, M, d, r0, c0, 0, M, acc, unused);
+  tile<false, VEC>(sm, P, Mp, R, muT, Mk, d, r0, c0, 0, M, acc, unused);
   float* stg = reinterpret_cast<float*>(&sm[0]);
   const int cg = threadIdx.x & 15, rg = threadIdx.x >> 4;
 #pragma unroll
@@ -367,7 +367,7 @@ __device__ __forceinline__ void mean_lr_epilogue_vec(
 // formed it (draft_mean; c2_{k+j} / c2_c from the tables and cstep[b]).
 template <bool VEC>
 __global__ __launch_bounds__(kThreads, 2) void gmm_mean_lr_bf16_kernel(
-    int R, int M, int d, int K1, const uint16_t* __restrict__ P,
+    int R, int M, int Mp, int Mk, int d, int K1, const uint16_t* __restrict__ P,
     const uint16_t* __restrict__ muT, const float* __restrict__ X, const float* __restrict__ rowc,
     const float* __restrict__ SV, const int32_t* __restrict__ cstep,
     const float4* __restrict__ coef, float* __restrict__ mq, double* __restrict__ lrp, bool vecd,
@@ -389,7 +389,7 @@ __global__ __launch_bounds__(kThreads, 2) void gmm_mean_lr_bf16_kernel(
   // it comes after, so that no early wait stalls the workgroup)
   const int B = R / K1;
   const int csi = cstep[min(r0 / K1 + (int)threadIdx.x, B - 1)];
-  tile<false, VEC>(sm, P, M, R, muT, M, d, r0, c0, 0, M, acc, unused);
+  tile<false, VEC>(sm, P, Mp, R, muT, Mk, d, r0, c0, 0, M, acc, unused);
   float* stg = reinterpret_cast<float*>(&sm[0]);
   float* gz = reinterpret_cast<float*>(&sm[1]);
   const int cg = threadIdx.x & 15, rg = threadIdx.x >> 4;
@@ -723,8 +723,9 @@ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // compute unit when d is a whole number of chunks, else over 512 slots of two
 // 128 x 128 workgroups per compute unit.
 // Buffers for R rows; the split over d is chosen for plan_rows rows (0: R).
-Plan make_plan(const Target& t, int R, int plan_rows = 0) {
+Plan make_plan(const Target& t, int R, int plan_rows = 0, bool padded = true) {
   Plan p{};
+  const size_t M = padded ? t.Mp : t.M;
   p.wide = t.d % KC == 0;
   const int tm = p.wide ? bf16w::WT : TM, tn = p.wide ? bf16w::WT : TN;
   const int slots = p.wide ? 256 : 512;
@@ -746,11 +747,11 @@ Plan make_plan(const Target& t, int R, int plan_rows = 0) {
   p.S = (t.d + p.ksplit - 1) / p.ksplit;
   size_t off = 0;
   p.off_part = off;
-  off = align256(off + sizeof(float) * (size_t)p.S * R * t.M);
+  off = align256(off + sizeof(float) * (size_t)p.S * R * M);
   p.off_xsq = off;
   off = align256(off + sizeof(double) * (size_t)p.S * R);
   p.off_p = off;
-  off = align256(off + sizeof(uint16_t) * (size_t)R * t.M);
+  off = align256(off + sizeof(uint16_t) * (size_t)R * M);
   p.off_rowc = off;
   off = align256(off + sizeof(float) * 3 * (size_t)R);
   p.total = off;
@@ -783,17 +784,19 @@ hipError_t logits_and_softmax(const Target& t, const Plan& p, const Bufs& w, int
   if (wide)
     e = launch_timed("gmm_logits_bf16", gmm_logits_bf16_wide_kernel,
                      dim3((t.M + bf16w::WT - 1) / bf16w::WT, (R + bf16w::WT - 1) / bf16w::WT, p.S),
-                     dim3(bf16w::kThreads), s, R, t.M, t.d, x, ldx, t.mu16, p.ksplit, w.part, w.xsq,
+                     dim3(bf16w::kThreads), s, R, t.M, t.Mp, t.d, t.dp, x, ldx, t.mu16, p.ksplit, w.part, w.xsq,
                      gate);
   else
     e = launch_timed("gmm_logits_bf16", vec ? gmm_logits_bf16_kernel<true> : gmm_logits_bf16_kernel<false>,
-                     g1, dim3(kThreads), s, R, t.M, t.d, x, ldx, t.mu16, p.ksplit, w.part, w.xsq,
+                     g1, dim3(kThreads), s, R, t.M, t.Mp, t.d, t.dp, x, ldx, t.mu16, p.ksplit, w.part, w.xsq,
                      gate);
   if (e != hipSuccess) return e;
   return gmm_softmax_launch(t, R, p.rows, p.S, w.part, w.xsq, step, w.P, true, w.rowc, s, gate);
 }
 
 }  // namespace
+
+size_t target_ws_bytes_unpadded_bf16(const Target& t, int rows) { return make_plan(t, rows, 0, false).total; }
 
 size_t target_ws_bytes_bf16(const Target& t, int rows, int plan_rows) {
   return make_plan(t, rows, plan_rows).total;
@@ -813,11 +816,11 @@ hipError_t target_mean_bf16_launch(const Target& t, int R, const float* x, int64
   dim3 g2((t.d + TN - 1) / TN, (R + TM - 1) / TM);
   return timed("gmm_mean_bf16", s, [&] {
     if (t.M % KC == 0)
-      gmm_mean_bf16_kernel<true><<<g2, kThreads, 0, s>>>(R, t.M, t.d, w.P, t.muT16, x, ldx, vecx,
+      gmm_mean_bf16_kernel<true><<<g2, kThreads, 0, s>>>(R, t.M, t.Mp, t.Mk, t.d, w.P, t.muT16, x, ldx, vecx,
                                                          w.rowc, mq, ldq, vecq, score, lds, vecs,
                                                          gate);
     else
-      gmm_mean_bf16_kernel<false><<<g2, kThreads, 0, s>>>(R, t.M, t.d, w.P, t.muT16, x, ldx, vecx,
+      gmm_mean_bf16_kernel<false><<<g2, kThreads, 0, s>>>(R, t.M, t.Mp, t.Mk, t.d, w.P, t.muT16, x, ldx, vecx,
                                                           w.rowc, mq, ldq, vecq, score, lds, vecs,
                                                           gate);
   });
@@ -852,7 +855,7 @@ hipError_t target_mean_lr_bf16_launch(const Target& t, int R, int K1, const floa
                    (int64_t)(TM + 2) * t.d * 4 < ((int64_t)1 << 31);
   return launch_timed("gmm_mean_lr_bf16",
                       vec ? gmm_mean_lr_bf16_kernel<true> : gmm_mean_lr_bf16_kernel<false>, g2,
-                      dim3(kThreads), s, R, t.M, t.d, K1, w.P, t.muT16, x, w.rowc, sv, cstep, t.coef,
+                      dim3(kThreads), s, R, t.M, t.Mp, t.Mk, t.d, K1, w.P, t.muT16, x, w.rowc, sv, cstep, t.coef,
                       mq, lrp, vecd, rnd, seed, gate, chain0);
 }
 
