@@ -198,19 +198,32 @@ __global__ __launch_bounds__(NW > 4 ? 64 * NW : kThreads) void gmm_softmax_kerne
     lw[c] = logw[mc];
     mq2[c] = musq[mc];
   }
-  double xs = 0.0;
-  for (int s = lane; s < S; s += 64) xs += xsq[(int64_t)s * R + rr];
+  // (at most 32 splits: one lane each)
+  const double xl = xsq[(int64_t)min(lane, S - 1) * R + rr];
+  double xs = lane < S ? xl : 0.0;
   double dot[4] = {0.0, 0.0, 0.0, 0.0};
   if (m0 < Mp) {
     const float* pr = part + (int64_t)rr * Mp + m0;
-#pragma unroll 8
-    for (int s = q; s < S; s += DS) {
-      const float4 v = *reinterpret_cast<const float4*>(pr + (int64_t)s * R * Mp);
-      dot[0] += (double)v.x;
-      dot[1] += (double)v.y;
-      dot[2] += (double)v.z;
-      dot[3] += (double)v.w;
-    }
+    // a batch of splits' loads together (a missing one repeats the last)
+    auto sum = [&](auto batch) {
+      constexpr int U = decltype(batch)::value;
+      for (int s0 = 0; s0 < S; s0 += U * DS) {
+        split::f32x4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          v[u] = *reinterpret_cast<const split::f32x4*>(pr + (int64_t)min(s0 + q + u * DS, S - 1) * R * Mp);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const bool in = s0 + q + u * DS < S;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) dot[c] += in ? (double)v[u][c] : 0.0;
+        }
+      }
+    };
+    if (S <= 2 * DS)
+      sum(std::integral_constant<int, 2>{});
+    else
+      sum(std::integral_constant<int, 8>{});
   }
   const double a = sig[n];
   double2 t[NC];
