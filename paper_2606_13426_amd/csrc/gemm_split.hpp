@@ -184,8 +184,16 @@ __device__ __forceinline__ bf16x8 frag(const uint16_t* p) {
   return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(p));
 }
 
-// The chunk's 2 steps x 4 column blocks x RB row blocks x 6 terms.
-template <int RB>
+// The chunk's 2 steps x 4 column blocks x RB row blocks x 6 terms.  APART: the
+// five small terms of a step are summed from zero and added to the leading
+// product's sum once, two roundings of the running sum per step instead of six:
+// in a contraction of few terms (d or M no multiple of 64) six show beside the
+// one or two of a float32 instruction (error of a score against 64 bits, 2 x
+// 191 components: 8.1e-7 there, 4.7e-7 apart; 4 x 20: 5.6e-7, 4.5e-7; 4107 x
+// 100: 1.11e-7 both).  Whole multiples of 64 keep the chain: the extra
+// registers take a wavefront per SIMD (a sampler call of 1024 x 3072 846 us
+// against 816).
+template <int RB, bool APART>
 __device__ __forceinline__ void mma_chunk(const uint16_t* lds, const AChunk (&a)[RB], Acc (&acc)[RB]) {
   const int lane = threadIdx.x & 63;
   const uint16_t* pb = lds + (lane & 15) * LDH + 8 * (lane >> 4);
@@ -201,12 +209,16 @@ __device__ __forceinline__ void mma_chunk(const uint16_t* lds, const AChunk (&a)
 #pragma unroll
       for (int r = 0; r < RB; ++r) {
         f32x4 c = acc[r].c[b];
+        if constexpr (APART) c = f32x4{0.f, 0.f, 0.f, 0.f};
         c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh, al[r], c, 0, 0, 0);
         c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bl, ah[r], c, 0, 0, 0);
         c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bm, am[r], c, 0, 0, 0);
         c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh, am[r], c, 0, 0, 0);
         c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bm, ah[r], c, 0, 0, 0);
-        acc[r].c[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh, ah[r], c, 0, 0, 0);
+        if constexpr (APART)
+          acc[r].c[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh, ah[r], acc[r].c[b], 0, 0, 0) + c;
+        else
+          acc[r].c[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh, ah[r], c, 0, 0, 0);
       }
     }
   }
@@ -220,7 +232,7 @@ __device__ __forceinline__ void mma_chunk(const uint16_t* lds, const AChunk (&a)
 // would cost the occupancy that hides those loads behind the other
 // workgroups' matrix work.  The caller's first use of lds afterwards must
 // follow a barrier.
-template <bool SQ, int RB>
+template <bool SQ, int RB, bool APART>
 __device__ __forceinline__ void tile_run(uint16_t* lds, const ARows<RB>& arows, const BRows& brows,
                                          int kbeg, int kend, AChunk (&ra)[RB], BChunk& rb, Acc (&acc)[RB],
                                          double (&sq)[RB]) {
@@ -230,7 +242,7 @@ __device__ __forceinline__ void tile_run(uint16_t* lds, const ARows<RB>& arows, 
 #pragma unroll
     for (int r = 0; r < RB; ++r) sq[r] += squares(ra[r]);
   }
-  mma_chunk<RB>(lds, ra, acc);
+  mma_chunk<RB, APART>(lds, ra, acc);
   for (int k0 = kbeg + KC; k0 < kend; k0 += KC) {
     load_b(brows, k0, rb);
     load_a<RB>(arows, k0, ra);
@@ -241,12 +253,12 @@ __device__ __forceinline__ void tile_run(uint16_t* lds, const ARows<RB>& arows, 
 #pragma unroll
       for (int r = 0; r < RB; ++r) sq[r] += squares(ra[r]);
     }
-    mma_chunk<RB>(lds, ra, acc);
+    mma_chunk<RB, APART>(lds, ra, acc);
   }
 }
 
 // The last, partial chunk at k0 of rows of len elements.
-template <bool SQ, int RB>
+template <bool SQ, int RB, bool APART>
 __device__ __forceinline__ void tile_tail(uint16_t* lds, const ARows<RB>& arows, const BRows& brows, int k0,
                                           int len, Acc (&acc)[RB], double (&sq)[RB]) {
   AChunk ra[RB];
@@ -260,7 +272,7 @@ __device__ __forceinline__ void tile_tail(uint16_t* lds, const ARows<RB>& arows,
 #pragma unroll
     for (int r = 0; r < RB; ++r) sq[r] += squares(ra[r]);
   }
-  mma_chunk<RB>(lds, ra, acc);
+  mma_chunk<RB, APART>(lds, ra, acc);
 }
 
 // Row (inside the tile) of row block r's accumulators of this lane, and the
