@@ -1065,11 +1065,15 @@ sd_status sd_run_plain_em(sd_target target, int32_t B, uint64_t seed, float* y_o
   int32_t* step = reinterpret_cast<int32_t*>(base + a256(sizeof(float) * (size_t)B * t.d));
   void* tws = base + a256(sizeof(float) * (size_t)B * t.d) + a256(sizeof(int32_t) * (size_t)B);
   const int d = t.d;
-  SD_HIP(init_chains_launch(B, d, seed, y_out, s));
+  // a step's target call writes the next states itself (EmStep), from one of the
+  // two buffers to the other; the last step ends in y_out
+  const int N = t.sc.N;
+  float* const buf[2] = {N % 2 == 0 ? y_out : mq, N % 2 == 0 ? mq : y_out};
+  SD_HIP(init_chains_launch(B, d, seed, buf[0], s));
   SD_HIP(fill_i32_launch(step, B, 0, s));
-  for (int n = 0; n < t.sc.N; ++n) {
-    SD_HIP(target_mean_launch(t, B, y_out, d, step, mq, d, nullptr, 0, tws, s, nullptr));
-    SD_HIP(em_noise_launch(B, d, n, (float)sched_sigma(t.sc, n), seed, mq, y_out, step, s));
+  for (int n = 0; n < N; ++n) {
+    const EmStep em{seed, n, (float)sched_sigma(t.sc, n), step};
+    SD_HIP(target_mean_launch(t, B, buf[n & 1], d, step, buf[(n + 1) & 1], d, nullptr, 0, tws, s, nullptr, 0, &em));
   }
   return SD_OK;
 }

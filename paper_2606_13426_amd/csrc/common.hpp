@@ -147,12 +147,21 @@ size_t target_ws_bytes_bf16(const Target& t, int rows, int plan_rows = 0);
 // The same with rows of M components (the measure of sd_target_mean_noalloc's limit).
 size_t target_ws_bytes_unpadded(const Target& t, int rows);
 size_t target_ws_bytes_unpadded_bf16(const Target& t, int rows);
+// The plain Euler-Maruyama step that a target call takes in its last kernel:
+// the means go out with their noise added, y = m^q + sigma xi (TARGET stream of
+// chain = row, round n, slot 1), and step[row] becomes n + 1.
+struct EmStep {
+  uint64_t seed;
+  int n;
+  float sigma;
+  int32_t* step;
+};
 // Rows' EM means (and scores if score != nullptr).  gate: nullable device flag;
 // when it reads 0 every kernel exits at once (finished sampler rounds).
 hipError_t target_mean_launch(const Target& t, int rows, const float* x, int64_t ldx,
                               const int32_t* step, float* mq, int64_t ldq, float* score,
                               int64_t lds, void* ws, hipStream_t s, const int* gate,
-                              int plan_rows = 0);
+                              int plan_rows = 0, const EmStep* em = nullptr);
 
 // The sampler's target call on its [B][K+1][d] block (x rows contiguous,
 // row stride d) that also leaves the verification's partial sums in
@@ -170,7 +179,7 @@ int lr_tiles(const Target& t, int K1);
 hipError_t target_mean_bf16_launch(const Target& t, int rows, const float* x, int64_t ldx,
                                    const int32_t* step, float* mq, int64_t ldq, float* score,
                                    int64_t lds, void* ws, hipStream_t s, const int* gate,
-                                   int plan_rows = 0);
+                                   int plan_rows = 0, const EmStep* em = nullptr);
 hipError_t target_mean_lr_bf16_launch(const Target& t, int rows, int K1, const float* x,
                                       const int32_t* step, float* mq, const float* sv,
                                       const int32_t* cstep, double* lrp, const uint32_t* rnd,
@@ -258,10 +267,6 @@ hipError_t reflection_launch(int B, int K, int d, const float* yd, sd_stride ys,
                              sd_stride mps, const float* mq, sd_stride mqs, const double* sigma,
                              const int32_t* kb, const int32_t* left, const int32_t* tau,
                              const uint32_t* rnd, uint64_t seed, float* y, hipStream_t s);
-// One plain Euler-Maruyama step on B rows: y = mq + sigma_n xi (TARGET
-// stream, round n, slot 1), and step[b] = n + 1 for the next target call.
-hipError_t em_noise_launch(int B, int d, int n, float sigma_n, uint64_t seed, const float* mq,
-                           float* y, int32_t* step, hipStream_t s);
 // Sampler-only kernels.
 hipError_t fill_i32_launch(int32_t* p, int64_t n, int32_t v, hipStream_t s);
 // *f0 = 1 if a chain of [0, split) has k < N, else 0; *f1 the same for

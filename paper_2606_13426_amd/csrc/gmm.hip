@@ -300,13 +300,15 @@ __global__ __launch_bounds__(NW > 4 ? 64 * NW : kThreads) void gmm_softmax_kerne
 // O = P mu with the EM epilogue: P split in registers, mu^T from its pre-split
 // planes.  A lane's accumulators are four consecutive columns of one row, so x
 // comes in and the means go out in 16-byte pieces, 64 bytes of 16 rows per
-// instruction.
-template <int EDGE, bool APART>
+// instruction.  EM: the plain Euler-Maruyama step (EmStep), whose noise as a
+// kernel of its own was a fourth of a small step's launches and one more pass
+// over the rows.
+template <int EDGE, bool APART, bool EM>
 __global__ __launch_bounds__(kThreads) void gmm_mean_split_kernel(
     int R, int Mp, int Mk, int d, const float* __restrict__ P, const uint16_t* __restrict__ muTs,
     const float* __restrict__ X, int64_t ldx, const float* __restrict__ rowc,
     float* __restrict__ mq, int64_t ldq, float* __restrict__ score, int64_t lds_,
-    const int* gate) {
+    const int* gate, EmStep em) {
   __shared__ uint16_t lds[split::kLdsBytes / 2];
   const int r0 = blockIdx.x * TILE, c0 = blockIdx.y * TILE;
   const split::ARows<1> arows = split::a_rows<1>(P, Mp, R, r0);
@@ -329,15 +331,17 @@ __global__ __launch_bounds__(kThreads) void gmm_mean_split_kernel(
   double unused[1] = {0.0};
   split::tile_run<false, 1, APART>(lds, arows, brows, 0, Mp, sa, sb, acc, unused);
   if (row >= R) return;
+  if (EM && blockIdx.y == 0 && split::out_col(0) == 0) em.step[row] = em.n + 1;
 #pragma unroll
   for (int b = 0; b < 4; ++b) {
     const int col = c0 + split::out_col(b), cnt = EDGE == 0 ? 4 : d - col;
     const float4 x = xv[b];
     const split::f32x4 o = acc[0].c[b];
     const float4 sc = make_float4(o[0] - rho * x.x, o[1] - rho * x.y, o[2] - rho * x.z, o[3] - rho * x.w);
-    store_quad<false>(mq + (int64_t)row * ldq + col, cnt,
-               make_float4(c1 * x.x + c2 * sc.x, c1 * x.y + c2 * sc.y, c1 * x.z + c2 * sc.z, c1 * x.w + c2 * sc.w));
-    if (score) store_quad<false>(score + (int64_t)row * lds_ + col, cnt, sc);
+    float4 q = make_float4(c1 * x.x + c2 * sc.x, c1 * x.y + c2 * sc.y, c1 * x.z + c2 * sc.z, c1 * x.w + c2 * sc.w);
+    if constexpr (EM) q = em_state(q, em.sigma, (uint32_t)(col >> 2), (uint32_t)row, (uint32_t)em.n, em.seed);
+    store_quad<false>(mq + (int64_t)row * ldq + col, cnt, q);
+    if (!EM && score) store_quad<false>(score + (int64_t)row * lds_ + col, cnt, sc);
   }
 }
 
@@ -633,10 +637,10 @@ hipError_t gmm_softmax_launch(const Target& t, int R, int plan_rows, int S, cons
 hipError_t target_mean_launch(const Target& t, int R, const float* x, int64_t ldx,
                               const int32_t* step, float* mq, int64_t ldq, float* score,
                               int64_t lds, void* ws, hipStream_t s, const int* gate,
-                              int plan_rows) {
+                              int plan_rows, const EmStep* em) {
   if (t.prec == SD_BF16)
     return target_mean_bf16_launch(t, R, x, ldx, step, mq, ldq, score, lds, ws, s, gate,
-                                   plan_rows);
+                                   plan_rows, em);
   const Plan p = make_plan(t, R, plan_rows);
   char* base = static_cast<char*>(ws);
   float* part = reinterpret_cast<float*>(base + p.off_part);
@@ -649,12 +653,17 @@ hipError_t target_mean_launch(const Target& t, int R, const float* x, int64_t ld
   if (e != hipSuccess) return e;
   dim3 g2((R + TILE - 1) / TILE, (t.d + TILE - 1) / TILE);
   const int edge = edge_of(t.d);
-  return launch_timed("gmm_mean",
-                      edge == 2   ? gmm_mean_split_kernel<2, true>
-                      : edge == 1 ? gmm_mean_split_kernel<1, true>
-                      : t.M % TILE ? gmm_mean_split_kernel<0, true>
-                                  : gmm_mean_split_kernel<0, false>, g2, dim3(kThreads), s, R, t.Mp, t.Mk, t.d, P,
-                      t.muT_split, x, ldx, rowc, mq, ldq, score, lds, gate);
+  auto go = [&](auto noise) {
+    constexpr bool EM = decltype(noise)::value;
+    return launch_timed(EM ? "em_step" : "gmm_mean",
+                        edge == 2    ? gmm_mean_split_kernel<2, true, EM>
+                        : edge == 1  ? gmm_mean_split_kernel<1, true, EM>
+                        : t.M % TILE ? gmm_mean_split_kernel<0, true, EM>
+                                     : gmm_mean_split_kernel<0, false, EM>,
+                        g2, dim3(kThreads), s, R, t.Mp, t.Mk, t.d, P, t.muT_split, x, ldx, rowc, mq, ldq, score,
+                        lds, gate, em ? *em : EmStep{});
+  };
+  return em ? go(std::true_type{}) : go(std::false_type{});
 }
 
 hipError_t target_mean_lr_launch(const Target& t, int R, int K1, const float* x,

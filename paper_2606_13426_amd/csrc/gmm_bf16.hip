@@ -16,6 +16,8 @@
 // The mean GEMMs' 128 x 128 accumulator tile is handed to the epilogue
 // through LDS in two passes of 64 columns, each over the operand buffers'
 // storage.
+#include <type_traits>
+
 #include "bufio.hpp"
 #include "common.hpp"
 #include "gemm_bf16.hpp"
@@ -205,13 +207,14 @@ __device__ __forceinline__ float comp(const float4& v, int c) {
   return c == 0 ? v.x : c == 1 ? v.y : c == 2 ? v.z : v.w;
 }
 
-// Public target call: m^q = c1 x + c2 (O - rho x) (and the score if asked).
-template <bool VEC>
+// Public target call: m^q = c1 x + c2 (O - rho x) (and the score if asked); EM:
+// the plain Euler-Maruyama step (EmStep).
+template <bool VEC, bool EM>
 __global__ __launch_bounds__(kThreads, 2) void gmm_mean_bf16_kernel(
     int R, int M, int Mp, int Mk, int d, const uint16_t* __restrict__ P,
     const uint16_t* __restrict__ muT, const float* __restrict__ X, int64_t ldx, bool vecx,
     const float* __restrict__ rowc, float* __restrict__ mq, int64_t ldq, bool vecq,
-    float* __restrict__ score, int64_t lds, bool vecs, const int* gate) {
+    float* __restrict__ score, int64_t lds, bool vecs, const int* gate, EmStep em) {
   if (gate && *gate == 0) return;
   __shared__ OperandLds sm[2];
   __shared__ float rc[3 * TM];
@@ -249,10 +252,14 @@ __global__ __launch_bounds__(kThreads, 2) void gmm_mean_bf16_kernel(
       const float4 x = xv[i];
       const float4 sv = make_float4(ov.x - rho * x.x, ov.y - rho * x.y, ov.z - rho * x.z,
                                     ov.w - rho * x.w);
-      st4(mq + (int64_t)row * ldq + col, cnt, vecq,
-          make_float4(c1 * x.x + c2 * sv.x, c1 * x.y + c2 * sv.y, c1 * x.z + c2 * sv.z,
-                      c1 * x.w + c2 * sv.w));
-      if (score) st4(score + (int64_t)row * lds + col, cnt, vecs, sv);
+      float4 qv = make_float4(c1 * x.x + c2 * sv.x, c1 * x.y + c2 * sv.y, c1 * x.z + c2 * sv.z,
+                              c1 * x.w + c2 * sv.w);
+      if constexpr (EM) {
+        qv = em_state(qv, em.sigma, (uint32_t)(col >> 2), (uint32_t)row, (uint32_t)em.n, em.seed);
+        if (col == 0) em.step[row] = em.n + 1;
+      }
+      st4(mq + (int64_t)row * ldq + col, cnt, vecq, qv);
+      if (!EM && score) st4(score + (int64_t)row * lds + col, cnt, vecs, sv);
     }
   }
 }
@@ -805,7 +812,7 @@ size_t target_ws_bytes_bf16(const Target& t, int rows, int plan_rows) {
 hipError_t target_mean_bf16_launch(const Target& t, int R, const float* x, int64_t ldx,
                                    const int32_t* step, float* mq, int64_t ldq, float* score,
                                    int64_t lds, void* ws, hipStream_t s, const int* gate,
-                                   int plan_rows) {
+                                   int plan_rows, const EmStep* em) {
   const Plan p = make_plan(t, R, plan_rows);
   const Bufs w = carve(p, ws);
   const bool vecx = (ldx % 4 == 0) && aligned16(x);
@@ -814,16 +821,14 @@ hipError_t target_mean_bf16_launch(const Target& t, int R, const float* x, int64
   const bool vecq = (ldq % 4 == 0) && aligned16(mq);
   const bool vecs = score && (lds % 4 == 0) && aligned16(score);
   dim3 g2((t.d + TN - 1) / TN, (R + TM - 1) / TM);
-  return timed("gmm_mean_bf16", s, [&] {
-    if (t.M % KC == 0)
-      gmm_mean_bf16_kernel<true><<<g2, kThreads, 0, s>>>(R, t.M, t.Mp, t.Mk, t.d, w.P, t.muT16, x, ldx, vecx,
-                                                         w.rowc, mq, ldq, vecq, score, lds, vecs,
-                                                         gate);
-    else
-      gmm_mean_bf16_kernel<false><<<g2, kThreads, 0, s>>>(R, t.M, t.Mp, t.Mk, t.d, w.P, t.muT16, x, ldx, vecx,
-                                                          w.rowc, mq, ldq, vecq, score, lds, vecs,
-                                                          gate);
-  });
+  auto go = [&](auto noise) {
+    constexpr bool EM = decltype(noise)::value;
+    return launch_timed(EM ? "em_step_bf16" : "gmm_mean_bf16",
+                        t.M % KC == 0 ? gmm_mean_bf16_kernel<true, EM> : gmm_mean_bf16_kernel<false, EM>, g2,
+                        dim3(kThreads), s, R, t.M, t.Mp, t.Mk, t.d, w.P, t.muT16, x, ldx, vecx, w.rowc, mq, ldq,
+                        vecq, score, lds, vecs, gate, em ? *em : EmStep{});
+  };
+  return em ? go(std::true_type{}) : go(std::false_type{});
 }
 
 hipError_t target_mean_lr_bf16_launch(const Target& t, int R, int K1, const float* x,

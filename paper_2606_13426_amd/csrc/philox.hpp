@@ -78,6 +78,14 @@ __device__ __forceinline__ float4 normals4(uint4 w) {
                      rc * __builtin_amdgcn_cosf(ud), rc * __builtin_amdgcn_sinf(ud));
 }
 
+// q + sigma xi of four coordinates (group g) of a plain Euler-Maruyama step:
+// the TARGET stream's slot 1 of the chain's round n.
+__device__ __forceinline__ float4 em_state(float4 q, float sigma, uint32_t g, uint32_t chain, uint32_t n,
+                                           uint64_t seed) {
+  const float4 z = normals4(philox(g, chain, n, (TAG_TARGET << 24) | 1u, seed));
+  return make_float4(q.x + sigma * z.x, q.y + sigma * z.y, q.z + sigma * z.z, q.w + sigma * z.w);
+}
+
 __device__ __forceinline__ float get4(const float4& v, int i) {
   return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w;
 }
