@@ -30,6 +30,7 @@ namespace {
 
 constexpr int kThreads = 256;
 
+template <bool SPREAD>
 __global__ __launch_bounds__(kThreads) void advance_kernel(
     Sched sc, const float4* __restrict__ coef, int B, int K, int d, uint64_t seed,
     const int32_t* __restrict__ kcur, const uint32_t* __restrict__ rcur,
@@ -44,6 +45,7 @@ __global__ __launch_bounds__(kThreads) void advance_kernel(
     bool frozen, bool stream, const int* gate, int chain0, int trace_ld) {
   // every scalar input is requested before the first is used (the gate too)
   __shared__ float4 cfs[SD_MAX_BLOCK];
+  __shared__ float4 zs[SPREAD ? kSpreadRows : 1][64];
   const int N = sc.N, K1 = K + 1;
   const int b = blockIdx.y;
   const uint32_t chain = (uint32_t)(chain0 + b);  // the generator's chain index
@@ -86,12 +88,15 @@ __global__ __launch_bounds__(kThreads) void advance_kernel(
   const bool drafts = !frozen && knew < N;
   if (drafts) {
     draft_coefs(sc, coef, knew, min(K, N - knew), cc.w, cfs);
-    __syncthreads();
+    if (!SPREAD) __syncthreads();
   }
-  const int g = blockIdx.x * kThreads + threadIdx.x;
+  // SPREAD: the four wavefronts share 64 groups (draft_rows_spread); what is
+  // written once, the first one writes
+  const bool first = !SPREAD || threadIdx.x < 64;
+  const int g = SPREAD ? blockIdx.x * 64 + (threadIdx.x & 63) : blockIdx.x * kThreads + threadIdx.x;
   const int e0 = 4 * g;
-  if (e0 >= d) return;
-  const int cnt = min(4, d - e0);
+  if (SPREAD ? !first && !drafts : e0 >= d) return;
+  const int cnt = max(0, min(4, d - e0));
   const bool vec = vec_ok && cnt == 4;
   float* xb = X + (int64_t)b * K1 * d + e0;
   float* sb = SV + (int64_t)b * d + e0;
@@ -138,7 +143,7 @@ __global__ __launch_bounds__(kThreads) void advance_kernel(
   // advance: the Frozen Drafter's draft (from y) and the run's output once the
   // chain has reached step N; otherwise x row 0 carries it
   if (frozen || knew >= N) store4(y + (int64_t)b * d + e0, cnt, vec, yv);
-  if (knew >= N) return;
+  if (knew >= N) return;  // (the first wavefront alone is here, and below)
   if (frozen) {
     store4(xb, cnt, vec, yv, stream);
     return;
@@ -148,9 +153,21 @@ __global__ __launch_bounds__(kThreads) void advance_kernel(
   load4(qb + (int64_t)cr * d, cnt, vec, qcv);
 #pragma unroll
   for (int c = 0; c < 4; ++c) sv[c] = qcv[c] - cc.x * xcv[c];  // c2_c S_c
-  store4(sb, cnt, vec, sv);
-  store4(xb, cnt, vec, yv, stream);
-  draft_rows(cfs, K, min(K, N - knew), chain, r + 1u, seed, g, yv, sv, xb, d, nullptr, d, cnt, vec, stream);
+  if constexpr (SPREAD) {
+    float y0[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) y0[c] = yv[c];
+    draft_rows_spread(cfs, zs, K, min(K, N - knew), chain, r + 1u, seed, g, yv, sv, xb, d, nullptr, d, cnt, vec,
+                      stream);
+    if (first) {
+      store4(sb, cnt, vec, sv);
+      store4(xb, cnt, vec, y0, stream);
+    }
+  } else {
+    store4(sb, cnt, vec, sv);
+    store4(xb, cnt, vec, yv, stream);
+    draft_rows(cfs, K, min(K, N - knew), chain, r + 1u, seed, g, yv, sv, xb, d, nullptr, d, cnt, vec, stream);
+  }
 }
 
 }  // namespace
@@ -166,10 +183,12 @@ hipError_t advance_launch(const Sched& sc, const float4* coef, int B, int K, int
                           hipStream_t s, const int* gate, int chain0, int trace_ld,
                           int64_t stream_bytes) {
   const int ng = (d + 3) / 4;
-  dim3 grid((ng + kThreads - 1) / kThreads, B);
+  const bool spread = spread_rows(B, K, d);
+  const int per = spread ? 64 : kThreads;  // groups of a workgroup
+  dim3 grid((ng + per - 1) / per, B);
   const bool vec = (d % 4 == 0) && aligned16(x) && aligned16(sv) && aligned16(mq) && aligned16(y);
   const bool stream = stream_rows(stream_bytes > 0 ? stream_bytes : (int64_t)B * (K + 1) * d * 4);
-  return launch_timed("advance", advance_kernel, grid, dim3(kThreads), s, sc, coef, B, K, d, seed,
+  return launch_timed("advance", spread ? advance_kernel<true> : advance_kernel<false>, grid, dim3(kThreads), s, sc, coef, B, K, d, seed,
                       kcur, rcur, crow_cur, cstep_cur, knext, rnext, crow_next, cstep_next, tau, rmode,
                       rcoef, rsig, x, sv, mq, y, step, sigma, hist, steps, act_next, trace, r,
                       trace_rounds, vec, frozen, stream, gate, chain0, trace_ld > 0 ? trace_ld : B);

@@ -73,7 +73,7 @@ __global__ __launch_bounds__(kThreads) void sampler_init_kernel(
 //   c2_n S_c = (c2_n / c2_c) (m^q_c - c1_c x_c),
 // read from the same x / mq buffers before this chain's rows are overwritten
 // (each thread reads and then writes only its own coordinates).
-template <bool CACHE_FROM_MEANS>
+template <bool CACHE_FROM_MEANS, bool SPREAD>
 __global__ __launch_bounds__(kThreads) void draft_kernel(
     Sched sc, const float4* __restrict__ coef, int K, int d, const float* __restrict__ y,
     const float* __restrict__ cs,
@@ -84,6 +84,7 @@ __global__ __launch_bounds__(kThreads) void draft_kernel(
     bool vec_ok, bool stream, const int* gate, int chain0) {
   if (gate && *gate == 0) return;
   __shared__ float4 cfs[SD_MAX_BLOCK];
+  __shared__ float4 zs[SPREAD ? kSpreadRows : 1][64];
   const int b = blockIdx.y;
   const int k = kk[b];
   if (k >= sc.N) return;
@@ -91,11 +92,14 @@ __global__ __launch_bounds__(kThreads) void draft_kernel(
   const uint32_t r = rnd[b];
   const float4 cc = CACHE_FROM_MEANS ? step_coef(sc, coef, cstep[b]) : make_float4(0.f, 0.f, 0.f, 1.0f);
   draft_coefs(sc, coef, k, kb, cc.w, cfs);
-  __syncthreads();
-  const int g = blockIdx.x * kThreads + threadIdx.x;
+  if (!SPREAD) __syncthreads();
+  // SPREAD: the four wavefronts share 64 groups (draft_rows_spread); what is
+  // written once, the first one writes
+  const bool first = !SPREAD || threadIdx.x < 64;
+  const int g = SPREAD ? blockIdx.x * 64 + (threadIdx.x & 63) : blockIdx.x * kThreads + threadIdx.x;
   const int e0 = 4 * g;
-  if (e0 >= d) return;
-  const int cnt = min(4, d - e0);
+  if (!SPREAD && e0 >= d) return;
+  const int cnt = max(0, min(4, d - e0));
   const bool vec = vec_ok && cnt == 4;
   float yv[4], sv[4];
   float* xb = x + (int64_t)b * xc + e0;
@@ -108,12 +112,20 @@ __global__ __launch_bounds__(kThreads) void draft_kernel(
     load4(mqprev + (int64_t)b * qc + (int64_t)cr * qr + e0, cnt, vec, qcv);
 #pragma unroll
     for (int c = 0; c < 4; ++c) sv[c] = qcv[c] - cc.x * xcv[c];  // c2_c S_c
-    if (svout) store4(svout + (int64_t)b * d + e0, cnt, vec, sv);
+    if (svout && first) store4(svout + (int64_t)b * d + e0, cnt, vec, sv);
   } else {
     load4(cs + (int64_t)b * d + e0, cnt, vec, sv);
   }
-  store4(xb, cnt, vec, yv, stream);
-  draft_rows(cfs, K, kb, (uint32_t)(chain0 + b), r, seed, g, yv, sv, xb, xr, mb, mr, cnt, vec, stream);
+  if constexpr (SPREAD) {
+    float y0[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) y0[c] = yv[c];
+    draft_rows_spread(cfs, zs, K, kb, (uint32_t)(chain0 + b), r, seed, g, yv, sv, xb, xr, mb, mr, cnt, vec, stream);
+    if (first) store4(xb, cnt, vec, y0, stream);
+  } else {
+    store4(xb, cnt, vec, yv, stream);
+    draft_rows(cfs, K, kb, (uint32_t)(chain0 + b), r, seed, g, yv, sv, xb, xr, mb, mr, cnt, vec, stream);
+  }
 }
 
 __global__ void fill_i32_kernel(int32_t* p, int64_t n, int32_t v) {
@@ -239,12 +251,14 @@ hipError_t draft_launch(const Sched& sc, int B, int K, int d, const float* y, co
                         const int32_t* k, const uint32_t* rnd, uint64_t seed, float* x,
                         sd_stride xs, float* mp, sd_stride mps, hipStream_t s, const int* gate) {
   const int ng = (d + 3) / 4;
-  dim3 grid((ng + kThreads - 1) / kThreads, B);
+  const bool spread = spread_rows(B, K, d);
+  const int per = spread ? 64 : kThreads;  // groups of a workgroup
+  dim3 grid((ng + per - 1) / per, B);
   const bool vec = draft_vec(d, xs, mps, y, x, mp) && aligned16(cs);
   // (both blocks are written: together they decide what the cache can hold)
   const bool stream = stream_rows((int64_t)B * (2 * K + 1) * d * 4);
   return timed("draft_block", s, [&] {
-    draft_kernel<false><<<grid, kThreads, 0, s>>>(sc, nullptr, K, d, y, cs, nullptr, nullptr, nullptr, 0, 0,
+    (spread ? draft_kernel<false, true> : draft_kernel<false, false>)<<<grid, kThreads, 0, s>>>(sc, nullptr, K, d, y, cs, nullptr, nullptr, nullptr, 0, 0,
                                                   k, rnd, seed, x, xs.chain, xs.row, mp, mps.chain,
                                                   mps.row, nullptr, vec, stream, gate, 0);
   });
@@ -257,12 +271,14 @@ hipError_t draft_cached_launch(const Sched& sc, const float4* coef, int B, int K
                                uint64_t seed, float* x, sd_stride xs, float* sv,
                                hipStream_t s, const int* gate, int chain0, int64_t stream_bytes) {
   const int ng = (d + 3) / 4;
-  dim3 grid((ng + kThreads - 1) / kThreads, B);
+  const bool spread = spread_rows(B, K, d);
+  const int per = spread ? 64 : kThreads;  // groups of a workgroup
+  dim3 grid((ng + per - 1) / per, B);
   const bool vec = draft_vec(d, xs, sd_stride{d, d}, y, x, sv) && aligned16(mqprev) &&
                    mqs.chain % 4 == 0 && mqs.row % 4 == 0;
   const bool stream = stream_rows(stream_bytes > 0 ? stream_bytes : (int64_t)B * (K + 1) * d * 4);
   return timed("draft_block", s, [&] {
-    draft_kernel<true><<<grid, kThreads, 0, s>>>(sc, coef, K, d, y, nullptr, crow, cstep, mqprev,
+    (spread ? draft_kernel<true, true> : draft_kernel<true, false>)<<<grid, kThreads, 0, s>>>(sc, coef, K, d, y, nullptr, crow, cstep, mqprev,
                                                  mqs.chain, mqs.row, k, rnd, seed, x, xs.chain,
                                                  xs.row, nullptr, 0, 0, sv, vec, stream, gate,
                                                  chain0);

@@ -198,7 +198,7 @@ __global__ __launch_bounds__(NW > 4 ? 64 * NW : kThreads) void gmm_softmax_kerne
     lw[c] = logw[mc];
     mq2[c] = musq[mc];
   }
-  // (at most 32 splits: one lane each)
+  // (at most 64 splits: one lane each)
   const double xl = xsq[(int64_t)min(lane, S - 1) * R + rr];
   double xs = lane < S ? xl : 0.0;
   double dot[4] = {0.0, 0.0, 0.0, 0.0};
@@ -410,8 +410,8 @@ __global__ __launch_bounds__(kThreads) void gmm_mean_lr_kernel(
 #pragma unroll
   for (int u = 0; u < kGItems; ++u)
     rn[u] = rnd[min(b_first + (int)((threadIdx.x + kThreads * u) >> 4), B - 1)];
-  // (the step index only: the table lookup that depends on it waits until
-  // after the contraction, so that no wait here covers the bulk loads)
+  // (the table lookup that depends on the step follows the bulk loads, and is
+  // used after the contraction: its wait for the step covers none of them)
   const int csi = cstep[min(b_first + (int)threadIdx.x, B - 1)];
   // keep that issue order: the scheduler must not hoist the bulk loads above
   __builtin_amdgcn_sched_barrier(0);
@@ -422,6 +422,7 @@ __global__ __launch_bounds__(kThreads) void gmm_mean_lr_kernel(
   for (int i = 0; i < 5; ++i) xv[i] = load_quad<EDGE>(X + (int64_t)min(r0 + lrb + i, R - 1) * d, col, d);
   svl = load_quad<EDGE>(SV + (int64_t)min(bl, B - 1) * d, col, d);
   svh = load_quad<EDGE>(SV + (int64_t)min(bh, B - 1) * d, col, d);
+  const float csw = coef[csi].w;  // 1 / c2 at the chain's cache step
   split::Acc acc[1];
   split::zero(acc[0]);
   double unused[1] = {0.0};
@@ -431,7 +432,7 @@ __global__ __launch_bounds__(kThreads) void gmm_mean_lr_kernel(
   for (int b = 0; b < 4; ++b)
     *reinterpret_cast<split::f32x4*>(&stage[split::out_row<1>(0) * LDW + split::out_col(b)]) = acc[0].c[b];
   if (threadIdx.x < 3 * TILE) rc[threadIdx.x] = r0 + (int)threadIdx.x / 3 < R ? rcv : 0.f;
-  if (threadIdx.x < TILE) cscale[threadIdx.x] = coef[csi].w;
+  if (threadIdx.x < TILE) cscale[threadIdx.x] = csw;
   // G of the residual (RESID stream of each chain's current round) depends
   // only on the chain and the coordinate: drawn once per chain of the tile
   // (item e: chain e / 16, coordinates 4 (e % 16) ..)
@@ -536,18 +537,20 @@ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // Split of the logits GEMM over d: the number of k-chunks per split and the
 // number of splits minimise (rounds of workgroups over 512 slots, two per
 // compute unit) x (chunks per workgroup), i.e. the critical path, preferring
-// fewer splits on ties.
+// fewer splits on ties.  The unpadded measure of a workspace keeps the limit of
+// 32 splits that decided which calls the fixed scratch takes.
 // Buffers for R rows; the split is chosen for plan_rows rows (0: R).
-Plan make_plan(const Target& t, int R, int plan_rows = 0, bool padded = true) {
+// At most 64 splits (a lane of the softmax each).
+Plan make_plan(const Target& t, int R, int plan_rows = 0, bool padded = true, int max_splits = 64) {
   Plan p{};
   const size_t M = padded ? t.Mp : t.M;
   // (tiles of kSplitRows rows, two workgroups per compute unit)
   const int Rp = plan_rows > 0 ? plan_rows : R;
   const int tiles = ((Rp + kSplitRows - 1) / kSplitRows) * ((t.M + TILE - 1) / TILE);
   const int nchunks = (t.d + KC - 1) / KC;
-  constexpr int kSlots = 512, kMaxSplits = 32;
+  constexpr int kSlots = 512;
   int best_cost = 1 << 30, best_per = nchunks;
-  for (int S = 1; S <= kMaxSplits && S <= nchunks; ++S) {
+  for (int S = 1; S <= max_splits && S <= nchunks; ++S) {
     const int per = (nchunks + S - 1) / S;
     const int splits = (nchunks + per - 1) / per;
     const int cost = ((tiles * splits + kSlots - 1) / kSlots) * per;
@@ -598,7 +601,7 @@ size_t target_ws_bytes(const Target& t, int rows, int plan_rows) {
 }
 
 size_t target_ws_bytes_unpadded(const Target& t, int rows) {
-  return t.prec == SD_BF16 ? target_ws_bytes_unpadded_bf16(t, rows) : make_plan(t, rows, 0, false).total;
+  return t.prec == SD_BF16 ? target_ws_bytes_unpadded_bf16(t, rows) : make_plan(t, rows, 0, false, 32).total;
 }
 
 hipError_t gmm_softmax_launch(const Target& t, int R, int plan_rows, int S, const float* part, const double* xsq,

@@ -106,4 +106,55 @@ __device__ __forceinline__ void draft_rows(const float4* lds, int K, int kb, uin
   }
 }
 
+// Draft rows of few chains, by a workgroup of four wavefronts over the same 64
+// groups of coordinates (g, one per lane): a launch of fewer wavefronts than
+// SIMDs takes as long as one thread's serial draws, so each wavefront draws the
+// normals of every fourth row into zs, all four walk the recursion, and each
+// stores the rows it drew.  The first barrier also orders the callers' reads of
+// the chain's rows before these stores, and publishes their coefs (draft_coefs).
+// Same arithmetic as draft_rows.
+constexpr int kSpreadRows = 16;
+__device__ __forceinline__ void draft_rows_spread(const float4* coefs, float4 (*zs)[64], int K, int kb,
+                                                  uint32_t chain, uint32_t rnd, uint64_t seed, int g,
+                                                  float (&yv)[4], const float (&sv)[4], float* xb, int64_t xr,
+                                                  float* mb, int64_t mr, int cnt, bool vec, bool stream) {
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  float m[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int i0 = 1; i0 <= kb; i0 += kSpreadRows) {
+    if (i0 > 1) __syncthreads();  // the previous rows' normals are consumed
+#pragma unroll
+    for (int u = 0; u < kSpreadRows / 4; u += 2) {
+      if (i0 + w + 4 * u > kb) break;
+      // (two rows at a time, the second perhaps past the block: their chains overlap)
+      const float4 za = normals4(philox((uint32_t)g, chain, rnd, (TAG_DRAFT << 24) | (uint32_t)(i0 + w + 4 * u), seed));
+      const float4 zb = normals4(philox((uint32_t)g, chain, rnd, (TAG_DRAFT << 24) | (uint32_t)(i0 + w + 4 * u + 4), seed));
+      zs[w + 4 * u][lane] = za;
+      zs[w + 4 * u + 4][lane] = zb;
+    }
+    __syncthreads();
+    for (int i = i0; i <= min(kb, i0 + kSpreadRows - 1); ++i) {
+      const float4 z = zs[i - i0][lane], cf = coefs[i - 1];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        m[c] = draft_mean(cf.x, yv[c], cf.y, sv[c]);
+        yv[c] = m[c] + cf.z * get4(z, c);
+      }
+      if (((i - 1) & 3) != w) continue;
+      if (mb) store4(mb + (int64_t)(i - 1) * mr, cnt, vec, m, stream);
+      store4(xb + (int64_t)i * xr, cnt, vec, yv, stream);
+    }
+  }
+  for (int i = kb + 1; i <= K; ++i) {
+    if (((i - 1) & 3) != w) continue;
+    if (mb) store4(mb + (int64_t)(i - 1) * mr, cnt, vec, m, stream);
+    store4(xb + (int64_t)i * xr, cnt, vec, yv, stream);
+  }
+}
+
+// Whether a draft of B blocks of K rows in d coordinates is spread: at one
+// wavefront per 64 groups it would leave SIMDs (1024 on the chip) without any.
+inline bool spread_rows(int B, int K, int d) {
+  return K > 1 && (int64_t)B * (((d + 3) / 4 + 63) / 64) <= 1024;
+}
+
 }  // namespace sd

@@ -409,27 +409,31 @@ __global__ __launch_bounds__(kThreads) void scan_fused_kernel(
   while (kp < K) kp <<= 1;
   const int lpr = kThreads / kp, j = threadIdx.x / lpr, sub = threadIdx.x % lpr;
   double a2[4] = {0.0, 0.0, 0.0, 0.0}, az[4] = {0.0, 0.0, 0.0, 0.0}, ag[4] = {0.0, 0.0, 0.0, 0.0};
-  if (j < K) {
-    const double* pl = lrp + ((int64_t)b * K1 + j) * nct * 3;
-    int ct = sub;
-    for (; ct + 3 * lpr < nct; ct += 4 * lpr) {
+  const double* pl = lrp + ((int64_t)b * K1 + min(j, K - 1)) * nct * 3;
+  double q[4][3];
+  auto request = [&](int ct) {  // four tiles' partials (a missing one repeats the last)
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const double* q = pl + 3 * (ct + u * lpr);
-        a2[u] += q[0];
-        az[u] += q[1];
-        ag[u] += q[2];
-      }
-    }
+    for (int u = 0; u < 4; ++u)
 #pragma unroll
-    for (int u = 0; u < 3; ++u) {
-      if (ct + u * lpr < nct) {
-        const double* q = pl + 3 * (ct + u * lpr);
-        a2[u] += q[0];
-        az[u] += q[1];
-        ag[u] += q[2];
-      }
+      for (int e = 0; e < 3; ++e) q[u][e] = pl[3 * min(ct + u * lpr, nct - 1) + e];
+  };
+  auto add = [&](int ct) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const bool in = j < K && ct + u * lpr < nct;
+      a2[u] += in ? q[u][0] : 0.0;
+      az[u] += in ? q[u][1] : 0.0;
+      ag[u] += in ? q[u][2] : 0.0;
     }
+  };
+  request(sub);
+  // the chain's uniforms while the partials are on their way
+  Draws dr{};
+  if (threadIdx.x < 64) dr = draw_uniforms((uint32_t)(chain0 + b), r, seed, lane);
+  add(sub);
+  for (int ct = sub + 4 * lpr; ct - sub < nct; ct += 4 * lpr) {
+    request(ct);
+    add(ct);
   }
   if (live == 0) return;
   const int kb = k < N ? min(K, N - k) : 0;
@@ -443,11 +447,9 @@ __global__ __launch_bounds__(kThreads) void scan_fused_kernel(
   double s2 = (a2[0] + a2[1]) + (a2[2] + a2[3]);
   double sz = (az[0] + az[1]) + (az[2] + az[3]);
   double sgd = (ag[0] + ag[1]) + (ag[2] + ag[3]);
-  for (int o = 1; o < lpr; o <<= 1) {
-    s2 += __shfl_xor(s2, o);
-    sz += __shfl_xor(sz, o);
-    sgd += __shfl_xor(sgd, o);
-  }
+  s2 = group_sum(s2, lpr);
+  sz = group_sum(sz, lpr);
+  sgd = group_sum(sgd, lpr);
   __shared__ double sums[SD_MAX_BLOCK][3];
   if (sub == 0 && j < K) {
     sums[j][0] = s2;
@@ -456,7 +458,6 @@ __global__ __launch_bounds__(kThreads) void scan_fused_kernel(
   }
   __syncthreads();
   if (threadIdx.x >= 64) return;  // one wavefront decides
-  const Draws dr = draw_uniforms((uint32_t)(chain0 + b), r, seed, lane);
   const bool valid = lane < kb;
   s2 = valid ? sums[lane][0] : 0.0;
   sz = valid ? sums[lane][1] : 0.0;

@@ -66,6 +66,18 @@ __device__ __forceinline__ double wave_sum(double v) {
   return swap_add<true>(v, v);
 }
 
+// Sum over each aligned group of n lanes (a power of two from 4 to 64, the same
+// in the whole wavefront), in every lane of it.
+__device__ __forceinline__ double group_sum(double v, int n) {
+  v += dpp<kDppXor1>(v);
+  v += dpp<kDppXor2>(v);
+  if (n >= 8) v += dpp<kDppHalfMirror>(v);
+  if (n >= 16) v += dpp<kDppMirror>(v);
+  if (n >= 32) v = swap_add<false>(v, v);
+  if (n >= 64) v = swap_add<true>(v, v);
+  return v;
+}
+
 // Maximum over the wavefront, in every lane.
 __device__ __forceinline__ float wave_max(float v) {
   v = fmaxf(v, dpp<kDppXor1>(v));
