@@ -20,6 +20,11 @@ enum : uint32_t {
   TAG_TARGET = 6
 };
 
+// a ^ b ^ c in one instruction (truth table 0x96).
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
 __device__ __forceinline__ uint4 philox(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                         uint64_t seed) {
   uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
@@ -29,7 +34,8 @@ __device__ __forceinline__ uint4 philox(uint32_t c0, uint32_t c1, uint32_t c2, u
     const uint64_t p0 = (uint64_t)0xD2511F53u * c0, p1 = (uint64_t)0xCD9E8D57u * c2;
     const uint32_t lo0 = (uint32_t)p0, hi0 = (uint32_t)(p0 >> 32);
     const uint32_t lo1 = (uint32_t)p1, hi1 = (uint32_t)(p1 >> 32);
-    const uint32_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
+    // (the first round's n0 is the same for every counter c0: left to the scalar unit)
+    const uint32_t n0 = r == 0 ? hi1 ^ c1 ^ k0 : xor3(hi1, c1, k0), n2 = xor3(hi0, c3, k1);
     c0 = n0;
     c1 = lo1;
     c2 = n2;
@@ -50,18 +56,21 @@ __device__ __forceinline__ double uniform64(uint32_t w) {
 }
 
 // -2 ln u for the 24-bit uniform u = (m + 0.5) 2^-24 of word w, in float32
-// without losing the small-radius tail.  For u < 1/2, u is exact in float32.
-// For u >= 1/2, t = 1 - u = (2^24 - 1 - m + 0.5) 2^-24 is exact, w = fl(1 - t)
-// and ln u = ln w + (u - w)/w with u - w = -((w - 1) + t) exact, so one logf
-// serves both halves (no divergent branch).  The correction is below one ulp
-// of ln w, so the hardware reciprocal (about 1 ulp) is exact enough for it.
+// without losing the small-radius tail.  v = fl(u) is exact for u < 1/2; e = u -
+// v (0 or 2^-25 either way) is exact by the two subtractions, and ln u = ln v +
+// e/v, where e/v = e (1 + s + s^2) with s = 1 - v: e is not 0 only for v in
+// [1/2, 1], where that is within 2^-27 of it.  v is a normal number below or at
+// 1, so the hardware logarithm (base 2, about 1 ulp) needs no scaling, and its
+// product with ln 2 carries the constant's and the product's low parts.
 __device__ __forceinline__ float neg2log_u24(uint32_t w) {
-  const uint32_t m = w >> 8;
-  const bool hi = m >= (1u << 23);
-  const float t = ((float)((1u << 24) - 1u - m) + 0.5f) * 0x1p-24f;
-  const float wv = hi ? 1.0f - t : ((float)m + 0.5f) * 0x1p-24f;
-  const float corr = hi ? -((wv - 1.0f) + t) * __builtin_amdgcn_rcpf(wv) : 0.0f;
-  return -2.0f * (logf(wv) + corr);
+  constexpr float kHi = -2.0f * 0x1.62e42ep-1f, kLo = -2.0f * 0x1.efa39ep-25f;  // -2 ln 2
+  const float m = (float)(w >> 8) * 0x1p-24f;
+  const float v = m + 0x1p-25f;
+  const float e = -2.0f * ((m - v) + 0x1p-25f), s = 1.0f - v;
+  const float y = __builtin_amdgcn_logf(v);
+  const float h = y * kHi;
+  const float l = __fmaf_rn(y, kLo, __fmaf_rn(y, kHi, -h)) + __fmaf_rn(e, __fmaf_rn(s, s, s), e);
+  return __fmaf_rn(y, kHi, l);
 }
 
 // Box-Muller on (w0, w1) and (w2, w3): radius sqrt(-2 ln u_a), angle 2 pi u_b.
@@ -72,8 +81,8 @@ __device__ __forceinline__ float neg2log_u24(uint32_t w) {
 __device__ __forceinline__ float4 normals4(uint4 w) {
   const float ra = __builtin_amdgcn_sqrtf(neg2log_u24(w.x));
   const float rc = __builtin_amdgcn_sqrtf(neg2log_u24(w.z));
-  const float ub = ((float)(w.y >> 8) + 0.5f) * 0x1p-24f;
-  const float ud = ((float)(w.w >> 8) + 0.5f) * 0x1p-24f;
+  const float ub = __fmaf_rn((float)(w.y >> 8), 0x1p-24f, 0x1p-25f);
+  const float ud = __fmaf_rn((float)(w.w >> 8), 0x1p-24f, 0x1p-25f);
   return make_float4(ra * __builtin_amdgcn_cosf(ub), ra * __builtin_amdgcn_sinf(ub),
                      rc * __builtin_amdgcn_cosf(ud), rc * __builtin_amdgcn_sinf(ud));
 }
