@@ -535,25 +535,33 @@ struct Plan {
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Split of the logits GEMM over d: the number of k-chunks per split and the
-// number of splits minimise (rounds of workgroups over 512 slots, two per
-// compute unit) x (chunks per workgroup), i.e. the critical path, preferring
-// fewer splits on ties.  The unpadded measure of a workspace keeps the limit of
-// 32 splits that decided which calls the fixed scratch takes.
+// number of splits (at most 64: a lane of the softmax each) minimise the time of
+// the critical path, (rounds of workgroups over 512 slots, two per compute unit)
+// x (chunks per workgroup) x 2.4 us a chunk (twice that where rows of X are not
+// 16-byte aligned), plus that of the partials, written and read at 2.7 TB/s; both
+// rates from one and two chunks a workgroup at 2304 rows of 784 (two: logits 12.7
+// -> 11.4, softmax 6.8 -> 5.2 us) and two and three at 777 rows of 4107 (two is
+// better: 16.0 + 6.1 against 19.1 + 4.6 us).
+// measure: the workspace by which calls on the fixed scratch are accepted, rows
+// of M components and splits chosen by the critical path among at most 32.
 // Buffers for R rows; the split is chosen for plan_rows rows (0: R).
-// At most 64 splits (a lane of the softmax each).
-Plan make_plan(const Target& t, int R, int plan_rows = 0, bool padded = true, int max_splits = 64) {
+Plan make_plan(const Target& t, int R, int plan_rows = 0, bool measure = false) {
   Plan p{};
-  const size_t M = padded ? t.Mp : t.M;
+  const size_t M = measure ? t.M : t.Mp;
   // (tiles of kSplitRows rows, two workgroups per compute unit)
   const int Rp = plan_rows > 0 ? plan_rows : R;
   const int tiles = ((Rp + kSplitRows - 1) / kSplitRows) * ((t.M + TILE - 1) / TILE);
   const int nchunks = (t.d + KC - 1) / KC;
   constexpr int kSlots = 512;
-  int best_cost = 1 << 30, best_per = nchunks;
+  const int max_splits = measure ? 32 : 64;
+  const double chunk_us = t.d % 4 ? 4.8 : 2.4;
+  const double split_us = measure ? 0.0 : 8.0 * Rp * t.Mp / 2.7e6;
+  double best_cost = 1e30;
+  int best_per = nchunks;
   for (int S = 1; S <= max_splits && S <= nchunks; ++S) {
     const int per = (nchunks + S - 1) / S;
     const int splits = (nchunks + per - 1) / per;
-    const int cost = ((tiles * splits + kSlots - 1) / kSlots) * per;
+    const double cost = chunk_us * (((tiles * splits + kSlots - 1) / kSlots) * per) + split_us * splits;
     if (cost < best_cost) {
       best_cost = cost;
       best_per = per;
@@ -601,7 +609,7 @@ size_t target_ws_bytes(const Target& t, int rows, int plan_rows) {
 }
 
 size_t target_ws_bytes_unpadded(const Target& t, int rows) {
-  return t.prec == SD_BF16 ? target_ws_bytes_unpadded_bf16(t, rows) : make_plan(t, rows, 0, false, 32).total;
+  return t.prec == SD_BF16 ? target_ws_bytes_unpadded_bf16(t, rows) : make_plan(t, rows, 0, true).total;
 }
 
 hipError_t gmm_softmax_launch(const Target& t, int R, int plan_rows, int S, const float* part, const double* xsq,
