@@ -301,7 +301,7 @@ __device__ __forceinline__ void mean_lr_epilogue_vec(
     sl[p] = buf_ld4(vs, (uint32_t)(((bl - b_first) * d + col) * 4));
     sh[p] = buf_ld4(vs, (uint32_t)(((bh - b_first) * d + col) * 4));
   }
-  double t2 = 0.0, tz = 0.0, tg = 0.0;  // this lane's row (see reduce_rows16), both passes
+  double s2[8] = {}, sz[8] = {}, sgd[8] = {};  // of the thread's rows, both passes
 #pragma unroll
   for (int p = 0; p < 2; ++p) {
     __syncthreads();  // the operand tiles (p = 0) or the previous pass are consumed
@@ -318,10 +318,8 @@ __device__ __forceinline__ void mean_lr_epilogue_vec(
     }
     __syncthreads();
     const int col = c0 + epi_col(cg, p);
-    double s2[8], sz[8], sgd[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      s2[i] = sz[i] = sgd[i] = 0.0;
       const int lr = lr0 + i, row = r0 + lr;
       const int b = row / K1, j = row - b * K1;
       const float c1 = rc[3 * lr], c2 = rc[3 * lr + 1], rho = rc[3 * lr + 2];
@@ -339,7 +337,7 @@ __device__ __forceinline__ void mean_lr_epilogue_vec(
       const float4 sv = b == bl ? sl[p] : sh[p];
       const float4 gv = *reinterpret_cast<const float4*>(&gz[(b - b_first) * LDO + 4 * cg]);
       const float c2s = c2 * cscale[b - b_first];
-      double a2 = 0.0, az = 0.0, ag = 0.0;
+      double a2 = s2[i], az = sz[i], ag = sgd[i];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const float pe = draft_mean(c1, comp(x, e), c2s, comp(sv, e));  // m^p
@@ -353,10 +351,8 @@ __device__ __forceinline__ void mean_lr_epilogue_vec(
       sz[i] = keep ? az : 0.0;
       sgd[i] = keep ? ag : 0.0;
     }
-    t2 += reduce_rows16<8>(s2, cg);
-    tz += reduce_rows16<8>(sz, cg);
-    tg += reduce_rows16<8>(sgd, cg);
   }
+  const double t2 = reduce_rows16<8>(s2, cg), tz = reduce_rows16<8>(sz, cg), tg = reduce_rows16<8>(sgd, cg);
   const int row = r0 + lr0 + row_of<8>(cg);
   if ((cg & 1) == 0 && row < R) {
     double* o = lrp + ((int64_t)row * nct + ct) * 3;
@@ -669,12 +665,12 @@ __global__ __launch_bounds__(T::kThreads, T::TC == 128 ? 2 : 1) void gmm_mean_lr
       buf_st4_stream(vq, (uint32_t)(((row7 + 16 * rb + 8) * d + colp + 32 * pr) * 4), b3 ? qs[1] : recv);
     }
     // the four lanes of the row (sub = 0..3), in a fixed order
-    a2 += __shfl_xor(a2, 16);
-    az += __shfl_xor(az, 16);
-    ag += __shfl_xor(ag, 16);
-    a2 += __shfl_xor(a2, 32);
-    az += __shfl_xor(az, 32);
-    ag += __shfl_xor(ag, 32);
+    a2 = swap_add<false>(a2, a2);
+    az = swap_add<false>(az, az);
+    ag = swap_add<false>(ag, ag);
+    a2 = swap_add<true>(a2, a2);
+    az = swap_add<true>(az, az);
+    ag = swap_add<true>(ag, ag);
     if (sub == 0) {
       double* o = part + ((int64_t)wc * TR + lr) * 3;
       o[0] = keep ? a2 : 0.0;

@@ -3,11 +3,13 @@
 
 #include <hip/hip_runtime.h>
 
+#include "wavered.hpp"
+
 namespace sd {
 
 // Each of the 16 lanes (lane index cg in the group) holds NR per-row partial
-// sums (NR = 4 or 8) of the same NR rows.  Butterfly reduce-scatter: the
-// exchanges at distance 8, 4 (and 2 for NR = 8) halve the rows a lane keeps,
+// sums (NR = 4 or 8) of the same NR rows.  Reduce-scatter by DPP exchanges: with
+// lane cg ^ 8, then cg ^ 7 (and cg ^ 2 for NR = 8) a lane keeps half of its rows,
 // the remaining exchanges complete the sum, so lane cg ends with the total of
 // row row_of<NR>(cg) over all 16 lanes (lanes that differ only in the low
 // bits hold the same row).  Fixed order, hence deterministic.
@@ -24,24 +26,19 @@ __device__ __forceinline__ double reduce_rows16(const double (&v)[NR], int cg) {
   const bool b3 = cg & 8, b2 = cg & 4, b1 = cg & 2;
   double w[H];
 #pragma unroll
-  for (int i = 0; i < H; ++i) {
-    const double send = b3 ? v[i] : v[i + H];
-    w[i] = (b3 ? v[i + H] : v[i]) + __shfl_xor(send, 8);
-  }
+  for (int i = 0; i < H; ++i)
+    w[i] = (b3 ? v[i + H] : v[i]) + dpp<kDppRor8>(b3 ? v[i] : v[i + H]);
   constexpr int Q = H / 2;
   double u[Q];
 #pragma unroll
-  for (int i = 0; i < Q; ++i) {
-    const double send = b2 ? w[i] : w[i + Q];
-    u[i] = (b2 ? w[i + Q] : w[i]) + __shfl_xor(send, 4);
-  }
+  for (int i = 0; i < Q; ++i)
+    u[i] = (b2 ? w[i + Q] : w[i]) + dpp<kDppHalfMirror>(b2 ? w[i] : w[i + Q]);
   double z;
-  if constexpr (NR == 8) {
-    z = (b1 ? u[1] : u[0]) + __shfl_xor(b1 ? u[0] : u[1], 2);
-  } else {
-    z = u[0] + __shfl_xor(u[0], 2);
-  }
-  return z + __shfl_xor(z, 1);
+  if constexpr (NR == 8)
+    z = (b1 ? u[1] : u[0]) + dpp<kDppXor2>(b1 ? u[0] : u[1]);
+  else
+    z = u[0] + dpp<kDppXor2>(u[0]);
+  return z + dpp<kDppXor1>(z);
 }
 
 }  // namespace sd

@@ -10,8 +10,9 @@
 
 namespace sd {
 
-// DPP controls: lane ^ 1, lane ^ 2, 7 - lane (of 8), 15 - lane (of 16).
-constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140;
+// DPP controls: lane ^ 1, lane ^ 2, 7 - lane (of 8), 15 - lane (of 16), lane ^ 8
+// (a rotation of 16 by 8).
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140, kDppRor8 = 0x128;
 
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp32(uint32_t v) {
