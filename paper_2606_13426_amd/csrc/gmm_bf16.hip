@@ -16,6 +16,7 @@
 // The mean GEMMs' 128 x 128 accumulator tile is handed to the epilogue
 // through LDS in two passes of 64 columns, each over the operand buffers'
 // storage.
+#include <algorithm>
 #include <type_traits>
 
 #include "bufio.hpp"
@@ -696,6 +697,88 @@ __global__ __launch_bounds__(T::kThreads, T::TC == 128 ? 2 : 1) void gmm_mean_lr
   }
 }
 
+// The public target call on the same tiles (288 rows of any batch): m^q, the
+// score if asked, or the plain step (EM), from the accumulators where they are,
+// 16-byte pieces of whole 128-byte lines as in the sampler's kernel.
+template <class T, bool EM>
+__global__ __launch_bounds__(T::kThreads, 1) void gmm_mean_bf16_big_kernel(
+    int R, int M, int d, const uint16_t* __restrict__ P, const uint16_t* __restrict__ muT,
+    const float* __restrict__ X, int ldx, const float* __restrict__ rowc, float* __restrict__ mq, int ldq,
+    float* __restrict__ score, int lds, bool stream, const int* gate, EmStep em) {
+  using bf16b::CB;
+  using bf16b::RB;
+  using bf16b::TR;
+  if (gate && *gate == 0) return;
+  __shared__ typename T::Lds sm[2];
+  __shared__ float rc[3 * TR];
+  const int nrt = (R + TR - 1) / TR, nct = d / T::TC;
+  int rt;
+  const int ct = big_tile_order(nrt, nct, rt);
+  const int r0 = rt * TR, rows = min(TR, R - r0), c0 = ct * T::TC;
+  for (int e = threadIdx.x; e < 3 * TR; e += T::kThreads) rc[e] = e < 3 * rows ? rowc[3 * (int64_t)r0 + e] : 0.f;
+  bf16b::f32x4 acc[RB][CB];
+  bf16b::zero(acc);
+  T::run(sm, buf_view(muT + (int64_t)c0 * M, (int64_t)T::TC * M * 2), M,
+         buf_view(P + (int64_t)r0 * M, (int64_t)rows * M * 2), M, 0, M, acc);
+  // (the views end with the tile's last row: its columns lie below d <= ld)
+  const __amdgpu_buffer_rsrc_t vx = buf_view(X + (int64_t)r0 * ldx, ((int64_t)(rows - 1) * ldx + d) * 4);
+  const __amdgpu_buffer_rsrc_t vq = buf_view(mq + (int64_t)r0 * ldq, ((int64_t)(rows - 1) * ldq + d) * 4);
+  const __amdgpu_buffer_rsrc_t vs =
+      buf_view(score ? score + (int64_t)r0 * lds : mq, score ? ((int64_t)(rows - 1) * lds + d) * 4 : 0);
+  const int lane = threadIdx.x & 63, b3 = (lane >> 3) & 1;
+  const int row7 = T::out_row(0) - (lane & 15) + (lane & 7);
+  const int colp = c0 + T::out_col(0) + 16 * b3;
+  float4 xraw[RB][CB];
+  auto load_x = [&](int rb) {
+#pragma unroll
+    for (int h = 0; h < CB; ++h)
+      xraw[rb][h] = buf_ld4(vx, (uint32_t)(((row7 + 16 * rb + 8 * (h & 1)) * ldx + colp + 32 * (h >> 1)) * 4));
+  };
+  auto put = [&](__amdgpu_buffer_rsrc_t v, int ld, int rb, int pr, const float4 (&q)[2]) {
+    const float4 recv = xchg8(b3 ? q[0] : q[1]);
+    const uint32_t o = (uint32_t)(((row7 + 16 * rb) * ld + colp + 32 * pr) * 4);
+    const uint32_t o8 = o + (uint32_t)(8 * ld * 4);
+    const float4 a = b3 ? recv : q[0], b = b3 ? q[1] : recv;
+    if (stream) {
+      buf_st4_stream(v, o, a);
+      buf_st4_stream(v, o8, b);
+    } else {
+      buf_st4(v, o, a);
+      buf_st4(v, o8, b);
+    }
+  };
+  load_x(0);
+  load_x(1);
+  load_x(2);
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    if (rb + 3 < RB) load_x(rb + 3);
+    const int lr = T::out_row(rb);
+    const float c1 = rc[3 * lr], c2 = rc[3 * lr + 1], rho = rc[3 * lr + 2];
+#pragma unroll
+    for (int pr = 0; pr < CB / 2; ++pr) {
+      const float4 lo = xraw[rb][2 * pr], hi = xraw[rb][2 * pr + 1], recv = xchg8(b3 ? lo : hi);
+      float4 qs[2], ss[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const bf16b::f32x4 o = acc[rb][2 * pr + h];
+        const float4 x = h == 0 ? (b3 ? recv : lo) : (b3 ? hi : recv);
+        const float4 sc = make_float4(o[0] - rho * x.x, o[1] - rho * x.y, o[2] - rho * x.z, o[3] - rho * x.w);
+        float4 q = make_float4(c1 * x.x + c2 * sc.x, c1 * x.y + c2 * sc.y, c1 * x.z + c2 * sc.z,
+                               c1 * x.w + c2 * sc.w);
+        if constexpr (EM)
+          q = em_state(q, em.sigma, (uint32_t)((c0 + T::out_col(2 * pr + h)) >> 2), (uint32_t)(r0 + lr),
+                       (uint32_t)em.n, em.seed);
+        qs[h] = q;
+        ss[h] = sc;
+      }
+      put(vq, ldq, rb, pr, qs);
+      if (!EM && score) put(vs, lds, rb, pr, ss);
+    }
+    if (EM && c0 == 0 && T::out_col(0) == 0 && lr < rows) em.step[r0 + lr] = em.n + 1;
+  }
+}
+
 // The tile of the sampler's bf16 mean GEMM: 288 x 256, one workgroup per
 // compute unit.
 using MeanTile = bf16b::Tile<256, 64>;
@@ -709,6 +792,17 @@ inline bool big_mean_ok(const Target& t, int K1, bool vecd) {
   return vecd && t.d % MeanTile::TC == 0 && t.M % MeanTile::KC == 0 && t.M >= 512 && K1 <= bf16b::TR &&
          (int64_t)(bf16b::TR + 1) * t.d * 4 < ((int64_t)1 << 31) &&
          (int64_t)bf16b::TR * t.M * 2 < ((int64_t)1 << 31);
+}
+
+// Whether a public call of R rows runs on these tiles: where the sampler's rule
+// allows them, one workgroup per compute unit at a time loses to the 128 x 128
+// kernel only through tiles that are not full and a last wave that is not.
+inline bool big_public_ok(const Target& t, int R, int64_t ld) {
+  const int64_t tiles = (int64_t)((R + bf16b::TR - 1) / bf16b::TR) * (t.d / MeanTile::TC);
+  const int64_t waves = (tiles + 255) / 256;
+  return t.d % MeanTile::TC == 0 && t.M % MeanTile::KC == 0 && t.M >= 512 &&
+         (int64_t)(bf16b::TR + 1) * ld * 4 < ((int64_t)1 << 31) && (int64_t)bf16b::TR * t.M * 2 < ((int64_t)1 << 31) &&
+         4 * (int64_t)R * (t.d / MeanTile::TC) >= 3 * waves * 256 * bf16b::TR;
 }
 
 struct Plan {
@@ -816,6 +910,17 @@ hipError_t target_mean_bf16_launch(const Target& t, int R, const float* x, int64
   if (e != hipSuccess) return e;
   const bool vecq = (ldq % 4 == 0) && aligned16(mq);
   const bool vecs = score && (lds % 4 == 0) && aligned16(score);
+  const int64_t ldmax = std::max(ldx, std::max(ldq, score ? lds : (int64_t)0));
+  if (vecx && vecq && (vecs || !score) && big_public_ok(t, R, ldmax)) {
+    auto big = [&](auto noise) {
+      constexpr bool EM = decltype(noise)::value;
+      return launch_timed(EM ? "em_step_bf16" : "gmm_mean_bf16", gmm_mean_bf16_big_kernel<MeanTile, EM>,
+                          dim3(((R + bf16b::TR - 1) / bf16b::TR) * (t.d / MeanTile::TC)), dim3(MeanTile::kThreads),
+                          s, R, t.M, t.d, w.P, t.muT16, x, (int)ldx, w.rowc, mq, (int)ldq, score, (int)lds,
+                          stream_rows((int64_t)R * t.d * (score ? 8 : 4)), gate, em ? *em : EmStep{});
+    };
+    return em ? big(std::true_type{}) : big(std::false_type{});
+  }
   dim3 g2((t.d + TN - 1) / TN, (R + TM - 1) / TM);
   auto go = [&](auto noise) {
     constexpr bool EM = decltype(noise)::value;
