@@ -317,8 +317,10 @@ sd_status sd_run_sampler(sd_target target, int32_t B, int32_t K, sd_verify_mode 
  *                       kernels overlap the other's matrix work (joined back
  *                       into `stream` before the call returns); 0: the
  *                       library chooses (two when each half has at least
- *                       2048 target rows, B/2 (K+1)).  The results do not
- *                       depend on it:
+ *                       2048 target rows, B/2 (K+1), but one for a call of
+ *                       0 <= max_rounds < 32 whose drafts, B (K+1) d float32,
+ *                       take at most 256 MB).  The results do not depend on
+ *                       it:
  *                       every row is computed in the same order either way,
  *                       so y_out, tau_trace, the statistics and the state are
  *                       bit-identical.  A run split over calls may change it

@@ -507,9 +507,16 @@ inline int group_chains(int B, int groups, int g) {
 // two, ms per run): pixel3072 30.6 / 29.0, pixel12288 232 / 222, latent16384
 // 249 / 255 -- its 2304 rows make a logits grid of 252 one-per-CU workgroups,
 // and two halves need 280, a second wave.
-inline int choose_groups(int B, int K, int requested) {
+// A call that runs a slice of the rounds takes one group unless the draft block
+// exceeds the infinity cache: the second stream's fork and join cost a call about
+// 40 us, and two groups save 2 us a round at 1024 x 3072 (199 rounds 27.63 / 27.29
+// ms, 4 rounds 647 / 686 us), 10 to 28 where a block passes 256 MB (4 rounds of
+// 512 x 16384 2567 / 2495 us, of 512 x 17 x 12288 1998 / 1975).
+inline int choose_groups(int B, int K, int d, int requested, int max_rounds) {
   if (B < 2) return 1;
   if (requested == 1 || requested == 2) return requested;
+  constexpr int64_t kCacheBytes = (int64_t)256 << 20;
+  if (max_rounds >= 0 && max_rounds < 32 && (int64_t)B * (K + 1) * d * 4 <= kCacheBytes) return 1;
   return (int64_t)(B / 2) * (K + 1) >= 2048 ? 2 : 1;
 }
 
@@ -721,7 +728,7 @@ sd_status sd_run_sampler_ex(sd_target target, int32_t B, int32_t K,
   int64_t* totals = reinterpret_cast<int64_t*>(base + L.totals);
   void* tws = base + L.tws;
   const sd_stride xs{(int64_t)K1 * d, d}, mqs{(int64_t)K1 * d, d};
-  const int G = choose_groups(B, K, opts->groups);
+  const int G = choose_groups(B, K, d, opts->groups, opts->max_rounds);
   // the draft rows are streamed past the caches, or not, as for the whole block
   const int64_t block_bytes = (int64_t)B * K1 * d * 4;
 
