@@ -112,12 +112,19 @@ __device__ __forceinline__ double lane_value(double v, int i) {
   return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
+// 1/d to about an ulp (no finite value where d is zero or infinite).
+__device__ __forceinline__ double recip(double d) {
+  double r = __builtin_amdgcn_rcp(d);
+  r = fma(fma(-d, r, 1.0), r, r);
+  return fma(fma(-d, r, 1.0), r, r);
+}
+
 // x at g from four points (x_q, g_q): the cubic interpolant, and in *err the
 // larger distance to the quadratics through the first and the last three.
 __device__ __forceinline__ double cubic_at(const double (&px)[4], const double (&pg)[4], double g,
                                            double* err) {
-  const double r01 = 1.0 / (pg[0] - pg[1]), r02 = 1.0 / (pg[0] - pg[2]), r03 = 1.0 / (pg[0] - pg[3]);
-  const double r12 = 1.0 / (pg[1] - pg[2]), r13 = 1.0 / (pg[1] - pg[3]), r23 = 1.0 / (pg[2] - pg[3]);
+  const double r01 = recip(pg[0] - pg[1]), r02 = recip(pg[0] - pg[2]), r03 = recip(pg[0] - pg[3]);
+  const double r12 = recip(pg[1] - pg[2]), r13 = recip(pg[1] - pg[3]), r23 = recip(pg[2] - pg[3]);
   const double d0 = g - pg[0], d1 = g - pg[1], d2 = g - pg[2], d3 = g - pg[3];
   const double x3 = px[0] * (d1 * d2 * d3) * (r01 * r02 * r03) - px[1] * (d0 * d2 * d3) * (r01 * r12 * r13) +
                     px[2] * (d0 * d1 * d3) * (r02 * r12 * r23) - px[3] * (d0 * d1 * d2) * (r03 * r13 * r23);
@@ -185,11 +192,12 @@ __device__ double usample_exact(double logu, double la, double v, int lane) {
     double blo = lo, bhi = hi;
     if (centred) {
       const int e0 = min(max(cnt - 2, 0), top_lane - 3);
+      const double gx = sqrt(-fx);  // every lane's, before the reads: one square root
       double px[4], pg[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         px[q] = lane_value(x, e0 + q);
-        pg[q] = sqrt(-lane_value(fx, e0 + q));
+        pg[q] = lane_value(gx, e0 + q);
       }
       double err;
       const double xc = cubic_at(px, pg, gt, &err);
