@@ -302,7 +302,7 @@ __global__ __launch_bounds__(NW > 4 ? 64 * NW : kThreads) void gmm_softmax_kerne
 // comes in and the means go out in 16-byte pieces, 64 bytes of 16 rows per
 // instruction.  EM: the plain Euler-Maruyama step (EmStep), whose noise as a
 // kernel of its own was a fourth of a small step's launches and one more pass
-// over the rows.
+// over the rows (64 rows of 3072, a step: 16.7 -> 13.7 us, with the logits' splits).
 template <int EDGE, bool APART, bool EM>
 __global__ __launch_bounds__(kThreads) void gmm_mean_split_kernel(
     int R, int Mp, int Mk, int d, const float* __restrict__ P, const uint16_t* __restrict__ muTs,

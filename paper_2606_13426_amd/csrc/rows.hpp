@@ -153,6 +153,9 @@ __device__ __forceinline__ void draft_rows_spread(const float4* coefs, float4 (*
 
 // Whether a draft of B blocks of K rows in d coordinates is spread: at one
 // wavefront per 64 groups it would leave SIMDs (1024 on the chip) without any.
+// (advance 8 x 8 x 3072, 96 wavefronts: 7.5 -> 6.0 us; draft 300 x 20 x 64: 24.7
+// -> 9.9 a call with the coefficients of draft_coefs; at 256 x 8 x 784, 1024
+// wavefronts, 11.7 us either way.)
 inline bool spread_rows(int B, int K, int d) {
   return K > 1 && (int64_t)B * (((d + 3) / 4 + 63) / 64) <= 1024;
 }
