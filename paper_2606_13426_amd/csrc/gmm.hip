@@ -167,7 +167,9 @@ __global__ __launch_bounds__(kThreads, 2) void gmm_logits_split_kernel(
 // the wavefronts' own instructions are the limit, a lane keeps all splits of
 // four components and a wavefront takes 256.  NW wavefronts hold a row; every
 // input that does not hang on the step is requested at the start; lane l < S
-// sums ||x||^2.  The maximum is only a shift, so it is taken in float32.
+// sums ||x||^2.  The maximum is a float64 one: rounded to float32 it would be off
+// by more than the exponential's range from logits of about 2e9 on (a row far from
+// the data at a late step), and infinite from 3e38 on.
 // Per launch (rocprofv3), against one kernel of four components per lane with
 // LDS-permute reductions and the splits summed serially: 64 rows x 64
 // components of 24 splits 12.3 -> 4.7 us, 72 rows 11.9 -> 4.7, 4608 rows 11.9
@@ -237,13 +239,13 @@ __global__ __launch_bounds__(NW > 4 ? 64 * NW : kThreads) void gmm_softmax_kerne
     dot[0] = swap_add<false>(d02, d13);
   }
   double lg[NC];
-  float mx = -INFINITY;
+  double mx = -INFINITY;
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
     lg[c] = lw[c] - 0.5 * (double)d * t[c].x - 0.5 * (xs - 2.0 * a * dot[c] + a * a * mq2[c]) * t[c].y;
-    if (m + c < M) mx = fmaxf(mx, (float)lg[c]);
+    if (m + c < M) mx = fmax(mx, lg[c]);
   }
-  __shared__ float redm[kT / 64];
+  __shared__ double redm[kT / 64];
   __shared__ double2 reds[kT / 64];
   mx = wave_max(mx);
   const int w0 = (int)(threadIdx.x >> 6) - w;  // the row's first wavefront
@@ -251,13 +253,13 @@ __global__ __launch_bounds__(NW > 4 ? 64 * NW : kThreads) void gmm_softmax_kerne
     if (lane == 0) redm[w0 + w] = mx;
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < NW; ++i) mx = fmaxf(mx, redm[w0 + i]);
+    for (int i = 0; i < NW; ++i) mx = fmax(mx, redm[w0 + i]);
   }
   float e[NC];
   double sum = 0.0, sis = 0.0;
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
-    e[c] = m + c < M ? __expf((float)(lg[c] - (double)mx)) : 0.0f;
+    e[c] = m + c < M ? __expf((float)(lg[c] - mx)) : 0.0f;
     sum += (double)e[c];
     sis += (double)e[c] * t[c].y;
   }

@@ -44,7 +44,7 @@ __device__ __forceinline__ void swap16(uint32_t& a, uint32_t& b) {
   b = r[1];
 }
 template <bool ROW32>
-__device__ __forceinline__ double swap_add(double a, double b) {
+__device__ __forceinline__ void swap_pair(double& a, double& b) {
   const uint64_t ua = __builtin_bit_cast(uint64_t, a), ub = __builtin_bit_cast(uint64_t, b);
   uint32_t al = (uint32_t)ua, ah = (uint32_t)(ua >> 32), bl = (uint32_t)ub, bh = (uint32_t)(ub >> 32);
   if constexpr (ROW32) {
@@ -54,7 +54,19 @@ __device__ __forceinline__ double swap_add(double a, double b) {
     swap16(al, bl);
     swap16(ah, bh);
   }
-  return __builtin_bit_cast(double, ((uint64_t)ah << 32) | al) + __builtin_bit_cast(double, ((uint64_t)bh << 32) | bl);
+  a = __builtin_bit_cast(double, ((uint64_t)ah << 32) | al);
+  b = __builtin_bit_cast(double, ((uint64_t)bh << 32) | bl);
+}
+template <bool ROW32>
+__device__ __forceinline__ double swap_add(double a, double b) {
+  swap_pair<ROW32>(a, b);
+  return a + b;
+}
+template <bool ROW32>
+__device__ __forceinline__ double swap_max(double v) {
+  double w = v;
+  swap_pair<ROW32>(v, w);
+  return fmax(v, w);
 }
 
 // Sum over the wavefront, in every lane.
@@ -80,17 +92,13 @@ __device__ __forceinline__ double group_sum(double v, int n) {
 }
 
 // Maximum over the wavefront, in every lane.
-__device__ __forceinline__ float wave_max(float v) {
-  v = fmaxf(v, dpp<kDppXor1>(v));
-  v = fmaxf(v, dpp<kDppXor2>(v));
-  v = fmaxf(v, dpp<kDppHalfMirror>(v));
-  v = fmaxf(v, dpp<kDppMirror>(v));
-  uint32_t a = __builtin_bit_cast(uint32_t, v), b = a;
-  swap16(a, b);
-  v = fmaxf(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b));
-  a = b = __builtin_bit_cast(uint32_t, v);
-  swap32(a, b);
-  return fmaxf(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b));
+__device__ __forceinline__ double wave_max(double v) {
+  v = fmax(v, dpp<kDppXor1>(v));
+  v = fmax(v, dpp<kDppXor2>(v));
+  v = fmax(v, dpp<kDppHalfMirror>(v));
+  v = fmax(v, dpp<kDppMirror>(v));
+  v = swap_max<false>(v);
+  return swap_max<true>(v);
 }
 
 }  // namespace sd
