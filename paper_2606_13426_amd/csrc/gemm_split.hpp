@@ -9,7 +9,7 @@
 // exact in its float32 accumulator.  The three dropped terms (mid.lo, lo.mid,
 // lo.lo) are below 2^-23 |a||b| together, the size of one float32 rounding, so
 // the result is float32-accurate at 6/16 of the float32 instruction's
-// matrix-core time.
+// matrix-core time.  (Where that rounding shows, two of the three are kept: Sum.)
 //
 // Tile: 64 RB rows of A x 64 rows of B (the output's columns) per workgroup
 // of four wavefronts; wavefront w owns RB blocks of 16 rows (rows 16 (RB w +
@@ -184,16 +184,23 @@ __device__ __forceinline__ bf16x8 frag(const uint16_t* p) {
   return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(p));
 }
 
-// The chunk's 2 steps x 4 column blocks x RB row blocks x 6 terms.  APART: the
-// five small terms of a step are summed from zero and added to the leading
-// product's sum once, two roundings of the running sum per step instead of six:
-// in a contraction of few terms (d or M no multiple of 64) six show beside the
-// one or two of a float32 instruction (error of a score against 64 bits, 2 x
-// 191 components: 8.1e-7 there, 4.7e-7 apart; 4 x 20: 5.6e-7, 4.5e-7; 4107 x
-// 100: 1.11e-7 both).  Whole multiples of 64 keep the chain: the extra
-// registers take a wavefront per SIMD (a sampler call of 1024 x 3072 846 us
-// against 816).
-template <int RB, bool APART>
+// The chunk's 2 steps x 4 column blocks x RB row blocks of products:
+//   CHAIN      the six terms one after another on the running sum;
+//   APART      the five small ones of a step summed from zero and added to the
+//              leading product's sum once: two roundings of the running sum per
+//              step instead of six;
+//   APART_ALL  the same with mid.lo and lo.mid (what is left out is below 2^-32).
+// In a contraction of few terms six roundings show beside the one or two of a
+// float32 instruction (error of a score against 64 bits, 2 x 191 components:
+// 8.1e-7 there, 4.7e-7 apart; 4 x 20: 5.6e-7, 4.5e-7), so APART serves d or M
+// that are no multiple of 64.  Where one component has all of a row's weight its
+// mean GEMM is a single product, and dropping two terms of it adds to its one
+// rounding: score errors of up to 1.008 times a float32 instruction's over 70
+// ragged shapes (448 x 1 component, 2168 x 88), 1.000 with all of them, hence
+// APART_ALL there.  Whole multiples of 64 keep the chain: the extra registers
+// take a wavefront per SIMD (a sampler call of 1024 x 3072 846 us against 816).
+enum Sum { CHAIN, APART, APART_ALL };
+template <int RB, Sum SUM>
 __device__ __forceinline__ void mma_chunk(const uint16_t* lds, const AChunk (&a)[RB], Acc (&acc)[RB]) {
   const int lane = threadIdx.x & 63;
   const uint16_t* pb = lds + (lane & 15) * LDH + 8 * (lane >> 4);
@@ -209,13 +216,17 @@ __device__ __forceinline__ void mma_chunk(const uint16_t* lds, const AChunk (&a)
 #pragma unroll
       for (int r = 0; r < RB; ++r) {
         f32x4 c = acc[r].c[b];
-        if constexpr (APART) c = f32x4{0.f, 0.f, 0.f, 0.f};
+        if constexpr (SUM != CHAIN) c = f32x4{0.f, 0.f, 0.f, 0.f};
+        if constexpr (SUM == APART_ALL) {
+          c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bm, al[r], c, 0, 0, 0);
+          c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bl, am[r], c, 0, 0, 0);
+        }
         c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh, al[r], c, 0, 0, 0);
         c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bl, ah[r], c, 0, 0, 0);
         c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bm, am[r], c, 0, 0, 0);
         c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh, am[r], c, 0, 0, 0);
         c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bm, ah[r], c, 0, 0, 0);
-        if constexpr (APART)
+        if constexpr (SUM != CHAIN)
           acc[r].c[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh, ah[r], acc[r].c[b], 0, 0, 0) + c;
         else
           acc[r].c[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh, ah[r], c, 0, 0, 0);
@@ -225,14 +236,14 @@ __device__ __forceinline__ void mma_chunk(const uint16_t* lds, const AChunk (&a)
 }
 
 // Accumulate the tile over the chunks of k in [kbeg, kend) (at least one, all
-// inside A's rows), starting from the first chunk already loaded into ra, rb (so a caller can issue other loads after them:
-// the first wait then excludes those), the B planes staged through `lds`
-// (kLdsBytes); with SQ also this lane's float64 squares of A.  Later chunks
-// are loaded when they are due, not a chunk ahead: a prefetch register set
-// would cost the occupancy that hides those loads behind the other
-// workgroups' matrix work.  The caller's first use of lds afterwards must
-// follow a barrier.
-template <bool SQ, int RB, bool APART>
+// inside A's rows), starting from the first chunk already loaded into ra, rb (so
+// a caller can issue other loads after them: the first wait then excludes those),
+// the B planes staged through `lds` (kLdsBytes); with SQ also this lane's float64
+// squares of A.  Later chunks are loaded when they are due, not a chunk ahead: a
+// prefetch register set would cost the occupancy that hides those loads behind
+// the other workgroups' matrix work.  The caller's first use of lds afterwards
+// must follow a barrier.
+template <bool SQ, int RB, Sum SUM>
 __device__ __forceinline__ void tile_run(uint16_t* lds, const ARows<RB>& arows, const BRows& brows,
                                          int kbeg, int kend, AChunk (&ra)[RB], BChunk& rb, Acc (&acc)[RB],
                                          double (&sq)[RB]) {
@@ -242,7 +253,7 @@ __device__ __forceinline__ void tile_run(uint16_t* lds, const ARows<RB>& arows, 
 #pragma unroll
     for (int r = 0; r < RB; ++r) sq[r] += squares(ra[r]);
   }
-  mma_chunk<RB, APART>(lds, ra, acc);
+  mma_chunk<RB, SUM>(lds, ra, acc);
   for (int k0 = kbeg + KC; k0 < kend; k0 += KC) {
     load_b(brows, k0, rb);
     load_a<RB>(arows, k0, ra);
@@ -253,12 +264,12 @@ __device__ __forceinline__ void tile_run(uint16_t* lds, const ARows<RB>& arows, 
 #pragma unroll
       for (int r = 0; r < RB; ++r) sq[r] += squares(ra[r]);
     }
-    mma_chunk<RB, APART>(lds, ra, acc);
+    mma_chunk<RB, SUM>(lds, ra, acc);
   }
 }
 
 // The last, partial chunk at k0 of rows of len elements.
-template <bool SQ, int RB, bool APART>
+template <bool SQ, int RB, Sum SUM>
 __device__ __forceinline__ void tile_tail(uint16_t* lds, const ARows<RB>& arows, const BRows& brows, int k0,
                                           int len, Acc (&acc)[RB], double (&sq)[RB]) {
   AChunk ra[RB];
@@ -272,7 +283,7 @@ __device__ __forceinline__ void tile_tail(uint16_t* lds, const ARows<RB>& arows,
 #pragma unroll
     for (int r = 0; r < RB; ++r) sq[r] += squares(ra[r]);
   }
-  mma_chunk<RB, APART>(lds, ra, acc);
+  mma_chunk<RB, SUM>(lds, ra, acc);
 }
 
 // Row (inside the tile) of row block r's accumulators of this lane, and the

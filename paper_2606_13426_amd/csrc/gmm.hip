@@ -93,7 +93,7 @@ __device__ __forceinline__ float comp(const float4& v, int c) {
 // per lane need the registers).
 constexpr int kSplitRB = 2, kSplitRows = 64 * kSplitRB;
 
-template <bool RAGGED, bool APART>
+template <bool RAGGED, split::Sum SUM>
 __global__ __launch_bounds__(kThreads, 2) void gmm_logits_split_kernel(
     int R, int M, int Mp, int d, int dp, const float* __restrict__ X, int64_t ldx,
     const uint16_t* __restrict__ musplit, int ksplit, float* __restrict__ part,
@@ -123,13 +123,13 @@ __global__ __launch_bounds__(kThreads, 2) void gmm_logits_split_kernel(
     split::load_a<kSplitRB>(arows, kbeg, ra);
     if (gate && *gate == 0) return;
     if (want_sq)
-      split::tile_run<true, kSplitRB, APART>(lds, arows, brows, kbeg, kend, ra, rb, acc, sq);
+      split::tile_run<true, kSplitRB, SUM>(lds, arows, brows, kbeg, kend, ra, rb, acc, sq);
     else
-      split::tile_run<false, kSplitRB, APART>(lds, arows, brows, kbeg, kend, ra, rb, acc, sq);
+      split::tile_run<false, kSplitRB, SUM>(lds, arows, brows, kbeg, kend, ra, rb, acc, sq);
   } else if (gate && *gate == 0) {
     return;
   }
-  if (RAGGED && s == nsplit - 1) split::tile_tail<true, kSplitRB, APART>(lds, arows, brows, kend, d, acc, sq);
+  if (RAGGED && s == nsplit - 1) split::tile_tail<true, kSplitRB, SUM>(lds, arows, brows, kend, d, acc, sq);
   float* ps = part + (int64_t)s * R * Mp;
 #pragma unroll
   for (int r = 0; r < kSplitRB; ++r) {
@@ -305,7 +305,7 @@ __global__ __launch_bounds__(NW > 4 ? 64 * NW : kThreads) void gmm_softmax_kerne
 // instruction.  EM: the plain Euler-Maruyama step (EmStep), whose noise as a
 // kernel of its own was a fourth of a small step's launches and one more pass
 // over the rows (64 rows of 3072, a step: 16.7 -> 13.7 us, with the logits' splits).
-template <int EDGE, bool APART, bool EM>
+template <int EDGE, split::Sum SUM, bool EM>
 __global__ __launch_bounds__(kThreads) void gmm_mean_split_kernel(
     int R, int Mp, int Mk, int d, const float* __restrict__ P, const uint16_t* __restrict__ muTs,
     const float* __restrict__ X, int64_t ldx, const float* __restrict__ rowc,
@@ -331,7 +331,7 @@ __global__ __launch_bounds__(kThreads) void gmm_mean_split_kernel(
   split::Acc acc[1];
   split::zero(acc[0]);
   double unused[1] = {0.0};
-  split::tile_run<false, 1, APART>(lds, arows, brows, 0, Mp, sa, sb, acc, unused);
+  split::tile_run<false, 1, SUM>(lds, arows, brows, 0, Mp, sa, sb, acc, unused);
   if (row >= R) return;
   if (EM && blockIdx.y == 0 && split::out_col(0) == 0) em.step[row] = em.n + 1;
 #pragma unroll
@@ -369,7 +369,7 @@ __global__ __launch_bounds__(kThreads) void gmm_mean_split_kernel(
 // Columns past d read x, the cache and their products as zero and add nothing.  m^q is stored non-temporally: of a chain's
 // K + 1 rows the round reads back two (the residual's mean and the next cache
 // row).  Products on the bf16 matrix cores as in gmm_mean_split_kernel.
-template <int EDGE, bool APART>
+template <int EDGE, split::Sum SUM>
 __global__ __launch_bounds__(kThreads) void gmm_mean_lr_kernel(
     int R, int Mp, int Mk, int d, int K1, const float* __restrict__ P,
     const uint16_t* __restrict__ muTs, const float* __restrict__ X,
@@ -428,7 +428,7 @@ __global__ __launch_bounds__(kThreads) void gmm_mean_lr_kernel(
   split::Acc acc[1];
   split::zero(acc[0]);
   double unused[1] = {0.0};
-  split::tile_run<false, 1, APART>(reinterpret_cast<uint16_t*>(sm), arows, brows, 0, Mp, sa, sb, acc, unused);
+  split::tile_run<false, 1, SUM>(reinterpret_cast<uint16_t*>(sm), arows, brows, 0, Mp, sa, sb, acc, unused);
   __syncthreads();  // every wavefront is done with the operand planes
 #pragma unroll
   for (int b = 0; b < 4; ++b)
@@ -587,9 +587,9 @@ Plan make_plan(const Target& t, int R, int plan_rows = 0, bool measure = false) 
 
 hipError_t logits_launch(const Target& t, const Plan& p, int R, const float* x, int64_t ldx,
                          float* part, double* xsq, hipStream_t s, const int* gate) {
-  return launch_timed("gmm_logits", t.d % KC      ? gmm_logits_split_kernel<true, true>
-                                    : t.M % TILE ? gmm_logits_split_kernel<false, true>
-                                                 : gmm_logits_split_kernel<false, false>,
+  return launch_timed("gmm_logits", t.d % KC      ? gmm_logits_split_kernel<true, split::APART>
+                                    : t.M % TILE ? gmm_logits_split_kernel<false, split::APART>
+                                                 : gmm_logits_split_kernel<false, split::CHAIN>,
                       dim3(p.S, (R + kSplitRows - 1) / kSplitRows, t.Mp / TILE), dim3(kThreads), s, R, t.M, t.Mp,
                       t.d, t.dp, x, ldx, t.mu_split, p.ksplit, part, xsq, gate);
 }
@@ -669,10 +669,10 @@ hipError_t target_mean_launch(const Target& t, int R, const float* x, int64_t ld
   auto go = [&](auto noise) {
     constexpr bool EM = decltype(noise)::value;
     return launch_timed(EM ? "em_step" : "gmm_mean",
-                        edge == 2    ? gmm_mean_split_kernel<2, true, EM>
-                        : edge == 1  ? gmm_mean_split_kernel<1, true, EM>
-                        : t.M % TILE ? gmm_mean_split_kernel<0, true, EM>
-                                     : gmm_mean_split_kernel<0, false, EM>,
+                        edge == 2    ? gmm_mean_split_kernel<2, split::APART_ALL, EM>
+                        : edge == 1  ? gmm_mean_split_kernel<1, split::APART_ALL, EM>
+                        : t.M % TILE ? gmm_mean_split_kernel<0, split::APART_ALL, EM>
+                                     : gmm_mean_split_kernel<0, split::CHAIN, EM>,
                         g2, dim3(kThreads), s, R, t.Mp, t.Mk, t.d, P, t.muT_split, x, ldx, rowc, mq, ldq, score,
                         lds, gate, em ? *em : EmStep{});
   };
@@ -700,10 +700,11 @@ hipError_t target_mean_lr_launch(const Target& t, int R, int K1, const float* x,
   dim3 g2((t.d + TILE - 1) / TILE, (R + TILE - 1) / TILE);
   const int edge = edge_of(t.d);
   return launch_timed("gmm_mean_lr",
-                      edge == 2   ? gmm_mean_lr_kernel<2, true>
-                      : edge == 1 ? gmm_mean_lr_kernel<1, true>
-                      : t.M % TILE || K1 < 4 ? gmm_mean_lr_kernel<0, true>
-                                  : gmm_mean_lr_kernel<0, false>, g2, dim3(kThreads), s, R, t.Mp, t.Mk, t.d, K1, P,
+                      edge == 2   ? gmm_mean_lr_kernel<2, split::APART_ALL>
+                      : edge == 1 ? gmm_mean_lr_kernel<1, split::APART_ALL>
+                      : t.M % TILE ? gmm_mean_lr_kernel<0, split::APART_ALL>
+                                   : gmm_mean_lr_kernel<0, split::CHAIN>,
+                      g2, dim3(kThreads), s, R, t.Mp, t.Mk, t.d, K1, P,
                       t.muT_split, x, rowc, sv, cstep, t.coef, mq, lrp, rnd, seed, gate, chain0);
 }
 

@@ -66,6 +66,30 @@ def test_target_of_any_shape(d, M, rows, offset, pad):
             assert bool((t.as_strided((rows - 1, pad), (d + pad, 1), t.storage_offset() + d) == -7.0).all())
 
 
+@pytest.mark.parametrize("d,M", [(448, 1), (1001, 1), (3, 1), (64, 3), (784, 100)])
+def test_single_products_are_rounded_once(d, M):
+    # One component far above the others has all the weight, and at x = 0 the score
+    # is then P mu, one product an element: float32 arithmetic rounds it once, by
+    # 2^-24 at most (5 % more covers the rounding of the split's small terms; the
+    # terms that the short form leaves out are 2^-23)
+    N, rows = 40, 70
+    p = make_gmm(d, M, mu_std=1.0, var=(0.05, 0.4), dirichlet=1.0, seed=d)
+    log_w = np.full(M, -2000.0, np.float32)
+    log_w[0] = 0.0
+    mu = np.array(p["mu"], np.float32)
+    mu[1:] = 30.0 * mu[1:]
+    sched = _lib.schedule(N)
+    tgt = _lib.Target(sched, mu, p["var"], log_w)
+    step = torch.arange(rows, device=DEV, dtype=torch.int32) % N
+    x = torch.zeros(rows, d, device=DEV)
+    mq, sc = torch.empty_like(x), torch.empty_like(x)
+    _lib.sd_target_mean(tgt, x, step, mq, sc)
+    a = _lib.sd_schedule_table(sched)[0][:N]
+    weight = (a * (1.0 / (a * a * float(np.float32(p["var"][0])) + 1.0 - a * a))).astype(np.float32)
+    want = torch.from_numpy(weight.astype(np.float64)[step.cpu().numpy(), None] * mu[0].astype(np.float64)).to(DEV)
+    assert float(((sc.double() - want).abs() / want.abs()).max()) <= 1.05 * 2.0 ** -24
+
+
 @pytest.mark.parametrize("d,M,K", [(1, 2, 1), (3, 5, 2), (66, 70, 1), (65, 3, 2), (130, 64, 3), (67, 9, 7)])
 def test_sampler_of_any_shape(d, M, K):
     # chains of 2, 3 and 4 rows meet a thread's four rows at every offset
