@@ -33,7 +33,8 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 FP32_PEAK_TFLOPS = 157.3
 BF16_PEAK_TFLOPS = 2500.0   # dense bf16 MFMA
-GEMMS = ("gmm_logits", "gmm_mean", "gmm_mean_lr", "gmm_logits_bf16", "gmm_mean_bf16", "gmm_mean_lr_bf16")
+GEMMS = ("gmm_logits", "gmm_mean", "gmm_mean_lr", "gmm_logits_bf16", "gmm_mean_bf16", "gmm_mean_bf16_big",
+         "gmm_mean_lr_bf16")
 METRIC = "verified chain-steps/sec + mean accepted steps per block; % MFMA / HBM peak"
 
 # HBM bytes per launch of a workload's dominant kernel from two rocprofv3 passes
@@ -119,7 +120,7 @@ def algorithmic_work(name, B, K, d, M, act, rows_verified, runs, nct=1):
     """
     rounds = len(act)
     R = B * (K + 1)
-    bf = name.endswith("_bf16")
+    bf = "_bf16" in name
     eb = 2 if bf else 4
     if name in ("gmm_logits", "gmm_logits_bf16"):
         rows = R * rounds + B
@@ -128,7 +129,7 @@ def algorithmic_work(name, B, K, d, M, act, rows_verified, runs, nct=1):
         rows = R * rounds
         return (2.0 * rows * M * d * runs,
                 (rows * d * 8 + B * rounds * d * 4 + rounds * M * d * eb) * runs, eb)
-    if name in ("gmm_mean", "gmm_mean_bf16"):
+    if name in ("gmm_mean", "gmm_mean_bf16", "gmm_mean_bf16_big"):
         return 2.0 * B * M * d * runs, (B * d * 8 + M * d * eb) * runs, eb
     if name == "gmm_softmax":
         rows = R * rounds + B

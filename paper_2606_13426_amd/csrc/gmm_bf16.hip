@@ -797,11 +797,16 @@ inline bool big_mean_ok(const Target& t, int K1, bool vecd) {
          (int64_t)bf16b::TR * t.M * 2 < ((int64_t)1 << 31);
 }
 
-// Whether a public call of R rows runs on these tiles: where the sampler's rule
+// Whether a target call planned for R rows runs on these tiles: where the sampler's rule
 // allows them, one workgroup per compute unit at a time loses to the 128 x 128
 // kernel only through tiles that are not full and a last wave that is not: at
 // three quarters of both together they meet (70 / 0.75 against 96 us of
-// contraction).
+// contraction; both measured at 2304 x 16384 x 1024 only).
+// R: the plan's rows, not the call's, so that a part of a batch takes the whole's
+// kernel: the two go over k in different instructions, whose sums had the same bits
+// in every case compared, which nothing promises (Frozen Drafter in two groups of
+// 432 and 900 states: 498 / 497 and 529 / 531 us a round by the call's rows / by the
+// plan's).
 inline bool big_public_ok(const Target& t, int R, int64_t ld) {
   const int64_t tiles = (int64_t)((R + bf16b::TR - 1) / bf16b::TR) * (t.d / MeanTile::TC);
   const int64_t waves = (tiles + 255) / 256;
@@ -916,10 +921,10 @@ hipError_t target_mean_bf16_launch(const Target& t, int R, const float* x, int64
   const bool vecq = (ldq % 4 == 0) && aligned16(mq);
   const bool vecs = score && (lds % 4 == 0) && aligned16(score);
   const int64_t ldmax = std::max(ldx, std::max(ldq, score ? lds : (int64_t)0));
-  if (vecx && vecq && (vecs || !score) && big_public_ok(t, R, ldmax)) {
+  if (vecx && vecq && (vecs || !score) && big_public_ok(t, p.rows, ldmax)) {
     auto big = [&](auto noise) {
       constexpr bool EM = decltype(noise)::value;
-      return launch_timed(EM ? "em_step_bf16" : "gmm_mean_bf16", gmm_mean_bf16_big_kernel<MeanTile, EM>,
+      return launch_timed(EM ? "em_step_bf16_big" : "gmm_mean_bf16_big", gmm_mean_bf16_big_kernel<MeanTile, EM>,
                           dim3(((R + bf16b::TR - 1) / bf16b::TR) * (t.d / MeanTile::TC)), dim3(MeanTile::kThreads),
                           s, R, t.M, t.d, w.P, t.muT16, x, (int)ldx, w.rowc, mq, (int)ldq, score, (int)lds,
                           stream_rows((int64_t)R * t.d * (score ? 8 : 4)), gate, em ? *em : EmStep{});

@@ -70,6 +70,35 @@ def test_two_groups_equal_one(case):
     _same(one, two)
 
 
+def _seen(*names):
+    return [_lib.sd_profile_seen(n) for n in names]
+
+
+def test_frozen_call_on_half_the_states_takes_the_kernel_of_all():
+    # the Frozen Drafter's call on all 864 states takes the 288-row tiles of a public
+    # call; 432 alone would take the 128-row ones, but half of a batch is summed as the
+    # whole is.  (The components overlap, so that a row's weights spread over many.)
+    d, M, B, K, N = 16384, 512, 864, 2, 12
+    p = make_gmm(d, M, mu_std=0.01, var=(0.2, 0.2), dirichlet=1.0, seed=d + M)
+    tgt = _lib.Target(_lib.schedule(N), p["mu"], p["var"], p["log_w"], precision=_lib.SD_BF16)
+    runs, seen = [], []
+    for groups in (1, 2):
+        _lib.sd_profile_enable(True)
+        runs.append(_lib.sd_run_sampler_ex(tgt, B, K, 11, trace_rounds=N, groups=groups, **FROZEN))
+        torch.cuda.synchronize()
+        seen.append(_seen("gmm_mean_bf16_big", "gmm_mean_bf16"))
+        _lib.sd_profile_enable(False)
+        assert runs[-1][1]["groups"] == groups
+    assert seen[0][0] > 0 and seen[1][0] == 2 * seen[0][0] and seen[0][1] == seen[1][1] == 0
+    _same(*runs)
+    # and alone
+    x, step = torch.randn(B // 2, d, device="cuda"), torch.zeros(B // 2, dtype=torch.int32, device="cuda")
+    _lib.sd_profile_enable(True)
+    _lib.sd_target_mean(tgt, x, step, torch.empty_like(x))
+    assert _seen("gmm_mean_bf16_big", "gmm_mean_bf16") == [0, 1]
+    _lib.sd_profile_enable(False)
+
+
 def test_split_run_changing_groups_equals_one_call():
     tgt, B, K, N, kw = _target(((1024, 512), 72, 8, 60, _lib.SD_BF16, {}))
     one = _lib.sd_run_sampler_ex(tgt, B, K, 5, trace_rounds=N, groups=1)

@@ -71,8 +71,19 @@ def test_logits_over_many_splits(d, M, rows):
 
 
 def _bf16_target(d, M, N):
-    p = make_gmm(d, M, mu_std=1.0, var=(0.05, 0.4), dirichlet=1.0, seed=M)
+    # components that overlap: a row's weights spread over many of them (apart, one
+    # has all the weight and the order of the sums could not show)
+    p = make_gmm(d, M, mu_std=0.01, var=(0.2, 0.2), dirichlet=1.0, seed=M)
     return _lib.Target(_lib.schedule(N), p["mu"], p["var"], p["log_w"], _lib.SD_BF16)
+
+
+def _launches(call, *names):
+    """The launches of the kernels `names` during call(), and its result."""
+    _lib.sd_profile_enable(True)
+    out = call()
+    n = [_lib.sd_profile_seen(k) for k in names]
+    _lib.sd_profile_enable(False)
+    return n, out
 
 
 # 864 = 3 tiles of 288 rows (192 of 256 workgroups: the least that takes them),
@@ -94,10 +105,23 @@ def test_public_mean_tiles_agree(d, M, rows, pad):
         assert extra == 0 or bool((mq[:, d:] == -7.0).all()) and bool((sc[:, d:] == -7.0).all())
         return mq[:, :d], sc[:, :d]
 
-    big, small = call(pad, True), call(1, True)
+    kernels = ("gmm_mean_bf16_big", "gmm_mean_bf16")
+    n, big = _launches(lambda: call(pad, True), *kernels)
+    assert n == [1, 0]
+    n, small = _launches(lambda: call(1, True), *kernels)
+    assert n == [0, 1]
     for a, b in zip(big, small):
         assert float(((a - b).abs() / b.abs().amax(1, keepdim=True)).max()) <= 2.0 ** -19
     assert torch.equal(call(pad, False)[0], big[0])
+
+
+def test_public_mean_tiles_begin_at_three_quarters_of_a_wave():
+    tgt = _bf16_target(16384, 512, 10)
+    for rows, want in ((863, [0, 1]), (864, [1, 0])):
+        x = torch.zeros(rows, 16384, device=DEV)
+        step = torch.zeros(rows, dtype=torch.int32, device=DEV)
+        n, _ = _launches(lambda: _lib.sd_target_mean(tgt, x, step, torch.empty_like(x)), "gmm_mean_bf16_big", "gmm_mean_bf16")
+        assert n == want, rows
 
 
 # (3, 1) the float32 kernels, bf16 on 128 x 128 tiles, and on 288 x 256 ones
