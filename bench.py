@@ -103,6 +103,12 @@ def _counts_from_trace(trace, N, K):
     return np.array(act), np.array(rows_verified), np.array(rows_target)
 
 
+def target_us(prof):
+    """us of a profile's target calls: logits, softmax and mean kernels, the mean of a plain Euler-Maruyama step
+    (em_step, which adds the step's noise) among them."""
+    return 1e3 * sum(v[1] for k, v in prof.items() if k.startswith(("gmm_", "em_step")))
+
+
 def algorithmic_work(name, B, K, d, M, act, rows_verified, runs, nct=1):
     """(flops, bytes, dtype bytes) of a kernel's algorithmic work over `runs` sampler runs.
 
@@ -367,7 +373,7 @@ def variants_bench(lib, name, steps):
     em_sec, _ = timed_runs(lambda: lib.sd_run_plain_em(tgt, B, seed, y_out=y, ws=em_ws), reps)
     em_prof = profiled(lambda: lib.sd_run_plain_em(tgt, B, seed, y_out=y, ws=em_ws))
     # speedup terms, per round of the block sampler (Free and Frozen) and per EM step
-    tq1 = 1e3 * sum(v[1] for k, v in em_prof.items() if k.startswith("gmm_")) / N   # us per target call on B rows
+    tq1 = target_us(em_prof) / N   # us per target call on B rows (with a plain step's noise, which its last kernel adds)
     # (one chain group: a round's kernels then run one after another, so
     # their event times add up to the round)
     free_prof = profiled(sampler(lib.SD_BLOCK, lib.SD_RESIDUAL_DECOMPOSITION, lib.SD_DRAFTER_FREE, 1.0, groups=1))
@@ -385,10 +391,10 @@ def variants_bench(lib, name, steps):
         rounds = prof["scan_fused"][0]
         per = lambda names: 1e3 * sum(prof[k][1] for k in names if k in prof) / rounds
         round_us = per(list(prof))
-        return dict(target_us=per([k for k in prof if k.startswith("gmm_")]),
+        return dict(target_us=target_us(prof) / rounds,
                     verify_residual_commit_us=per(["scan_fused", "advance"]),
                     draft_kernel_us=per(["draft_block"]),
-                    round_us=round_us, target_over_time_q1=per([k for k in prof if k.startswith("gmm_")]) / tq1,
+                    round_us=round_us, target_over_time_q1=target_us(prof) / rounds / tq1,
                     predicted_speedup=be * tq1 / round_us)
 
     # the latency-bound regime the paper's speedup assumes (a target call on a
