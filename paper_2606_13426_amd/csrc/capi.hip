@@ -147,6 +147,9 @@ hipError_t scratch_address(void** out) {
 
 static inline size_t a256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// Bytes of mu that a target's creation moves at a time.
+constexpr size_t kUploadBytes = (size_t)8 << 20;
+
 static bool sched_ok(const sd_schedule* s) {
   return s && s->n_steps >= 1 && s->beta_min > 0.0 && s->beta_max >= s->beta_min &&
          s->churn > 0.0 && isfinite(s->beta_max) && isfinite(s->churn);
@@ -225,10 +228,14 @@ sd_status sd_target_create(const sd_schedule* sched, int32_t d, int32_t n_comp, 
   t->Mk = (n_comp + 7) / 8 * 8;
   const size_t planes = bf ? 1 : 3, na = planes * M * (size_t)t->dp, nt = planes * D * (size_t)t->Mk;
   uint16_t *&opa = bf ? t->mu16 : t->mu_split, *&opt = bf ? t->muT16 : t->muT_split;
-  bool ok = hipMalloc(&t->mu, sizeof(float) * M * D) == hipSuccess &&
-            hipMalloc(&opa, sizeof(uint16_t) * (na + kOperandSlack)) == hipSuccess &&
+  // mu passes through the tables' allocation before they are written, a slice of
+  // whole 32-component blocks at a time: no float32 copy is held, and nothing is
+  // freed (hipFree would wait for every stream of the device).
+  const size_t row_bytes = sizeof(float) * D,
+               slice = M * row_bytes <= kUploadBytes ? M : std::max<size_t>(32, kUploadBytes / row_bytes / 32 * 32);
+  bool ok = hipMalloc(&opa, sizeof(uint16_t) * (na + kOperandSlack)) == hipSuccess &&
             hipMalloc(&opt, sizeof(uint16_t) * (nt + kOperandSlack)) == hipSuccess &&
-            hipMalloc(&t->tables, table_bytes) == hipSuccess;
+            hipMalloc(&t->tables, std::max(table_bytes, std::min(slice, M) * row_bytes)) == hipSuccess;
   if (!ok) {
     set_error("sd_target_create: device allocation failed");
     sd_target_destroy(reinterpret_cast<sd_target>(t));
@@ -263,10 +270,14 @@ sd_status sd_target_create(const sd_schedule* sched, int32_t d, int32_t n_comp, 
     return SD_EHIP;
   }
   // the operand planes are made on the device (rounding, split and transpose)
-  ok = hipMemcpy(t->mu, mu, sizeof(float) * M * D, hipMemcpyHostToDevice) == hipSuccess &&
-       fill_i32_launch(reinterpret_cast<int32_t*>(opa + na), kOperandSlack / 2, 0, nullptr) == hipSuccess &&
-       fill_i32_launch(reinterpret_cast<int32_t*>(opt + nt), kOperandSlack / 2, 0, nullptr) == hipSuccess &&
-       operands_launch(*t, (int)planes, t->mu, opa, opt, nullptr) == hipSuccess;
+  ok = fill_i32_launch(reinterpret_cast<int32_t*>(opa + na), kOperandSlack / 2, 0, nullptr) == hipSuccess &&
+       fill_i32_launch(reinterpret_cast<int32_t*>(opt + nt), kOperandSlack / 2, 0, nullptr) == hipSuccess;
+  for (size_t m = 0; ok && m < M; m += slice) {
+    const size_t n = std::min(slice, M - m);
+    ok = hipMemcpy(t->tables, mu + m * D, n * row_bytes, hipMemcpyHostToDevice) == hipSuccess &&
+         operands_launch(*t, (int)planes, static_cast<const float*>(t->tables), (int)m, (int)n, opa, opt, nullptr) ==
+             hipSuccess;
+  }
   std::vector<char> tables(table_bytes);
   auto host_at = [&](size_t o) { return tables.data() + o; };
   double2* ls = reinterpret_cast<double2*>(host_at(o_ls));
@@ -287,10 +298,6 @@ sd_status sd_target_create(const sd_schedule* sched, int32_t d, int32_t n_comp, 
   }
   ok = ok && hipMemcpy(t->tables, tables.data(), table_bytes, hipMemcpyHostToDevice) == hipSuccess &&
        hipStreamSynchronize(nullptr) == hipSuccess;
-  if (bf) {
-    (void)hipFree(t->mu);
-    t->mu = nullptr;
-  }
   if (!ok) {
     set_error("sd_target_create: copy to device failed");
     sd_target_destroy(reinterpret_cast<sd_target>(t));
@@ -303,7 +310,6 @@ sd_status sd_target_create(const sd_schedule* sched, int32_t d, int32_t n_comp, 
 sd_status sd_target_destroy(sd_target target) {
   if (!target) return SD_OK;
   Target* t = reinterpret_cast<Target*>(target);
-  if (t->mu) (void)hipFree(t->mu);
   if (t->mu_split) (void)hipFree(t->mu_split);
   if (t->muT_split) (void)hipFree(t->muT_split);
   if (t->mu16) (void)hipFree(t->mu16);

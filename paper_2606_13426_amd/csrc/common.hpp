@@ -95,7 +95,6 @@ struct Target {
   // 16-byte addresses; kOperandSlack elements follow the last plane, for the
   // chunk that crosses the last row's end).
   int Mp, dp, Mk;
-  float* mu;      // [M][d], float32 precision only
   uint16_t* mu16;   // [M][dp] bf16 (round to nearest even), bf16 precision only
   uint16_t* muT16;  // [d][Mk] bf16, bf16 precision only
   // float32 precision: the exact three-term bf16 splits of mu and mu^T
@@ -134,9 +133,11 @@ constexpr int kStatNan = SD_MAX_BLOCK + 4, kStatGate = kStatNan + 1, kStatTag = 
 static_assert(kStatTag < kStatWords, "the words hold every total and the tag");
 static_assert(sizeof(Target::side) / sizeof(hipStream_t) == kFlagGroups, "one side stream per flag group");
 
-// The bf16 operand planes of the device array mu [M][d] (3: the exact split, 1:
-// rounded), A [planes][M][dp] and T [planes][d][Mk].
-hipError_t operands_launch(const Target& t, int planes, const float* mu, uint16_t* A, uint16_t* T, hipStream_t s);
+// The bf16 operand planes (3: the exact split, 1: rounded), A [planes][M][dp] and
+// T [planes][d][Mk], of components m0 .. m0 + n - 1 (m0 a multiple of 32, n too
+// unless they end with the last one), whose means are the device array mu [n][d].
+hipError_t operands_launch(const Target& t, int planes, const float* mu, int m0, int n, uint16_t* A, uint16_t* T,
+                           hipStream_t s);
 
 // Workspace of a target call on `rows` rows whose logits GEMM is split over d
 // as for plan_rows rows (0: rows).  The split fixes the order in which the

@@ -496,33 +496,35 @@ __global__ __launch_bounds__(kThreads) void gmm_mean_lr_kernel(
   }
 }
 
-// The bf16 operand planes of mu [M][d]: NP = 3 the exact split, NP = 1 its
-// rounding.  A [NP][M][dp] as it is, T [NP][d][Mk] transposed through LDS;
-// both zero in the padding of their rows.
+// The bf16 operand planes of components mb .. me - 1, mu [me - mb][d]: NP = 3 the
+// exact split, NP = 1 its rounding.  A [NP][M][dp] as it is, T [NP][d][Mk]
+// transposed through LDS; both zero in the padding of their rows (T's is written
+// with the last component's).
 template <int NP>
-__global__ __launch_bounds__(kThreads) void operands_kernel(int M, int Mk, int d, int dp,
+__global__ __launch_bounds__(kThreads) void operands_kernel(int M, int Mk, int d, int dp, int mb, int me,
                                                             const float* __restrict__ mu,
                                                             uint16_t* __restrict__ A, uint16_t* __restrict__ T) {
   __shared__ uint16_t tile[NP][32][34];
-  const int i0 = blockIdx.x * 32, m0 = blockIdx.y * 32, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  const int i0 = blockIdx.x * 32, m0 = mb + blockIdx.y * 32, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
 #pragma unroll
   for (int h = 0; h < 4; ++h) {
     const int m = m0 + ty + 8 * h, i = i0 + tx;
-    float v = m < M && i < d ? mu[(int64_t)m * d + i] : 0.0f;
+    float v = m < me && i < d ? mu[(int64_t)(m - mb) * d + i] : 0.0f;
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
       const __bf16 b = (__bf16)v;
       v -= (float)b;
       const uint16_t u = __builtin_bit_cast(uint16_t, b);
       tile[p][ty + 8 * h][tx] = u;
-      if (m < M && i < dp) A[((int64_t)p * M + m) * dp + i] = u;
+      if (m < me && i < dp) A[((int64_t)p * M + m) * dp + i] = u;
     }
   }
   __syncthreads();
+  const int mt = me == M ? Mk : me;
 #pragma unroll
   for (int h = 0; h < 4; ++h) {
     const int i = i0 + ty + 8 * h, m = m0 + tx;
-    if (i < d && m < Mk)
+    if (i < d && m < mt)
 #pragma unroll
       for (int p = 0; p < NP; ++p) T[((int64_t)p * d + i) * Mk + m] = tile[p][tx][ty + 8 * h];
   }
@@ -596,12 +598,12 @@ hipError_t logits_launch(const Target& t, const Plan& p, int R, const float* x, 
 
 }  // namespace
 
-hipError_t operands_launch(const Target& t, int planes, const float* mu, uint16_t* A, uint16_t* T, hipStream_t s) {
-  const dim3 grid((t.dp + 31) / 32, (t.Mk + 31) / 32);
-  if (planes == 3)
-    operands_kernel<3><<<grid, kThreads, 0, s>>>(t.M, t.Mk, t.d, t.dp, mu, A, T);
-  else
-    operands_kernel<1><<<grid, kThreads, 0, s>>>(t.M, t.Mk, t.d, t.dp, mu, A, T);
+hipError_t operands_launch(const Target& t, int planes, const float* mu, int m0, int n, uint16_t* A, uint16_t* T,
+                           hipStream_t s) {
+  const int m1 = m0 + n;
+  const dim3 grid((t.dp + 31) / 32, ((m1 == t.M ? t.Mk : m1) - m0 + 31) / 32);
+  (planes == 3 ? operands_kernel<3> : operands_kernel<1>)<<<grid, kThreads, 0, s>>>(t.M, t.Mk, t.d, t.dp, m0, m1, mu,
+                                                                                    A, T);
   return hipGetLastError();
 }
 
