@@ -148,11 +148,45 @@ def test_plain_step_is_mean_plus_noise(d, M, B, bf16, N):
     assert float((got - y).abs().max()) <= 2.0 ** -19 * float(y.abs().max())
 
 
+def _state(tgt, B, K, rounds, groups):
+    """A slice's statistics, trace and the state it leaves; its workspace, to go on from."""
+    ws = torch.zeros(_lib.sd_sampler_workspace(tgt, B, K), dtype=torch.uint8, device=DEV)
+    trace = torch.zeros(40, B, dtype=torch.int32, device=DEV)
+    _, st, _ = _lib.sd_run_sampler_ex(tgt, B, K, 0, max_rounds=rounds, groups=groups, ws=ws, trace=trace)
+    v = _lib.sd_sampler_state(tgt, B, K, ws, st["rounds"])
+    keep = ("x", "k", "round", "cache", "cache_step", "mq", "lrp", "tau", "coins", "log_alpha_res", "ties")
+    return st, trace, {k: v[k].clone() for k in keep}, ws
+
+
 def test_slices_choose_one_group():
     # the choice by rows holds for calls that run many rounds; a slice of few
     # takes one group, with the same state as any grouping
     p = make_gmm(64, 8, mu_std=1.0, var=(0.01, 0.2), dirichlet=1.0, seed=1)
     tgt = _lib.Target(_lib.schedule(40), p["mu"], p["var"], p["log_w"])
-    for rounds, want in ((4, 1), (31, 1), (32, 2), (-1, 2)):
-        _, st, _ = _lib.sd_run_sampler_ex(tgt, 456, 8, 0, max_rounds=rounds)
+    B, K = 456, 8
+    y, whole, trace = _lib.sd_run_sampler_ex(tgt, B, K, 0, trace_rounds=40)
+    assert whole["groups"] == 2 and whole["finished"]
+    for rounds, want in ((4, 1), (31, 1), (32, 2)):
+        st, tr, state, ws = _state(tgt, B, K, rounds, 0)
         assert st["groups"] == want, (rounds, st["groups"])
+        for groups in (1, 2):
+            st2, tr2, state2, _ = _state(tgt, B, K, rounds, groups)
+            assert st2["groups"] == groups and torch.equal(tr, tr2)
+            for k in state:
+                assert torch.equal(state[k], state2[k]), (rounds, groups, k)
+        # the run continued from the slice equals the whole call
+        y2, st, _ = _lib.sd_run_sampler_ex(tgt, B, K, 0, start_round=st["rounds"], ws=ws, trace=tr)
+        assert torch.equal(y, y2) and torch.equal(trace, tr)
+        assert all(st[k] == whole[k] for k in ("rounds", "steps", "ties", "tau_hist"))
+
+
+# 456 blocks of 9 rows: the largest d within 256 MB, and one more
+@pytest.mark.parametrize("d,want", [(16352, 1), (16353, 2)])
+def test_slices_of_blocks_past_the_infinity_cache_keep_two_groups(d, want):
+    p = make_gmm(d, 3, mu_std=1.0, var=(0.01, 0.2), dirichlet=1.0, seed=1)
+    tgt = _lib.Target(_lib.schedule(40), p["mu"], p["var"], p["log_w"])
+    st, tr, state, ws = _state(tgt, 456, 8, 2, 0)
+    assert st["groups"] == want and (456 * 9 * 4 * d > 256 << 20) == (want == 2)
+    del ws
+    _, tr2, state2, ws = _state(tgt, 456, 8, 2, 3 - want)
+    assert torch.equal(tr, tr2) and all(torch.equal(state[k], state2[k]) for k in state)
