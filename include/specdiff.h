@@ -318,7 +318,7 @@ sd_status sd_run_sampler(sd_target target, int32_t B, int32_t K, sd_verify_mode 
  *                       into `stream` before the call returns); 0: the
  *                       library chooses (two when each half has at least
  *                       2048 target rows, B/2 (K+1), but one for a call of
- *                       0 <= max_rounds < 32 whose drafts, B (K+1) d float32,
+ *                       0 <= max_rounds < 8 whose drafts, B (K+1) d float32,
  *                       take at most 256 MB).  The results do not depend on
  *                       it:
  *                       every row is computed in the same order either way,

@@ -513,16 +513,25 @@ inline int group_chains(int B, int groups, int g) {
 // two, ms per run): pixel3072 30.6 / 29.0, pixel12288 232 / 222, latent16384
 // 249 / 255 -- its 2304 rows make a logits grid of 252 one-per-CU workgroups,
 // and two halves need 280, a second wave.
-// A call that runs a slice of the rounds takes one group unless the draft block
-// exceeds the infinity cache: the second stream's fork and join cost a call about
-// 40 us, and two groups save 2 us a round at 1024 x 3072 (199 rounds 27.63 / 27.29
-// ms, 4 rounds 647 / 686 us), 10 to 28 where a block passes 256 MB (4 rounds of
-// 512 x 16384 2567 / 2495 us, of 512 x 17 x 12288 1998 / 1975).
+// A call of fewer than 8 rounds takes one group while the draft block fits the
+// infinity cache: the second stream's fork and join cost a call about 40 us, and
+// what two groups save a round differs.  Microseconds of one group / two, calls of
+// 4, 8 and 24 rounds:
+//   1024 chains x 9 x 784     (28 MB)   396 / 447    715 / 713   1938 / 1829
+//   2048 x 5 x 784, M = 100   (31 MB)   539 / 561    988 / 944   2752 / 2498
+//   256 x 17 x 3072           (51 MB)   413 / 474    741 / 795   2047 / 2023
+//   512 x 9 x 3072            (54 MB)   441 / 488    790 / 826   2186 / 2064
+//   1024 x 9 x 3072          (108 MB)   672 / 725   1231 / 1269  3453 / 3427
+//   256 x 16 x 12288, bf16   (192 MB)  1155 / 1184  2126 / 2094  5976 / 5708
+//   256 x 20 x 12288, bf16   (240 MB)  1326 / 1356  2479 / 2406  7011 / 6634
+//   480 x 9 x 16384, bf16    (270 MB)  1588 / 1586  2931 / 2810  8264 / 7685
+// From 8 rounds on the choice is the whole run's: it loses up to 7 % of a call there
+// (256 x 17 x 3072), one group up to 10 % of a longer one (2048 x 5 x 784).
 inline int choose_groups(int B, int K, int d, int requested, int max_rounds) {
   if (B < 2) return 1;
   if (requested == 1 || requested == 2) return requested;
   constexpr int64_t kCacheBytes = (int64_t)256 << 20;
-  if (max_rounds >= 0 && max_rounds < 32 && (int64_t)B * (K + 1) * d * 4 <= kCacheBytes) return 1;
+  if (max_rounds >= 0 && max_rounds < 8 && (int64_t)B * (K + 1) * d * 4 <= kCacheBytes) return 1;
   return (int64_t)(B / 2) * (K + 1) >= 2048 ? 2 : 1;
 }
 

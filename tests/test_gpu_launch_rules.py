@@ -166,7 +166,7 @@ def test_slices_choose_one_group():
     B, K = 456, 8
     y, whole, trace = _lib.sd_run_sampler_ex(tgt, B, K, 0, trace_rounds=40)
     assert whole["groups"] == 2 and whole["finished"]
-    for rounds, want in ((4, 1), (31, 1), (32, 2)):
+    for rounds, want in ((4, 1), (7, 1), (8, 2), (32, 2)):
         st, tr, state, ws = _state(tgt, B, K, rounds, 0)
         assert st["groups"] == want, (rounds, st["groups"])
         for groups in (1, 2):
