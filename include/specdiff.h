@@ -104,16 +104,15 @@ sd_status sd_schedule_table(const sd_schedule* sched, double* host_out);
  * mean m^q_n(x) = c1_n x + c2_n score (eq. target-distribution).
  * mu [M][d], var [M], log_w [M] are HOST arrays copied at creation.
  * d >= 1, 1 <= n_comp <= 1024.  precision selects the GEMM operand type:
- * SD_FP32 multiplies float32 operands to float32 accuracy (on the aligned
- * path as six bf16 products of exact three-term bf16 splits of each operand,
- * whose dropped terms are below 2^-23 of |a b|, accumulated in float32;
- * elsewhere with float32 matrix instructions); SD_BF16 stores mu as bf16 (round to
- * nearest even) and rounds x and the softmax weights to bf16 before the two
- * products, accumulating in float32 (||x||^2, ||mu||^2 and the softmax stay
- * float64 from the float32 values, ||x||^2 on the widest logits tiles as a
+ * SD_FP32 multiplies float32 operands to float32 accuracy (as six bf16 products
+ * of exact three-term bf16 splits of each operand, eight in the second product
+ * where d or n_comp is no multiple of 64; the dropped terms are below 2^-23,
+ * with eight 2^-32, of |a b|), accumulated in float32; SD_BF16 stores mu as bf16
+ * (round to nearest even) and rounds x and the softmax weights to bf16 before
+ * the two products, accumulating in float32 (||x||^2, ||mu||^2 and the softmax
+ * stay float64 from the float32 values, ||x||^2 on the widest logits tiles as a
  * float64 sum of float32 partials of four squares; the epilogue is float32).
- * Only the copies
- * of the chosen precision are allocated. */
+ * Only the copies of the chosen precision are allocated. */
 sd_status sd_target_create(const sd_schedule* sched, int32_t d, int32_t n_comp,
                            const float* mu, const float* var, const float* log_w,
                            sd_precision precision, sd_target* out);
@@ -135,10 +134,14 @@ sd_status sd_target_mean(sd_target target, int32_t rows, const float* x, int64_t
  * 128 MiB array of device memory that the library holds on every GPU it runs
  * on until the process ends (sd_target_mean_noalloc_max_bytes).  The call
  * allocates nothing (its first use on a GPU without a target created there
- * only looks up that GPU's copy).  Rows whose workspace
- * (sd_target_mean_workspace) exceeds it return SD_EINVAL: split them over
- * calls.  Every call on one GPU uses the same memory: calls that overlap on
- * one GPU (concurrent streams or threads) race and give undefined results.
+ * only looks up that GPU's copy).  A call is accepted while its rows' own data,
+ * rows (S (4 n_comp + 8) + w n_comp + 12) bytes with S <= 32 (SD_BF16: 8) the
+ * parts that the first product is split in and w = 4 (SD_BF16: 2), fits that
+ * array; more rows return SD_EINVAL: split them over calls.  The kernels' rows
+ * are longer (sd_target_mean_workspace): where those exceed the array the call
+ * takes its rows in parts, one after another on `stream`, with the same results.
+ * Every call on one GPU uses the same memory: calls that overlap on one GPU
+ * (concurrent streams or threads) race and give undefined results.
  * Arguments, layouts and errors otherwise as sd_target_mean. */
 sd_status sd_target_mean_noalloc(sd_target target, int32_t rows, const float* x,
                                  int64_t x_row_stride, const int32_t* step, float* mq,
@@ -395,9 +398,9 @@ sd_status sd_sampler_state(sd_target target, int32_t B, int32_t K, void* ws, siz
  * law the sampler reproduces: Y_0 ~ N(0, I) (INIT stream, as sd_run_sampler)
  * and for n = 0..N-1
  *     Y_{n+1} = m^q_n(Y_n) + sigma_n xi_n,   xi_n: TARGET stream, round n, slot 1,
- * one target call on B rows per step.  y_out [B][d] holds the state during
- * the call and Y_N at the end.  ws: >= sd_plain_em_workspace bytes, 256-byte
- * aligned. */
+ * one target call on B rows per step.  y_out [B][d] holds Y_N at the end; before,
+ * it is scratch (the state alternates between it and the workspace).
+ * ws: >= sd_plain_em_workspace bytes, 256-byte aligned. */
 size_t sd_plain_em_workspace(sd_target target, int32_t B);
 sd_status sd_run_plain_em(sd_target target, int32_t B, uint64_t seed, float* y_out, void* ws,
                           size_t ws_bytes, sd_stream stream);

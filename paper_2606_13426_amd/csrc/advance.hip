@@ -188,7 +188,8 @@ hipError_t advance_launch(const Sched& sc, const float4* coef, int B, int K, int
   dim3 grid((ng + per - 1) / per, B);
   const bool vec = (d % 4 == 0) && aligned16(x) && aligned16(sv) && aligned16(mq) && aligned16(y);
   const bool stream = stream_rows(stream_bytes > 0 ? stream_bytes : (int64_t)B * (K + 1) * d * 4);
-  return launch_timed("advance", spread ? advance_kernel<true> : advance_kernel<false>, grid, dim3(kThreads), s, sc, coef, B, K, d, seed,
+  return launch_timed("advance", spread ? advance_kernel<true> : advance_kernel<false>, grid,
+                      dim3(kThreads), s, sc, coef, B, K, d, seed,
                       kcur, rcur, crow_cur, cstep_cur, knext, rnext, crow_next, cstep_next, tau, rmode,
                       rcoef, rsig, x, sv, mq, y, step, sigma, hist, steps, act_next, trace, r,
                       trace_rounds, vec, frozen, stream, gate, chain0, trace_ld > 0 ? trace_ld : B);

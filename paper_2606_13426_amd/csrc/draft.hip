@@ -257,10 +257,10 @@ hipError_t draft_launch(const Sched& sc, int B, int K, int d, const float* y, co
   const bool vec = draft_vec(d, xs, mps, y, x, mp) && aligned16(cs);
   // (both blocks are written: together they decide what the cache can hold)
   const bool stream = stream_rows((int64_t)B * (2 * K + 1) * d * 4);
+  const auto kernel = spread ? draft_kernel<false, true> : draft_kernel<false, false>;
   return timed("draft_block", s, [&] {
-    (spread ? draft_kernel<false, true> : draft_kernel<false, false>)<<<grid, kThreads, 0, s>>>(sc, nullptr, K, d, y, cs, nullptr, nullptr, nullptr, 0, 0,
-                                                  k, rnd, seed, x, xs.chain, xs.row, mp, mps.chain,
-                                                  mps.row, nullptr, vec, stream, gate, 0);
+    kernel<<<grid, kThreads, 0, s>>>(sc, nullptr, K, d, y, cs, nullptr, nullptr, nullptr, 0, 0, k, rnd, seed,
+                                     x, xs.chain, xs.row, mp, mps.chain, mps.row, nullptr, vec, stream, gate, 0);
   });
 }
 
@@ -277,11 +277,10 @@ hipError_t draft_cached_launch(const Sched& sc, const float4* coef, int B, int K
   const bool vec = draft_vec(d, xs, sd_stride{d, d}, y, x, sv) && aligned16(mqprev) &&
                    mqs.chain % 4 == 0 && mqs.row % 4 == 0;
   const bool stream = stream_rows(stream_bytes > 0 ? stream_bytes : (int64_t)B * (K + 1) * d * 4);
+  const auto kernel = spread ? draft_kernel<true, true> : draft_kernel<true, false>;
   return timed("draft_block", s, [&] {
-    (spread ? draft_kernel<true, true> : draft_kernel<true, false>)<<<grid, kThreads, 0, s>>>(sc, coef, K, d, y, nullptr, crow, cstep, mqprev,
-                                                 mqs.chain, mqs.row, k, rnd, seed, x, xs.chain,
-                                                 xs.row, nullptr, 0, 0, sv, vec, stream, gate,
-                                                 chain0);
+    kernel<<<grid, kThreads, 0, s>>>(sc, coef, K, d, y, nullptr, crow, cstep, mqprev, mqs.chain, mqs.row, k, rnd,
+                                     seed, x, xs.chain, xs.row, nullptr, 0, 0, sv, vec, stream, gate, chain0);
   });
 }
 

@@ -17,9 +17,8 @@
 // of 64 and K + 1 < 4 used to take element-wise loads and float32 matrix
 // instructions: 777 rows of 4107 x 100 components logits 27.8 -> 16.7 us, mean
 // 26.7 -> 18.7; a round's 2304 rows of 784 x 100 logits 15.5 -> 12.7, mean
-// 21.4 -> 14.0.  The partial logits and P have rows of Mp = M
-// rounded up to 64 components (P is zero past M), so every shape takes the
-// same kernels.
+// 21.4 -> 14.0.  The partial logits and P have rows of Mp = M rounded up to 64
+// components (P is zero past M), so every shape takes the same kernels.
 #include <type_traits>
 
 #include "common.hpp"
@@ -366,9 +365,9 @@ __global__ __launch_bounds__(kThreads) void gmm_mean_split_kernel(
 // (one extra load for the last), and the rows meet at most two chains (two
 // cache-row loads: four rows from a multiple of four on, for every K + 1 >= 2);
 // the per-row sums are reduced over the 16 lanes of a row (rowsum.hpp).
-// Columns past d read x, the cache and their products as zero and add nothing.  m^q is stored non-temporally: of a chain's
-// K + 1 rows the round reads back two (the residual's mean and the next cache
-// row).  Products on the bf16 matrix cores as in gmm_mean_split_kernel.
+// Columns past d read x, the cache and their products as zero and add nothing.
+// m^q is stored non-temporally: of a chain's K + 1 rows the round reads back two
+// (the residual's mean and the next cache row).  Products on the bf16 matrix cores as in gmm_mean_split_kernel.
 template <int EDGE, split::Sum SUM>
 __global__ __launch_bounds__(kThreads) void gmm_mean_lr_kernel(
     int R, int Mp, int Mk, int d, int K1, const float* __restrict__ P,
@@ -541,11 +540,13 @@ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // Split of the logits GEMM over d: the number of k-chunks per split and the
 // number of splits (at most 64: a lane of the softmax each) minimise the time of
 // the critical path, (rounds of workgroups over 512 slots, two per compute unit)
-// x (chunks per workgroup) x 2.4 us a chunk (twice that where rows of X are not
-// 16-byte aligned), plus that of the partials, written and read at 2.7 TB/s; both
-// rates from one and two chunks a workgroup at 2304 rows of 784 (two: logits 12.7
-// -> 11.4, softmax 6.8 -> 5.2 us) and two and three at 777 rows of 4107 (two is
-// better: 16.0 + 6.1 against 19.1 + 4.6 us).
+// x (chunks per workgroup) x 2.4 us a chunk (twice that where no row of X but the
+// first is 16-byte aligned), plus that of the partials, written and read at 2.7
+// TB/s.  Both rates come from two shapes: one and two chunks a workgroup at 2304
+// rows of 784 (two: logits 12.7 -> 11.4, softmax 6.8 -> 5.2 us) and two and three
+// at 777 rows of 4107 (two is better: 16.0 + 6.1 against 19.1 + 4.6 us).  The
+// alignment is judged by d, which is what the workspace query knows: rows of a
+// longer stride, or from an odd address, are priced as those of d are.
 // measure: the workspace by which calls on the fixed scratch are accepted, rows
 // of M components and splits chosen by the critical path among at most 32.
 // Buffers for R rows; the split is chosen for plan_rows rows (0: R).

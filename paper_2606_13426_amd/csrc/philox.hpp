@@ -60,8 +60,10 @@ __device__ __forceinline__ double uniform64(uint32_t w) {
 // v (0 or 2^-25 either way) is exact by the two subtractions, and ln u = ln v +
 // e/v, where e/v = e (1 + s + s^2) with s = 1 - v: e is not 0 only for v in
 // [1/2, 1], where that is within 2^-27 of it.  v is a normal number below or at
-// 1, so the hardware logarithm (base 2, about 1 ulp) needs no scaling, and its
-// product with ln 2 carries the constant's and the product's low parts.
+// 1, so the hardware logarithm (base 2, about 1 ulp) needs no scaling.  Its product
+// with ln 2 is compensated in the standard way: the constant in two floats (ln 2
+// rounded, and what the rounding left), the product's own rounding error from a
+// fused multiply-add (Dekker's product; Numer. Math. 18 (1971)).
 __device__ __forceinline__ float neg2log_u24(uint32_t w) {
   constexpr float kHi = -2.0f * 0x1.62e42ep-1f, kLo = -2.0f * 0x1.efa39ep-25f;  // -2 ln 2
   const float m = (float)(w >> 8) * 0x1p-24f;
