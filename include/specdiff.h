@@ -106,8 +106,8 @@ sd_status sd_schedule_table(const sd_schedule* sched, double* host_out);
  * d >= 1, 1 <= n_comp <= 1024.  precision selects the GEMM operand type:
  * SD_FP32 multiplies float32 operands to float32 accuracy (as six bf16 products
  * of exact three-term bf16 splits of each operand, eight in the second product
- * where d or n_comp is no multiple of 64; the dropped terms are below 2^-23,
- * with eight 2^-32, of |a b|), accumulated in float32; SD_BF16 stores mu as bf16
+ * where n_comp, or d in the sampler, is no multiple of 64; the dropped terms are
+ * below 2^-23, with eight 2^-32, of |a b|), accumulated in float32; SD_BF16 stores mu as bf16
  * (round to nearest even) and rounds x and the softmax weights to bf16 before
  * the two products, accumulating in float32 (||x||^2, ||mu||^2 and the softmax
  * stay float64 from the float32 values, ||x||^2 on the widest logits tiles as a

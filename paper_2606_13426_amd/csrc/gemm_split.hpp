@@ -192,13 +192,15 @@ __device__ __forceinline__ bf16x8 frag(const uint16_t* p) {
 //   APART_ALL  the same with mid.lo and lo.mid (what is left out is below 2^-32).
 // In a contraction of few terms six roundings show beside the one or two of a
 // float32 instruction (error of a score against 64 bits, 2 x 191 components:
-// 8.1e-7 there, 4.7e-7 apart; 4 x 20: 5.6e-7, 4.5e-7), so APART serves d or M
-// that are no multiple of 64.  Where one component has all of a row's weight its
-// mean GEMM is a single product, and dropping two terms of it adds to its one
+// 8.1e-7 there, 4.7e-7 apart; 4 x 20: 5.6e-7, 4.5e-7), so APART serves the logits
+// where d or M is no multiple of 64.  Where one component has all of a row's weight
+// its mean GEMM is a single product, and dropping two terms of it adds to its one
 // rounding: score errors of up to 1.008 times a float32 instruction's over 70
 // ragged shapes (448 x 1 component, 2168 x 88), 1.000 with all of them, hence
-// APART_ALL there.  Whole multiples of 64 keep the chain: the extra registers
-// take a wavefront per SIMD (a sampler call of 1024 x 3072 846 us against 816).
+// APART_ALL for the mean GEMMs that once took float32 instructions (M no multiple
+// of 64; in the sampler's, d too).  The others keep the chain they had: the extra
+// registers take a wavefront per SIMD (a sampler call of 1024 x 3072 846 us against
+// 816).
 enum Sum { CHAIN, APART, APART_ALL };
 template <int RB, Sum SUM>
 __device__ __forceinline__ void mma_chunk(const uint16_t* lds, const AChunk (&a)[RB], Acc (&acc)[RB]) {
