@@ -135,8 +135,9 @@ __global__ __launch_bounds__(kThreads, 2) void gmm_logits_split_kernel(
     const int row = r0 + split::out_row<kSplitRB>(r);
     if (row >= R) continue;
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
-      *reinterpret_cast<split::f32x4*>(&ps[(int64_t)row * Mp + c0 + split::out_col(b)]) = acc[r].c[b];
+    for (int b = 0; b < 4; ++b)  // (columns past M are not read)
+      if (c0 + split::out_col(b) < M)
+        *reinterpret_cast<split::f32x4*>(&ps[(int64_t)row * Mp + c0 + split::out_col(b)]) = acc[r].c[b];
   }
   if (want_sq) {
     // the four lanes of a row are l % 16 + 16 q
@@ -164,28 +165,30 @@ __global__ __launch_bounds__(kThreads, 2) void gmm_logits_split_kernel(
 // the components 4 l .. 4 l + 3 of its wavefront (all in flight together), and
 // a reduce-scatter over q leaves each lane one component.  Otherwise, where
 // the wavefronts' own instructions are the limit, a lane keeps all splits of
-// four components and a wavefront takes 256.  NW wavefronts hold a row; every
-// input that does not hang on the step is requested at the start; lane l < S
-// sums ||x||^2.  The maximum is a float64 one: rounded to float32 it would be off
-// by more than the exponential's range from logits of about 2e9 on (a row far from
-// the data at a late step), and infinite from 3e38 on.
+// four components and a wavefront takes 256 of a row, or PACK rows of up to 256 /
+// PACK.  NW wavefronts hold a row; every input that does not hang on the step is
+// requested at the start; the row's lanes sum ||x||^2, a split each.  The maximum
+// is a float64 one: rounded to float32 it would be off by more than the
+// exponential's range from logits of about 2e9 on (a row far from the data at a
+// late step), and infinite from 3e38 on.
 // Per launch (rocprofv3), against one kernel of four components per lane with
 // LDS-permute reductions and the splits summed serially: 64 rows x 64
-// components of 24 splits 12.3 -> 4.7 us, 72 rows 11.9 -> 4.7, 4608 rows 11.9
-// -> 9.3, 777 rows x 100 8.8 -> 5.7, 2304 x 1024 (66 MB of partials) 18.5 ->
-// 18.0.
-template <int NW, bool SPREAD, class TP>
+// components of 24 splits 12.3 -> 4.7 us, 72 rows 11.9 -> 4.7, 777 rows x 100
+// 8.8 -> 5.7, 2304 x 1024 (66 MB of partials) 18.5 -> 18.0.
+template <int NW, bool SPREAD, int PACK, class TP>
 __global__ __launch_bounds__(NW > 4 ? 64 * NW : kThreads) void gmm_softmax_kernel(
     int R, int M, int Mp, int d, int S, const float* __restrict__ part, const double* __restrict__ xsq,
     const int32_t* __restrict__ step, const double* __restrict__ sig, const double2* __restrict__ ls,
     const double* __restrict__ logw, const double* __restrict__ musq, const float4* __restrict__ coef,
     TP* __restrict__ P, float* __restrict__ rowc, const int* gate) {
-  constexpr int kT = NW > 4 ? 64 * NW : kThreads, RPW = kT / (64 * NW);
+  static_assert(PACK == 1 || (NW == 1 && !SPREAD), "rows share a wavefront that holds whole rows");
+  constexpr int kT = NW > 4 ? 64 * NW : kThreads, RPW = PACK * kT / (64 * NW);
   constexpr int NC = SPREAD ? 1 : 4, DS = SPREAD ? 4 : 1;  // components per lane, split stride
-  const int lane = threadIdx.x & 63, w = (threadIdx.x >> 6) % NW;
-  const int row = blockIdx.x * RPW + (int)(threadIdx.x >> 6) / NW;
+  constexpr int LR = 64 / PACK;                            // lanes of a wavefront that hold a row
+  const int lane = threadIdx.x & (LR - 1), w = (threadIdx.x >> 6) % NW;
+  const int row = blockIdx.x * RPW + (int)(threadIdx.x / (LR * NW));
   const bool on = row < R;
-  const int rr = on ? row : R - 1;  // wavefronts of a missing row follow the last one (no stores)
+  const int rr = on ? row : R - 1;  // lanes of a missing row follow the last one (no stores)
   const int live = gate ? *gate : 1;
   const int n = step[rr];
   const int q = SPREAD ? lane >> 4 : 0, l = SPREAD ? lane & 15 : lane;
@@ -199,11 +202,16 @@ __global__ __launch_bounds__(NW > 4 ? 64 * NW : kThreads) void gmm_softmax_kerne
     lw[c] = logw[mc];
     mq2[c] = musq[mc];
   }
-  // (at most 64 splits: one lane each)
-  const double xl = xsq[(int64_t)min(lane, S - 1) * R + rr];
-  double xs = lane < S ? xl : 0.0;
+  // (at most 64 splits: one lane each, or PACK)
+  double xs = 0.0;
+#pragma unroll
+  for (int u = 0; u < PACK; ++u) {
+    const int sp = lane + u * LR;
+    const double xl = xsq[(int64_t)min(sp, S - 1) * R + rr];
+    xs += sp < S ? xl : 0.0;
+  }
   double dot[4] = {0.0, 0.0, 0.0, 0.0};
-  if (m0 < Mp) {
+  if (m0 < M) {
     const float* pr = part + (int64_t)rr * Mp + m0;
     // a batch of splits' loads together (a missing one repeats the last)
     auto sum = [&](auto batch) {
@@ -232,7 +240,7 @@ __global__ __launch_bounds__(NW > 4 ? 64 * NW : kThreads) void gmm_softmax_kerne
   for (int c = 0; c < NC; ++c) t[c] = ls[(int64_t)n * M + min(m + c, M - 1)];
   const float4 cf = coef[n];
   if (live == 0) return;
-  xs = wave_sum(xs);
+  xs = group_sum(xs, LR);
   if constexpr (SPREAD) {
     const double d02 = swap_add<true>(dot[0], dot[2]), d13 = swap_add<true>(dot[1], dot[3]);
     dot[0] = swap_add<false>(d02, d13);
@@ -246,7 +254,7 @@ __global__ __launch_bounds__(NW > 4 ? 64 * NW : kThreads) void gmm_softmax_kerne
   }
   __shared__ double redm[kT / 64];
   __shared__ double2 reds[kT / 64];
-  mx = wave_max(mx);
+  mx = group_max(mx, LR);
   const int w0 = (int)(threadIdx.x >> 6) - w;  // the row's first wavefront
   if constexpr (NW > 1) {
     if (lane == 0) redm[w0 + w] = mx;
@@ -262,8 +270,8 @@ __global__ __launch_bounds__(NW > 4 ? 64 * NW : kThreads) void gmm_softmax_kerne
     sum += (double)e[c];
     sis += (double)e[c] * t[c].y;
   }
-  sum = wave_sum(sum);
-  sis = wave_sum(sis);
+  sum = group_sum(sum, LR);
+  sis = group_sum(sis, LR);
   if constexpr (NW > 1) {
     if (lane == 0) reds[w0 + w] = make_double2(sum, sis);
     __syncthreads();
@@ -620,34 +628,46 @@ size_t target_ws_bytes_unpadded(const Target& t, int rows) {
 hipError_t gmm_softmax_launch(const Target& t, int R, int plan_rows, int S, const float* part, const double* xsq,
                               const int32_t* step, void* P, bool p_bf16, float* rowc,
                               hipStream_t s, const int* gate) {
-  auto launch = [&](auto nw, auto spread) {
-    constexpr int NW = decltype(nw)::value;
+  auto launch = [&](auto nw, auto spread, auto pack) {
+    constexpr int NW = decltype(nw)::value, PACK = decltype(pack)::value;
     constexpr bool SP = decltype(spread)::value;
-    constexpr int kT = NW > 4 ? 64 * NW : kThreads, RPW = kT / (64 * NW);
+    constexpr int kT = NW > 4 ? 64 * NW : kThreads, RPW = PACK * kT / (64 * NW);
     auto go = [&](auto kernel, auto* p) {
       return launch_timed("gmm_softmax", kernel, dim3((R + RPW - 1) / RPW), dim3(kT), s, R, t.M, t.Mp, t.d, S,
                           part, xsq, step, t.sig, t.ls, t.logw, t.musq, t.coef, p, rowc, gate);
     };
-    if (p_bf16) return go(gmm_softmax_kernel<NW, SP, uint16_t>, static_cast<uint16_t*>(P));
-    return go(gmm_softmax_kernel<NW, SP, float>, static_cast<float*>(P));
+    if (p_bf16) return go(gmm_softmax_kernel<NW, SP, PACK, uint16_t>, static_cast<uint16_t*>(P));
+    return go(gmm_softmax_kernel<NW, SP, PACK, float>, static_cast<float*>(P));
   };
-  // Spread rows while their wavefronts are at most eight per SIMD (a latency);
-  // beyond, four components per lane
-  // (2304 x 1024: 18.0 us against 29.7 spread; 4352 x 256: 26.3 against 30.1).  plan_rows, not R,
-  // decides, so that a part of a batch sums as the whole does.
+  // Spread rows while their wavefronts are fewer than four per SIMD (a latency);
+  // from there on four components per lane, four or two rows in a wavefront where
+  // they fit one (us spread / here, by HIP events):
+  //   M = 4     8192 rows  7.5 / 6.2    65536 rows 31.1 / 17.2
+  //   M = 64    4096 rows  5.9 / 5.2     9216 rows  7.0 / 6.2   65536 rows 30.8 / 16.0
+  //   M = 100   2048 rows  6.3 / 4.9    16384 rows 18.7 / 10.7
+  //   M = 256   1024 rows  5.1 / 5.4     2048 rows  8.0 / 5.9    4352 rows 30.1 / 26.3 (bf16)
+  //   M = 1000   128 rows  4.1 / 4.0      384 rows  7.6 / 4.4    2304 rows 29.7 / 18.0 (bf16, M = 1024)
+  // plan_rows, not R, decides, so that a part of a batch sums as the whole does.
   const int64_t waves = (int64_t)plan_rows * ((t.M + 63) / 64);
   const std::true_type sp{};
   const std::false_type wide{};
-  if (t.M <= 64) return launch(std::integral_constant<int, 1>{}, sp);
-  if (t.M <= 128) return launch(std::integral_constant<int, 2>{}, sp);
-  if (waves > 8192) {
-    if (t.M <= 256) return launch(std::integral_constant<int, 1>{}, wide);
-    if (t.M <= 512) return launch(std::integral_constant<int, 2>{}, wide);
-    return launch(std::integral_constant<int, 4>{}, wide);
+  constexpr std::integral_constant<int, 1> k1{};
+  constexpr std::integral_constant<int, 2> k2{};
+  constexpr std::integral_constant<int, 4> k4{};
+  constexpr std::integral_constant<int, 8> k8{};
+  constexpr std::integral_constant<int, 16> k16{};
+  if (waves >= 4096) {
+    if (t.M <= 64) return launch(k1, wide, k4);
+    if (t.M <= 128) return launch(k1, wide, k2);
+    if (t.M <= 256) return launch(k1, wide, k1);
+    if (t.M <= 512) return launch(k2, wide, k1);
+    return launch(k4, wide, k1);
   }
-  if (t.M <= 256) return launch(std::integral_constant<int, 4>{}, sp);
-  if (t.M <= 512) return launch(std::integral_constant<int, 8>{}, sp);
-  return launch(std::integral_constant<int, 16>{}, sp);
+  if (t.M <= 64) return launch(k1, sp, k1);
+  if (t.M <= 128) return launch(k2, sp, k1);
+  if (t.M <= 256) return launch(k4, sp, k1);
+  if (t.M <= 512) return launch(k8, sp, k1);
+  return launch(k16, sp, k1);
 }
 
 hipError_t target_mean_launch(const Target& t, int R, const float* x, int64_t ldx,

@@ -69,16 +69,6 @@ __device__ __forceinline__ double swap_max(double v) {
   return fmax(v, w);
 }
 
-// Sum over the wavefront, in every lane.
-__device__ __forceinline__ double wave_sum(double v) {
-  v += dpp<kDppXor1>(v);
-  v += dpp<kDppXor2>(v);
-  v += dpp<kDppHalfMirror>(v);
-  v += dpp<kDppMirror>(v);
-  v = swap_add<false>(v, v);
-  return swap_add<true>(v, v);
-}
-
 // Sum over each aligned group of n lanes (a power of two from 4 to 64, the same
 // in the whole wavefront), in every lane of it.
 __device__ __forceinline__ double group_sum(double v, int n) {
@@ -90,15 +80,17 @@ __device__ __forceinline__ double group_sum(double v, int n) {
   if (n >= 64) v = swap_add<true>(v, v);
   return v;
 }
+__device__ __forceinline__ double wave_sum(double v) { return group_sum(v, 64); }
 
-// Maximum over the wavefront, in every lane.
-__device__ __forceinline__ double wave_max(double v) {
+// Maximum over each such group.
+__device__ __forceinline__ double group_max(double v, int n) {
   v = fmax(v, dpp<kDppXor1>(v));
   v = fmax(v, dpp<kDppXor2>(v));
-  v = fmax(v, dpp<kDppHalfMirror>(v));
-  v = fmax(v, dpp<kDppMirror>(v));
-  v = swap_max<false>(v);
-  return swap_max<true>(v);
+  if (n >= 8) v = fmax(v, dpp<kDppHalfMirror>(v));
+  if (n >= 16) v = fmax(v, dpp<kDppMirror>(v));
+  if (n >= 32) v = swap_max<false>(v);
+  if (n >= 64) v = swap_max<true>(v);
+  return v;
 }
 
 }  // namespace sd

@@ -33,8 +33,10 @@ def _reference(p, sched, x, step, bf16):
 
 
 # every way a row is held: one to sixteen wavefronts of one component a lane, and
-# (from 8192 wavefronts on) one, two and four of four components
-@pytest.mark.parametrize("M,rows", [(5, 70), (100, 33), (200, 40), (400, 40), (1000, 40), (130, 2740), (300, 1700), (600, 850)])
+# (from 4096 wavefronts on) a quarter and a half of a wavefront, one, two and four of
+# four components; last workgroups that are not full
+@pytest.mark.parametrize("M,rows", [(5, 70), (100, 33), (200, 40), (400, 40), (1000, 40), (5, 4101), (64, 4096), (65, 2050),
+                                    (100, 2049), (130, 1367), (300, 831), (600, 427)])
 @pytest.mark.parametrize("scale", [3.0, 5e3, 6e4, 1e20])
 @pytest.mark.parametrize("bf16", [False, True])
 def test_logits_far_from_zero(M, rows, scale, bf16):
