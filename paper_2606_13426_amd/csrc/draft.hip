@@ -72,8 +72,9 @@ __global__ __launch_bounds__(kThreads) void sampler_init_kernel(
 // of row crow of the previous round (step cstep), so
 //   c2_n S_c = (c2_n / c2_c) (m^q_c - c1_c x_c),
 // read from the same x / mq buffers before this chain's rows are overwritten
-// (each thread reads and then writes only its own coordinates).
-template <bool CACHE_FROM_MEANS, bool SPREAD>
+// (each thread reads and then writes only its own coordinates).  SINGLE: blocks of
+// one row (draft_single).
+template <bool CACHE_FROM_MEANS, bool SPREAD, bool SINGLE = false>
 __global__ __launch_bounds__(kThreads) void draft_kernel(
     Sched sc, const float4* __restrict__ coef, int K, int d, const float* __restrict__ y,
     const float* __restrict__ cs,
@@ -91,8 +92,10 @@ __global__ __launch_bounds__(kThreads) void draft_kernel(
   const int kb = min(K, sc.N - k);
   const uint32_t r = rnd[b];
   const float4 cc = CACHE_FROM_MEANS ? step_coef(sc, coef, cstep[b]) : make_float4(0.f, 0.f, 0.f, 1.0f);
-  draft_coefs(sc, coef, k, kb, cc.w, cfs);
-  if (!SPREAD) __syncthreads();
+  if constexpr (!SINGLE) {
+    draft_coefs(sc, coef, k, kb, cc.w, cfs);
+    if (!SPREAD) __syncthreads();
+  }
   // SPREAD: the four wavefronts share 64 groups (draft_rows_spread); what is
   // written once, the first one writes
   const bool first = !SPREAD || threadIdx.x < 64;
@@ -122,6 +125,10 @@ __global__ __launch_bounds__(kThreads) void draft_kernel(
     for (int c = 0; c < 4; ++c) y0[c] = yv[c];
     draft_rows_spread(cfs, zs, K, kb, (uint32_t)(chain0 + b), r, seed, g, yv, sv, xb, xr, mb, mr, cnt, vec, stream);
     if (first) store4(xb, cnt, vec, y0, stream);
+  } else if constexpr (SINGLE) {
+    store4(xb, cnt, vec, yv, stream);
+    draft_single(step_coef(sc, coef, k), cc.w, (uint32_t)(chain0 + b), r, seed, g, yv, sv, xb + xr, mb,
+                 cnt, vec, stream);
   } else {
     store4(xb, cnt, vec, yv, stream);
     draft_rows(cfs, K, kb, (uint32_t)(chain0 + b), r, seed, g, yv, sv, xb, xr, mb, mr, cnt, vec, stream);
@@ -257,7 +264,9 @@ hipError_t draft_launch(const Sched& sc, int B, int K, int d, const float* y, co
   const bool vec = draft_vec(d, xs, mps, y, x, mp) && aligned16(cs);
   // (both blocks are written: together they decide what the cache can hold)
   const bool stream = stream_rows((int64_t)B * (2 * K + 1) * d * 4);
-  const auto kernel = spread ? draft_kernel<false, true> : draft_kernel<false, false>;
+  const auto kernel = spread   ? draft_kernel<false, true>
+                      : K == 1 ? draft_kernel<false, false, true>
+                               : draft_kernel<false, false>;
   return timed("draft_block", s, [&] {
     kernel<<<grid, kThreads, 0, s>>>(sc, nullptr, K, d, y, cs, nullptr, nullptr, nullptr, 0, 0, k, rnd, seed,
                                      x, xs.chain, xs.row, mp, mps.chain, mps.row, nullptr, vec, stream, gate, 0);

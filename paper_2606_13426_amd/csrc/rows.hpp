@@ -106,6 +106,24 @@ __device__ __forceinline__ void draft_rows(const float4* lds, int K, int kb, uin
   }
 }
 
+// The draft row of a block of one (K = 1), whose coefficients each thread evaluates:
+// shared through LDS they cost the barrier and save nothing (60000 blocks of 1 x 16:
+// 40.0 -> 31.4 us a call, 35.0 with the coefficients of every row on each thread).
+__device__ __forceinline__ void draft_single(float4 cf, float scale, uint32_t chain, uint32_t rnd, uint64_t seed,
+                                             int g, const float (&yv)[4], const float (&sv)[4], float* x1,
+                                             float* mb, int cnt, bool vec, bool stream) {
+  const float4 z = normals4(philox((uint32_t)g, chain, rnd, (TAG_DRAFT << 24) | 1u, seed));
+  const float c2 = cf.y * scale;
+  float m[4], y[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    m[c] = draft_mean(cf.x, yv[c], c2, sv[c]);
+    y[c] = m[c] + cf.z * get4(z, c);
+  }
+  if (mb) store4(mb, cnt, vec, m, stream);
+  store4(x1, cnt, vec, y, stream);
+}
+
 // Draft rows of few chains, by a workgroup of four wavefronts over the same 64
 // groups of coordinates (g, one per lane): a launch of fewer wavefronts than
 // SIMDs takes as long as one thread's serial draws, so each wavefront draws the

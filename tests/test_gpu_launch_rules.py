@@ -50,6 +50,22 @@ def test_spread_draft_equals_one_thread_per_group(K, d, off, pad):
             assert torch.equal(a, b[:B])
 
 
+# blocks of one row take a kernel of their own: the first row of blocks of two, whose
+# chains here are too many to be spread
+@pytest.mark.parametrize("d", [1, 4, 63, 256, 1030])
+@pytest.mark.parametrize("off,pad", [(0, 0), (1, 3), (4, 4)])
+def test_single_draft_is_the_first_of_two(d, off, pad):
+    B = 1024 // ((d + 255) // 256) + 1
+    g = torch.Generator(device=DEV)
+    g.manual_seed(d)
+    y, cs = (torch.randn(B, d, generator=g, device=DEV) for _ in range(2))
+    k = torch.randint(0, 92, (B,), generator=g, device=DEV, dtype=torch.int32)  # some chains are done
+    rnd = torch.randint(0, 99, (B,), generator=g, device=DEV, dtype=torch.int32)
+    x1, m1 = _draft(B, 1, d, y, cs, k, rnd, off, pad)
+    x2, m2 = _draft(B, 2, d, y, cs, k, rnd, off, pad)
+    assert torch.equal(x1, x2[:, :2]) and torch.equal(m1, m2[:, :1])
+
+
 # 33 to 64 chunks of d on one tile of rows: a workgroup each; 65: two each
 @pytest.mark.parametrize("d,M,rows", [(2112, 64, 72), (3072, 64, 1), (4096, 70, 128), (4095, 64, 100), (4160, 64, 72), (4161, 3, 20),
                                       # rows that share a wavefront, 12 and 15 splits
