@@ -177,7 +177,7 @@ __global__ __launch_bounds__(kThreads, 2) void gmm_logits_split_kernel(
 // 8.8 -> 5.7, 2304 x 1024 (66 MB of partials) 18.5 -> 18.0.
 template <int NW, bool SPREAD, int PACK, class TP>
 __global__ __launch_bounds__(NW > 4 ? 64 * NW : kThreads) void gmm_softmax_kernel(
-    int R, int M, int Mp, int d, int S, const float* __restrict__ part, const double* __restrict__ xsq,
+    int R, int M, int Mp, int ldp, int d, int S, const float* __restrict__ part, const double* __restrict__ xsq,
     const int32_t* __restrict__ step, const double* __restrict__ sig, const double2* __restrict__ ls,
     const double* __restrict__ logw, const double* __restrict__ musq, const float4* __restrict__ coef,
     TP* __restrict__ P, float* __restrict__ rowc, const int* gate) {
@@ -284,7 +284,7 @@ __global__ __launch_bounds__(NW > 4 ? 64 * NW : kThreads) void gmm_softmax_kerne
     }
   }
   const double inv = 1.0 / sum;
-  if (on && m < Mp) {  // (the weights past M are zero)
+  if (on && m < ldp) {  // (the weights past M are zero)
     TP o[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
@@ -294,7 +294,7 @@ __global__ __launch_bounds__(NW > 4 ? 64 * NW : kThreads) void gmm_softmax_kerne
       else
         o[c] = pm;
     }
-    TP* pp = P + (int64_t)row * Mp + m;
+    TP* pp = P + (int64_t)row * ldp + m;
     if constexpr (NC == 4) {
       struct alignas(4 * sizeof(TP)) Quad { TP v[4]; };
       *reinterpret_cast<Quad*>(pp) = Quad{{o[0], o[1], o[2], o[3]}};
@@ -633,8 +633,8 @@ hipError_t gmm_softmax_launch(const Target& t, int R, int plan_rows, int S, cons
     constexpr bool SP = decltype(spread)::value;
     constexpr int kT = NW > 4 ? 64 * NW : kThreads, RPW = PACK * kT / (64 * NW);
     auto go = [&](auto kernel, auto* p) {
-      return launch_timed("gmm_softmax", kernel, dim3((R + RPW - 1) / RPW), dim3(kT), s, R, t.M, t.Mp, t.d, S,
-                          part, xsq, step, t.sig, t.ls, t.logw, t.musq, t.coef, p, rowc, gate);
+      return launch_timed("gmm_softmax", kernel, dim3((R + RPW - 1) / RPW), dim3(kT), s, R, t.M, t.Mp, p_bf16 ? t.Mk : t.Mp,
+                          t.d, S, part, xsq, step, t.sig, t.ls, t.logw, t.musq, t.coef, p, rowc, gate);
     };
     if (p_bf16) return go(gmm_softmax_kernel<NW, SP, PACK, uint16_t>, static_cast<uint16_t*>(P));
     return go(gmm_softmax_kernel<NW, SP, PACK, float>, static_cast<float*>(P));

@@ -212,7 +212,7 @@ __device__ __forceinline__ float comp(const float4& v, int c) {
 // the plain Euler-Maruyama step (EmStep).
 template <bool VEC, bool EM>
 __global__ __launch_bounds__(kThreads, 2) void gmm_mean_bf16_kernel(
-    int R, int M, int Mp, int Mk, int d, const uint16_t* __restrict__ P,
+    int R, int M, int Mk, int d, const uint16_t* __restrict__ P,
     const uint16_t* __restrict__ muT, const float* __restrict__ X, int64_t ldx, bool vecx,
     const float* __restrict__ rowc, float* __restrict__ mq, int64_t ldq, bool vecq,
     float* __restrict__ score, int64_t lds, bool vecs, const int* gate, EmStep em) {
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(kThreads, 2) void gmm_mean_bf16_kernel(
   f32x16 acc[2][2];
   zero(acc);
   double unused[8];
-  tile<false, VEC>(sm, P, Mp, R, muT, Mk, d, r0, c0, 0, M, acc, unused);
+  tile<false, VEC>(sm, P, Mk, R, muT, Mk, d, r0, c0, 0, M, acc, unused);
   float* stg = reinterpret_cast<float*>(&sm[0]);
   const int cg = threadIdx.x & 15, rg = threadIdx.x >> 4;
 #pragma unroll
@@ -371,7 +371,7 @@ __device__ __forceinline__ void mean_lr_epilogue_vec(
 // formed it (draft_mean; c2_{k+j} / c2_c from the tables and cstep[b]).
 template <bool VEC>
 __global__ __launch_bounds__(kThreads, 2) void gmm_mean_lr_bf16_kernel(
-    int R, int M, int Mp, int Mk, int d, int K1, const uint16_t* __restrict__ P,
+    int R, int M, int Mk, int d, int K1, const uint16_t* __restrict__ P,
     const uint16_t* __restrict__ muT, const float* __restrict__ X, const float* __restrict__ rowc,
     const float* __restrict__ SV, const int32_t* __restrict__ cstep,
     const float4* __restrict__ coef, float* __restrict__ mq, double* __restrict__ lrp, bool vecd,
@@ -393,7 +393,7 @@ __global__ __launch_bounds__(kThreads, 2) void gmm_mean_lr_bf16_kernel(
   // it comes after, so that no early wait stalls the workgroup)
   const int B = R / K1;
   const int csi = cstep[min(r0 / K1 + (int)threadIdx.x, B - 1)];
-  tile<false, VEC>(sm, P, Mp, R, muT, Mk, d, r0, c0, 0, M, acc, unused);
+  tile<false, VEC>(sm, P, Mk, R, muT, Mk, d, r0, c0, 0, M, acc, unused);
   float* stg = reinterpret_cast<float*>(&sm[0]);
   float* gz = reinterpret_cast<float*>(&sm[1]);
   const int cg = threadIdx.x & 15, rg = threadIdx.x >> 4;
@@ -936,7 +936,7 @@ hipError_t target_mean_bf16_launch(const Target& t, int R, const float* x, int64
     constexpr bool EM = decltype(noise)::value;
     return launch_timed(EM ? "em_step_bf16" : "gmm_mean_bf16",
                         t.M % KC == 0 ? gmm_mean_bf16_kernel<true, EM> : gmm_mean_bf16_kernel<false, EM>, g2,
-                        dim3(kThreads), s, R, t.M, t.Mp, t.Mk, t.d, w.P, t.muT16, x, ldx, vecx, w.rowc, mq, ldq,
+                        dim3(kThreads), s, R, t.M, t.Mk, t.d, w.P, t.muT16, x, ldx, vecx, w.rowc, mq, ldq,
                         vecq, score, lds, vecs, gate, em ? *em : EmStep{});
   };
   return em ? go(std::true_type{}) : go(std::false_type{});
@@ -971,7 +971,7 @@ hipError_t target_mean_lr_bf16_launch(const Target& t, int R, int K1, const floa
                    (int64_t)(TM + 2) * t.d * 4 < ((int64_t)1 << 31);
   return launch_timed("gmm_mean_lr_bf16",
                       vec ? gmm_mean_lr_bf16_kernel<true> : gmm_mean_lr_bf16_kernel<false>, g2,
-                      dim3(kThreads), s, R, t.M, t.Mp, t.Mk, t.d, K1, w.P, t.muT16, x, w.rowc, sv, cstep, t.coef,
+                      dim3(kThreads), s, R, t.M, t.Mk, t.d, K1, w.P, t.muT16, x, w.rowc, sv, cstep, t.coef,
                       mq, lrp, vecd, rnd, seed, gate, chain0);
 }
 
