@@ -135,8 +135,8 @@ __global__ __launch_bounds__(kThreads, 2) void gmm_logits_split_kernel(
     const int row = r0 + split::out_row<kSplitRB>(r);
     if (row >= R) continue;
 #pragma unroll
-    for (int b = 0; b < 4; ++b)  // (columns past M are not read)
-      if (c0 + split::out_col(b) < M)
+    for (int b = 0; b < 4; ++b)  // (columns past M are not read; the chain's M is whole)
+      if (SUM == split::CHAIN || c0 + split::out_col(b) < M)
         *reinterpret_cast<split::f32x4*>(&ps[(int64_t)row * Mp + c0 + split::out_col(b)]) = acc[r].c[b];
   }
   if (want_sq) {
@@ -642,11 +642,15 @@ hipError_t gmm_softmax_launch(const Target& t, int R, int plan_rows, int S, cons
   // Spread rows while their wavefronts are fewer than four per SIMD (a latency);
   // from there on four components per lane, four or two rows in a wavefront where
   // they fit one (us spread / here, by HIP events):
-  //   M = 4     8192 rows  7.5 / 6.2    65536 rows 31.1 / 17.2
-  //   M = 64    4096 rows  5.9 / 5.2     9216 rows  7.0 / 6.2   65536 rows 30.8 / 16.0
+  //   M = 4    16384 rows 11.9 / 8.3    65536 rows 31.1 / 17.2
+  //   M = 64    9216 rows  7.0 / 6.2    16384 rows 11.9 / 7.9   65536 rows 30.8 / 16.0
   //   M = 100   2048 rows  6.3 / 4.9    16384 rows 18.7 / 10.7
   //   M = 256   1024 rows  5.1 / 5.4     2048 rows  8.0 / 5.9    4352 rows 30.1 / 26.3 (bf16)
   //   M = 1000   128 rows  4.1 / 4.0      384 rows  7.6 / 4.4    2304 rows 29.7 / 18.0 (bf16, M = 1024)
+  // Rows of up to 64 components, a wavefront each, stay spread up to ten per SIMD: a
+  // launch may be half of the plan (chain groups), and beside the other half's kernels
+  // the wider launch is the better one (a run of 1024 x 9 x 3072, M = 64, in two
+  // groups 27.06 / 27.22 ms).
   // plan_rows, not R, decides, so that a part of a batch sums as the whole does.
   const int64_t waves = (int64_t)plan_rows * ((t.M + 63) / 64);
   const std::true_type sp{};
@@ -656,7 +660,7 @@ hipError_t gmm_softmax_launch(const Target& t, int R, int plan_rows, int S, cons
   constexpr std::integral_constant<int, 4> k4{};
   constexpr std::integral_constant<int, 8> k8{};
   constexpr std::integral_constant<int, 16> k16{};
-  if (waves >= 4096) {
+  if (waves >= (t.M <= 64 ? 10240 : 4096)) {
     if (t.M <= 64) return launch(k1, wide, k4);
     if (t.M <= 128) return launch(k1, wide, k2);
     if (t.M <= 256) return launch(k1, wide, k1);

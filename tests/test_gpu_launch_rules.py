@@ -68,8 +68,8 @@ def test_single_draft_is_the_first_of_two(d, off, pad):
 
 # 33 to 64 chunks of d on one tile of rows: a workgroup each; 65: two each
 @pytest.mark.parametrize("d,M,rows", [(2112, 64, 72), (3072, 64, 1), (4096, 70, 128), (4095, 64, 100), (4160, 64, 72), (4161, 3, 20),
-                                      # rows that share a wavefront, 12 and 15 splits
-                                      (3072, 64, 4100), (9000, 100, 2050)])
+                                      # rows that share a wavefront, 6 and 15 splits
+                                      (3072, 64, 10243), (9000, 100, 2050)])
 def test_logits_over_many_splits(d, M, rows):
     N = 50
     p = make_gmm(d, M, mu_std=1.0, var=(0.05, 0.4), dirichlet=1.0, seed=d)

@@ -33,9 +33,9 @@ def _reference(p, sched, x, step, bf16):
 
 
 # every way a row is held: one to sixteen wavefronts of one component a lane, and
-# (from 4096 wavefronts on) a quarter and a half of a wavefront, one, two and four of
-# four components; last workgroups that are not full
-@pytest.mark.parametrize("M,rows", [(5, 70), (100, 33), (200, 40), (400, 40), (1000, 40), (5, 4101), (64, 4096), (65, 2050),
+# (from 4096 wavefronts on, 10240 of up to 64 components) a quarter and a half of a
+# wavefront, one, two and four of four components; last workgroups that are not full
+@pytest.mark.parametrize("M,rows", [(5, 70), (100, 33), (200, 40), (400, 40), (1000, 40), (5, 10245), (64, 10240), (65, 2050),
                                     (100, 2049), (130, 1367), (300, 831), (600, 427)])
 @pytest.mark.parametrize("scale", [3.0, 5e3, 6e4, 1e20])
 @pytest.mark.parametrize("bf16", [False, True])
