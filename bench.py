@@ -45,14 +45,14 @@ METRIC = "verified chain-steps/sec + mean accepted steps per block; % MFMA / HBM
 PROFILE_EVERY = 4  # the timed runs' event sample of the dominant kernel's launches
 
 MEASURED_TRAFFIC = {
-    ("verify12288", "logratio_reduce"): dict(bytes=(19344.1 + 8.5) * 1e6, unit="verify.hip",
-                                             sources="7cb5cb276a21be1edb5612e45820ec882473a651"),
+    ("verify12288", "logratio_reduce"): dict(bytes=(19344.6 + 8.4) * 1e6, unit="verify.hip",
+                                             sources="3f0f064327e4c01bb031aa9d3e9bba19656910ea"),
     ("pixel3072", "gmm_mean_lr"): dict(bytes=(136.1 + 122.0) * 1e6, unit="gmm.hip",
-                                       sources="1d9832fb95c336178846c2f8d069c8aad7d8558d"),
-    ("latent16384", "gmm_mean_lr_bf16"): dict(bytes=(277.7 + 154.0) * 1e6, unit="gmm_bf16.hip",
-                                              sources="bc618f4030c65b9b569657e8f3ca128e666ddf1e"),
-    ("pixel12288", "gmm_mean_lr_bf16"): dict(bytes=(511.7 + 445.9) * 1e6, unit="gmm_bf16.hip",
-                                             sources="bc618f4030c65b9b569657e8f3ca128e666ddf1e"),
+                                       sources="91a68d6e3fad29f28b7f426ca96bcc5af6918801"),
+    ("latent16384", "gmm_mean_lr_bf16"): dict(bytes=(277.8 + 154.0) * 1e6, unit="gmm_bf16.hip",
+                                              sources="9651433925626325d7ee8d9e5fc0d503efb0b09d"),
+    ("pixel12288", "gmm_mean_lr_bf16"): dict(bytes=(513.4 + 446.4) * 1e6, unit="gmm_bf16.hip",
+                                             sources="9651433925626325d7ee8d9e5fc0d503efb0b09d"),
 }
 
 

@@ -16,8 +16,8 @@
 // padded to 16 bytes).  Rows that were not 16-byte aligned, d or M no multiple
 // of 64 and K + 1 < 4 used to take element-wise loads and float32 matrix
 // instructions: 777 rows of 4107 x 100 components logits 27.8 -> 16.7 us, mean
-// 26.7 -> 18.7; a round's 2304 rows of 784 x 100 logits 15.5 -> 12.7, mean
-// 21.4 -> 14.0.  The partial logits and P have rows of Mp = M rounded up to 64
+// 26.7 -> 19.2; a round's 2304 rows of 784 x 100 logits 15.5 -> 10.5, mean
+// 21.4 -> 15.0.  The partial logits and P have rows of Mp = M rounded up to 64
 // components (P is zero past M), so every shape takes the same kernels.
 #include <type_traits>
 
